@@ -50,6 +50,8 @@ struct Plan {
   int64_t n_pad;
   int nsplit16;
   // fp32 product
+  bool f32_split;                 // on the matrix cores (kmvm_split.hip) where the inputs' range allows
+  split::Plan f32p;
   int nsplit32;
   int nsplit64;
   int max_basis;
@@ -92,6 +94,9 @@ size_t plan_bytes(Plan& p, bool want_history) {
       add(4 * (size_t)p.nsplit16 * p.n_pad * p.rp);
     add(4 * 64);
     add(4 * 64);
+  } else if (p.f32_split) {
+    b += split::operand_bytes(p.f32p, p.kp.d);
+    add(std::max(split::part_bytes(p.f32p), 4 * (size_t)p.nsplit32 * n * r));
   } else {
     add(4 * (size_t)p.nsplit32 * n * r);
   }
@@ -134,6 +139,9 @@ void plan_carve(Plan& p, Arena& a, bool want_history) {
       p.part16 = a.take<float>((size_t)p.nsplit16 * p.n_pad * p.rp);
     p.scale = a.take<float>(64);
     p.inv_scale = a.take<float>(64);
+  } else if (p.f32_split) {
+    if (split::carve(p.f32p, p.kp.d, a) != GP_OK) return;
+    p.part32 = a.take<float>(std::max(split::part_bytes(p.f32p) / 4, (size_t)p.nsplit32 * n * r));
   } else {
     p.part32 = a.take<float>((size_t)p.nsplit32 * n * r);
   }
@@ -174,6 +182,9 @@ gp_status product(Plan& p, const float* v, float* out, const int* live, hipStrea
     return f16::launch_reduce(p.part16, p.nsplit16, p.n, p.n_pad, p.r, p.rp, p.inv_scale, p.kp.a2,
                               p.kp.s2, v, p.r, out, p.r, live, s);
   }
+  if (p.f32_split)
+    return split::product(p.f32p, p.kp, p.X, p.n, p.X, p.n, v, p.r, p.part32, p.part32, p.nsplit32,
+                          true, out, live, s);
   GP_TRY(valu::launch_partial(p.kp, p.X, p.n, p.X, p.n, v, p.r, p.part32, false, p.nsplit32, live,
                               s));
   return valu::launch_reduce32(p.part32, p.nsplit32, p.n, p.r, p.kp.a2, p.kp.s2, v, out, live, s);
@@ -302,6 +313,8 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
   if (p.sym) p.sp = f16::sym_plan(p.n_pad);
   p.nsplit16 = f16::choose_splits(p.n_pad, p.n_pad);
   p.nsplit32 = valu::choose_splits(n, n, d);
+  p.f32_split = !p.fp16 && split::use(p.kp.kind, n, n, d, r);
+  if (p.f32_split) p.f32p = split::plan(n, n, d, r, true, 64);
   p.nsplit64 = valu::choose_splits64(n, n, d);
   const bool want_history = stats && stats->history;
 
@@ -334,6 +347,8 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
   } else if (p.fp16) {
     GP_TRY(f16::prep_points(X, n, p.n_pad, p.kp, 0, p.Xr, s));
     GP_TRY(f16::prep_points(X, n, p.n_pad, p.kp, 1, p.Xc, s));
+  } else if (p.f32_split) {
+    GP_TRY(split::prepare(p.f32p, p.kp, X, n, X, n, s));
   }
   if (p.o.x0_given) {
     GP_TRY(quantise(p, U, false, nullptr, s));

@@ -196,9 +196,48 @@ static size_t f32_bytes(int64_t n1, int64_t, int r, int, int nsplit) {
   return 4 * (size_t)nsplit * n1 * r + 256;
 }
 
+// Float32 product on the matrix cores; the vector form's sums share the block
+// of the split partials (only one of the two forms runs).  *no_room: a fixed
+// block does not hold the operands.
+static gp_status kmvm_f32_split(const KParams& kp, const float* X1, int64_t n1, const float* X2,
+                                int64_t n2, const float* V, int r, float* out, bool add_noise,
+                                hipStream_t s, const ScratchSource& src, bool* no_room) {
+  const bool same = X1 == X2 && n1 == n2;
+  int vsplit = valu::choose_splits(n1, n2, kp.d);
+  split::Plan p = split::plan(n1, n2, kp.d, r, same, 64);
+  auto need = [&] {
+    return split::operand_bytes(p, kp.d) + 512 +
+           std::max(split::part_bytes(p), f32_bytes(n1, n2, r, 0, vsplit));
+  };
+  size_t bytes = need();
+  *no_room = false;
+  if (src.fixed) {
+    while (bytes > src.fixed_cap && (p.nsplit > 1 || vsplit > 1)) {
+      if (p.nsplit > 1) --p.nsplit;
+      if (vsplit > 1) --vsplit;
+      bytes = need();
+    }
+    *no_room = bytes > src.fixed_cap;
+    if (*no_room) return GP_OK;
+  }
+  Arena ar;
+  GP_TRY(scratch_arena(src, s, bytes, &ar));
+  GP_TRY(split::carve(p, kp.d, ar));
+  float* part = ar.take<float>(std::max((size_t)p.nsplit * p.n1_pad * p.rp, (size_t)vsplit * n1 * r));
+  if (!part) return set_error(GP_ERR_NOMEM, "internal: workspace sizing");
+  GP_TRY(split::prepare(p, kp, X1, n1, X2, n2, s));
+  return split::product(p, kp, X1, n1, X2, n2, V, r, part, part, vsplit, add_noise, out, nullptr,
+                        s);
+}
+
 static gp_status kmvm_f32(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                           int64_t n2, const float* V, int r, float* out, bool add_noise,
                           hipStream_t s, const ScratchSource& src) {
+  if (split::use(kp.kind, n1, n2, kp.d, r)) {
+    bool no_room = false;
+    GP_TRY(kmvm_f32_split(kp, X1, n1, X2, n2, V, r, out, add_noise, s, src, &no_room));
+    if (!no_room) return GP_OK;
+  }
   int nsplit;
   size_t bytes;
   GP_TRY(pick_splits(src, valu::choose_splits(n1, n2, kp.d), f32_bytes, n1, n2, r, 0, &nsplit,

@@ -212,15 +212,66 @@ namespace valu {
 constexpr int kRowsPerBlock = 256;
 constexpr int kStageCols = 64;
 // part is float (acc32) or double (acc64): [nsplit][n1][r]
+// skip: the launch does nothing when *skip != 0 (float32 accumulation only)
 gp_status launch_partial(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                          int64_t n2, const float* V, int r, void* part, bool acc64, int nsplit,
-                         const int* live, hipStream_t s);
+                         const int* live, hipStream_t s, const int* skip = nullptr);
 gp_status launch_reduce32(const float* part, int nsplit, int64_t n1, int r, float a2, float s2,
                           const float* V, float* out, const int* live, hipStream_t s);
 int choose_splits(int64_t n1, int64_t n2, int d);
 // column splits of the float64-accumulated product (true residual)
 int choose_splits64(int64_t n1, int64_t n2, int d);
 }  // namespace valu
+
+// ---------------------------------------------------------------------------
+// Float32 product on the matrix cores (kmvm_split.hip): exact integer products
+// for the distances, entries and right-hand sides in three bfloat16 parts.
+// ---------------------------------------------------------------------------
+namespace split {
+constexpr int kStageCols = 64;         // columns per LDS stage
+constexpr int kSplitMaxDim = 28;       // d + 4 slots of the first 32-wide chunk
+constexpr float kSplitMaxRadius = 32.0f;
+// smallest sets and smallest vector-form work n1 n2 (2 d + r + 12) (operations)
+// that take this form: its four extra launches cost about 20 us, which the
+// vector form's time passes from there on (N = 4000, d = 8, R = 16, work 7e8:
+// 44 us against 41; N = 8000, d = 3, R = 1, work 1.2e9: 48 against 40; 500 x
+// 20000, d = 8, R = 16, work 4e8: 56 against 63)
+constexpr int64_t kSplitMinRows = 256;
+constexpr double kSplitMinWork = 1073741824.0;
+// Scale data of a prepared point set, written on the device.
+struct Info {
+  float cs;                            // exponent scale times u^2
+  int ok;                              // 1: this form runs; 0: the vector form does
+  double inv_u;
+  double centre[kMaxDim];
+};
+__host__ __device__ constexpr int operand_chunks(int d) { return 1 + (5 * d + 6 + 31) / 32; }
+// 16-row subtiles per wave (their operands stay in registers)
+__host__ __device__ constexpr int subtiles(int kc) { return kc <= 3 ? 4 : 2; }
+struct Plan {
+  int kc, rp, nsplit, groups1, groups2;
+  bool same;                           // X1 and X2 are one set
+  int64_t n1_pad, n2_pad;
+  _Float16 *Xr, *Xc;
+  Info* info;
+  float* box;
+};
+// whether a float32 product of these sizes takes this form (the inputs' range
+// is checked on the device)
+bool use(int kind, int64_t n1, int64_t n2, int d, int r);
+Plan plan(int64_t n1, int64_t n2, int d, int r, bool same, int most_splits);
+size_t operand_bytes(const Plan& p, int d);
+size_t part_bytes(const Plan& p);
+gp_status carve(Plan& p, int d, Arena& ar);
+// operands of both sets (once per point set)
+gp_status prepare(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
+                  int64_t n2, hipStream_t s);
+// out = a2 K V (+ s2 V); vpart (vsplit x n1 x r) takes the vector form's sums
+// when the inputs' range rules this form out.
+gp_status product(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
+                  int64_t n2, const float* V, int r, float* part, float* vpart, int vsplit,
+                  bool add_noise, float* out, const int* live, hipStream_t s);
+}  // namespace split
 
 // ---------------------------------------------------------------------------
 // Conjugate-gradient step kernels (a3-a8 of the hot path).

@@ -26,10 +26,12 @@ __global__ __launch_bounds__(256) void kmvm_valu_kernel(const float* __restrict_
                                                         const float* __restrict__ X2, int64_t n2,
                                                         const float* __restrict__ V, int r, int c0,
                                                         KParams kp, AccT* __restrict__ part,
-                                                        int nsplit, const int* __restrict__ live) {
+                                                        int nsplit, const int* __restrict__ live,
+                                                        const int* __restrict__ skip) {
   __shared__ float sX[JT][DM];
   __shared__ AccT sV[JT][RT];
   if (live && *live == 0) return;
+  if (skip && *skip != 0) return;
   const int split = blockIdx.x % nsplit;
   const int64_t row_blk = (int64_t)(blockIdx.x / nsplit) * kRowsPerBlock * RPT;
   const int64_t nstage = ceil_div(n2, JT);
@@ -117,11 +119,11 @@ constexpr int rows_per_thread() {
 template <int KIND, int DM, int RT, int RPT>
 static gp_status launch_rows(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                              int64_t n2, const float* V, int r, void* part, int nsplit,
-                             const int* live, hipStream_t s) {
+                             const int* live, hipStream_t s, const int* skip) {
   const int64_t blocks = ceil_div(n1, (int64_t)kRowsPerBlock * RPT) * nsplit;
   for (int c0 = 0; c0 < r; c0 += RT) {
     kmvm_valu_kernel<KIND, DM, RT, RPT, float><<<(unsigned)blocks, kRowsPerBlock, 0, s>>>(
-        X1, n1, X2, n2, V, r, c0, kp, static_cast<float*>(part), nsplit, live);
+        X1, n1, X2, n2, V, r, c0, kp, static_cast<float*>(part), nsplit, live, skip);
     GP_HIP(hipGetLastError());
   }
   return GP_OK;
@@ -140,41 +142,48 @@ constexpr int64_t kSmallGrid = 256;
 template <int KIND, int DM, int RT>
 static gp_status launch_t(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                           int64_t n2, const float* V, int r, void* part, bool acc64, int nsplit,
-                          const int* live, hipStream_t s) {
+                          const int* live, hipStream_t s, const int* skip) {
   constexpr int RPT = rows_per_thread<DM>();
   (void)acc64;
   if constexpr (RPT > 1) {
     if (ceil_div(n1, (int64_t)kRowsPerBlock * RPT) * nsplit < kSmallGrid)
-      return launch_rows<KIND, DM, RT, 1>(kp, X1, n1, X2, n2, V, r, part, nsplit, live, s);
+      return launch_rows<KIND, DM, RT, 1>(kp, X1, n1, X2, n2, V, r, part, nsplit, live, s, skip);
   }
-  return launch_rows<KIND, DM, RT, RPT>(kp, X1, n1, X2, n2, V, r, part, nsplit, live, s);
+  return launch_rows<KIND, DM, RT, RPT>(kp, X1, n1, X2, n2, V, r, part, nsplit, live, s, skip);
 }
 
 template <int KIND, int DM>
 static gp_status launch_r(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                           int64_t n2, const float* V, int r, void* part, bool acc64, int nsplit,
-                          const int* live, hipStream_t s) {
-  if (r <= 1) return launch_t<KIND, DM, 1>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
-  if (r <= 4) return launch_t<KIND, DM, 4>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
-  if (r <= 8) return launch_t<KIND, DM, 8>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
-  return launch_t<KIND, DM, 16>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
+                          const int* live, hipStream_t s, const int* skip) {
+  if (r <= 1) return launch_t<KIND, DM, 1>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                           skip);
+  if (r <= 4) return launch_t<KIND, DM, 4>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                           skip);
+  if (r <= 8) return launch_t<KIND, DM, 8>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                           skip);
+  return launch_t<KIND, DM, 16>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s, skip);
 }
 
 template <int KIND>
 static gp_status launch_d(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                           int64_t n2, const float* V, int r, void* part, bool acc64, int nsplit,
-                          const int* live, hipStream_t s) {
+                          const int* live, hipStream_t s, const int* skip) {
   const int d = kp.d;
-  if (d <= 4) return launch_r<KIND, 4>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
-  if (d <= 8) return launch_r<KIND, 8>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
-  if (d <= 16) return launch_r<KIND, 16>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
-  if (d <= 32) return launch_r<KIND, 32>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
-  return launch_r<KIND, 64>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
+  if (d <= 4) return launch_r<KIND, 4>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                       skip);
+  if (d <= 8) return launch_r<KIND, 8>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                       skip);
+  if (d <= 16) return launch_r<KIND, 16>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                         skip);
+  if (d <= 32) return launch_r<KIND, 32>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                         skip);
+  return launch_r<KIND, 64>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s, skip);
 }
 
 gp_status launch_partial(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                          int64_t n2, const float* V, int r, void* part, bool acc64, int nsplit,
-                         const int* live, hipStream_t s) {
+                         const int* live, hipStream_t s, const int* skip) {
   if (n1 == 0 || r == 0) return GP_OK;
   if (acc64) {
     double* p64 = static_cast<double*>(part);
@@ -192,13 +201,16 @@ gp_status launch_partial(const KParams& kp, const float* X1, int64_t n1, const f
   }
   switch (kp.kind) {
     case GP_KERNEL_RBF:
-      return launch_d<GP_KERNEL_RBF>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
+      return launch_d<GP_KERNEL_RBF>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s, skip);
     case GP_KERNEL_MATERN52:
-      return launch_d<GP_KERNEL_MATERN52>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
+      return launch_d<GP_KERNEL_MATERN52>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                          skip);
     case GP_KERNEL_MATERN12:
-      return launch_d<GP_KERNEL_MATERN12>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
+      return launch_d<GP_KERNEL_MATERN12>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                          skip);
     case GP_KERNEL_MATERN32:
-      return launch_d<GP_KERNEL_MATERN32>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s);
+      return launch_d<GP_KERNEL_MATERN32>(kp, X1, n1, X2, n2, V, r, part, acc64, nsplit, live, s,
+                                          skip);
   }
   return set_error(GP_ERR_ARG, "unknown kernel kind %d", kp.kind);
 }

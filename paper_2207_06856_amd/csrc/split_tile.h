@@ -1,0 +1,67 @@
+// Squared distances to float32 accuracy on the binary16 matrix cores.
+//
+// With a = (x - c) / l (c the centre of the points' bounding box, float64) and
+// a unit u, a power of two with R / 2000 <= u < R / 1000 for the box's scaled
+// half diagonal R, every coordinate is cut into an integer and a remainder,
+// a / u = q + f with |q| <= 2000 and |f| <= 1/2.  Then
+//   |a_i - a_j|^2 / u^2 = |q_i - q_j|^2 + [2 (q_i - q_j).(f_i - f_j) + |f_i - f_j|^2].
+// The first term is a sum of products of integers that binary16 holds exactly
+// (q, -2q up to 4000 and even, |q|^2 <= 2004^2 as 2048 N1 + N0), and every
+// partial sum is an integer below 2^24: the first 32-wide MFMA forms it with no
+// rounding at all, so nothing is lost to the cancellation in
+// |a_i|^2 + |a_j|^2 - 2 a_i.a_j, which is what keeps a plain float32 (or
+// split) expansion from the accuracy of coordinate differences.  The bracket is
+// smaller by |f| / |q| ~ 2^-11, and the following MFMAs add it from f in two
+// binary16 parts and g = 2 q.f + |f|^2 in three; their float32 roundings are
+// about 2^-11 u^2, i.e. R^2 2^-31 at most in r^2.  Coordinate differences of
+// the float32 x / l carry 2 r |x / l| 2^-25, which is more than that at r ~ 1
+// up to R = kSplitMaxRadius, the limit of this form.
+// Not for Matern-1/2, whose value falls linearly in r at r = 0, where an
+// absolute error of r^2 would be magnified.
+//
+// Operand rows of KC 32-wide chunks (side 0: output rows, side 1: columns):
+//   slot        side 0              side 1
+//   0 .. d-1    q                   -2 q
+//   d .. d+3    1, 2048, N0, N1     N0, N1, 1, 2048
+//   32 + ..     q, q, f1, f2, f1    -2 f1, -2 f2, -2 q, -2 q, -2 f1     (d each)
+//   then        1, 1, 1, g1..g3     g1..g3, 1, 1, 1
+#pragma once
+
+#include "fused_tile.h"
+#include "internal.h"
+
+namespace gpmi {
+namespace split {
+
+using f16::f4;
+using f16::h4;
+using f16::h8;
+
+// r^2 / u^2 of 16 columns (operand fragments a) and 16 rows (b): element v of
+// a lane is column 4 g + v, row l16.
+template <int KC>
+__device__ __forceinline__ f4 sqdist(const h8 (&a)[KC], const h8 (&b)[KC]) {
+  f4 s = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kc = 0; kc < KC; ++kc) s = f16::mfma32<_Float16>(a[kc], b[kc], s);
+  return s;
+}
+
+// float32 kernel value from D = r^2 / u^2 (cs: Info::cs).
+template <int KIND>
+__device__ __forceinline__ float kval(float D, float cs) {
+  constexpr float kLn2f = 0.6931471805599453f;
+  if constexpr (KIND == GP_KERNEL_RBF) {
+    return __builtin_amdgcn_exp2f(D * cs);
+  } else {
+    const float sp = __builtin_amdgcn_sqrtf(fabsf(D * cs));   // distance times log2 e
+    const float e = __builtin_amdgcn_exp2f(-sp);
+    if constexpr (KIND == GP_KERNEL_MATERN32)
+      return fmaf(sp, kLn2f, 1.0f) * e;
+    else
+      return fmaf(sp, fmaf(sp, kLn2f * kLn2f / 3.0f, kLn2f), 1.0f) * e;
+  }
+}
+
+}  // namespace split
+}  // namespace gpmi
