@@ -212,7 +212,7 @@ namespace valu {
 constexpr int kRowsPerBlock = 256;
 constexpr int kStageCols = 64;
 // part is float (acc32) or double (acc64): [nsplit][n1][r]
-// skip: the launch does nothing when *skip != 0 (float32 accumulation only)
+// skip: the launch does nothing when *skip != 0
 gp_status launch_partial(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                          int64_t n2, const float* V, int r, void* part, bool acc64, int nsplit,
                          const int* live, hipStream_t s, const int* skip = nullptr);
@@ -240,7 +240,7 @@ constexpr int64_t kSplitMinRows = 256;
 constexpr double kSplitMinWork = 1073741824.0;
 // Scale data of a prepared point set, written on the device.
 struct Info {
-  float cs;                            // exponent scale times u^2
+  float cs;                            // exponent scale times u^2: a signed power of two
   int ok;                              // 1: this form runs; 0: the vector form does
   double inv_u;
   double centre[kMaxDim];
@@ -271,6 +271,17 @@ gp_status prepare(const Plan& p, const KParams& kp, const float* X1, int64_t n1,
 gp_status product(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
                   int64_t n2, const float* V, int r, float* part, float* vpart, int vsplit,
                   bool add_noise, float* out, const int* live, hipStream_t s);
+// Float64-accumulated sums of one point set (kmvm_split64.hip): part[split][i][c]
+// = sum over the split's columns of k(x_i, x_j) V_jc; the vector form's layout,
+// which it writes itself when the inputs' range rules this form out.
+// from this many points: preparing the operands costs about 20 us, what the
+// cheaper distances save at N = 6000 (R = 5: 64 us against 75 at N = 5000, 459
+// against 168 at N = 20,000, R = 1)
+constexpr int64_t kSplit64MinPoints = 8192;
+bool use64(int kind, int64_t n, int d);
+int choose_splits64(const Plan& p, int r);
+gp_status partial64(const Plan& p, const KParams& kp, const float* X, int64_t n, const float* V,
+                    int r, double* part, int nsplit, hipStream_t s);
 }  // namespace split
 
 // ---------------------------------------------------------------------------

@@ -104,15 +104,16 @@ __global__ __launch_bounds__(256) void info_kernel(const float* __restrict__ par
     double r2 = 0.0;
     for (int k = 0; k < d; ++k) r2 += half2[k];
     const bool ok = r2 <= (double)kSplitMaxRadius * kSplitMaxRadius;   // false for NaN
-    double u = 1.0;
+    // |arg| u^2 is a power of two >= |arg| (R / 2000)^2: the exponent argument
+    // is then an exact multiple of r^2 / u^2
+    int e = -100;
     if (ok && r2 > 0.0) {
-      int e;
-      const double f = frexp(sqrt(r2) / 2000.0, &e);     // f 2^e, f in [1/2, 1)
-      u = ldexp(1.0, f == 0.5 ? e - 1 : e);
-      if (u < 1e-30) u = 1e-30;                          // all points (nearly) equal
+      const double f = frexp(fabs(arg) * r2 / 4e6, &e);  // f 2^e, f in [1/2, 1)
+      if (f == 0.5) --e;
+      if (e < -100) e = -100;                            // all points (nearly) equal
     }
-    o->inv_u = 1.0 / u;
-    o->cs = (float)(arg * u * u);
+    o->inv_u = sqrt(ldexp(fabs(arg), -e));
+    o->cs = copysignf(ldexpf(1.0f, e), (float)arg);
     o->ok = ok ? 1 : 0;
   }
 }
@@ -542,9 +543,14 @@ gp_status carve(Plan& p, int d, Arena& ar) {
 
 gp_status prepare(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
                   int64_t n2, hipStream_t s) {
-  constexpr double kLog2e = 1.4426950408889634074;
-  const double arg = kp.kind == GP_KERNEL_RBF ? -0.5 * kLog2e
-                     : (kp.kind == GP_KERNEL_MATERN52 ? 5.0 : 3.0) * kLog2e * kLog2e;
+  // v_sqrt_f32 falls short of the root by 1.2e-8 of it on average (16M arguments
+  // in [1, 4), worst 9.3e-8), which every entry of a Matern sum would share:
+  // its argument is raised by twice that
+  constexpr double kLog2e = 1.4426950408889634074, kSqrtBias = 1.2e-8;
+  const double arg = kp.kind == GP_KERNEL_RBF
+                         ? -0.5 * kLog2e
+                         : (kp.kind == GP_KERNEL_MATERN52 ? 5.0 : 3.0) * kLog2e * kLog2e *
+                               (1.0 + 2.0 * kSqrtBias);
   box_kernel<<<(unsigned)(p.groups1 + p.groups2), 256, 0, s>>>(X1, n1, X2, n2, kp.d, p.groups1,
                                                                p.box);
   GP_HIP(hipGetLastError());

@@ -52,9 +52,11 @@ __global__ __launch_bounds__(256) void kmvm_f64_kernel(const float* __restrict__
                                                        const float* __restrict__ X2, int64_t n2,
                                                        const float* __restrict__ V, int r, int c0,
                                                        KParams kp, double* __restrict__ part,
-                                                       int nsplit, const int* __restrict__ live) {
+                                                       int nsplit, const int* __restrict__ live,
+                                                       const int* __restrict__ skip) {
   __shared__ Aug64Lds<T> sm;
   if (live && *live == 0) return;
+  if (skip && *skip != 0) return;
   const int split = blockIdx.x % nsplit;
   const int64_t row_blk = (int64_t)(blockIdx.x / nsplit) * aug_rows(T);
   const int64_t nstage = ceil_div(n2, (int64_t)JT64);
@@ -67,11 +69,11 @@ __global__ __launch_bounds__(256) void kmvm_f64_kernel(const float* __restrict__
 template <int KIND, int T>
 static gp_status launch_f64_t(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                               int64_t n2, const float* V, int r, double* part, int nsplit,
-                              const int* live, hipStream_t s) {
+                              const int* live, hipStream_t s, const int* skip) {
   const int64_t blocks = ceil_div(n1, (int64_t)aug_rows(T)) * nsplit;
   for (int c0 = 0; c0 < r; c0 += 16) {
     kmvm_f64_kernel<KIND, T><<<(unsigned)blocks, 256, 0, s>>>(X1, n1, X2, n2, V, r, c0, kp, part,
-                                                              nsplit, live);
+                                                              nsplit, live, skip);
     GP_HIP(hipGetLastError());
   }
   return GP_OK;
@@ -80,9 +82,9 @@ static gp_status launch_f64_t(const KParams& kp, const float* X1, int64_t n1, co
 template <int KIND>
 static gp_status launch_f64(const KParams& kp, const float* X1, int64_t n1, const float* X2,
                             int64_t n2, const float* V, int r, double* part, int nsplit,
-                            const int* live, hipStream_t s) {
+                            const int* live, hipStream_t s, const int* skip) {
 #define GP_F64_CASE(TT) \
-  case TT: return launch_f64_t<KIND, TT>(kp, X1, n1, X2, n2, V, r, part, nsplit, live, s);
+  case TT: return launch_f64_t<KIND, TT>(kp, X1, n1, X2, n2, V, r, part, nsplit, live, s, skip);
   switch (aug_slices_inst(kp.d)) {
     GP_F64_CASE(1) GP_F64_CASE(2) GP_F64_CASE(3) GP_F64_CASE(4) GP_F64_CASE(5) GP_F64_CASE(6)
     GP_F64_CASE(7) GP_F64_CASE(8) GP_F64_CASE(10) GP_F64_CASE(12) GP_F64_CASE(14)
@@ -189,13 +191,13 @@ gp_status launch_partial(const KParams& kp, const float* X1, int64_t n1, const f
     double* p64 = static_cast<double*>(part);
     switch (kp.kind) {
       case GP_KERNEL_RBF:
-        return launch_f64<GP_KERNEL_RBF>(kp, X1, n1, X2, n2, V, r, p64, nsplit, live, s);
+        return launch_f64<GP_KERNEL_RBF>(kp, X1, n1, X2, n2, V, r, p64, nsplit, live, s, skip);
       case GP_KERNEL_MATERN52:
-        return launch_f64<GP_KERNEL_MATERN52>(kp, X1, n1, X2, n2, V, r, p64, nsplit, live, s);
+        return launch_f64<GP_KERNEL_MATERN52>(kp, X1, n1, X2, n2, V, r, p64, nsplit, live, s, skip);
       case GP_KERNEL_MATERN12:
-        return launch_f64<GP_KERNEL_MATERN12>(kp, X1, n1, X2, n2, V, r, p64, nsplit, live, s);
+        return launch_f64<GP_KERNEL_MATERN12>(kp, X1, n1, X2, n2, V, r, p64, nsplit, live, s, skip);
       case GP_KERNEL_MATERN32:
-        return launch_f64<GP_KERNEL_MATERN32>(kp, X1, n1, X2, n2, V, r, p64, nsplit, live, s);
+        return launch_f64<GP_KERNEL_MATERN32>(kp, X1, n1, X2, n2, V, r, p64, nsplit, live, s, skip);
     }
     return set_error(GP_ERR_ARG, "unknown kernel kind %d", kp.kind);
   }

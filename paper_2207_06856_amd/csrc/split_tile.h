@@ -1,8 +1,8 @@
 // Squared distances to float32 accuracy on the binary16 matrix cores.
 //
 // With a = (x - c) / l (c the centre of the points' bounding box, float64) and
-// a unit u, a power of two with R / 2000 <= u < R / 1000 for the box's scaled
-// half diagonal R, every coordinate is cut into an integer and a remainder,
+// a unit u with R / 2000 <= u < R sqrt(2) / 2000 for the box's scaled half
+// diagonal R, every coordinate is cut into an integer and a remainder,
 // a / u = q + f with |q| <= 2000 and |f| <= 1/2.  Then
 //   |a_i - a_j|^2 / u^2 = |q_i - q_j|^2 + [2 (q_i - q_j).(f_i - f_j) + |f_i - f_j|^2].
 // The first term is a sum of products of integers that binary16 holds exactly
@@ -13,9 +13,11 @@
 // split) expansion from the accuracy of coordinate differences.  The bracket is
 // smaller by |f| / |q| ~ 2^-11, and the following MFMAs add it from f in two
 // binary16 parts and g = 2 q.f + |f|^2 in three; their float32 roundings are
-// about 2^-11 u^2, i.e. R^2 2^-31 at most in r^2.  Coordinate differences of
+// about 2^-11 u^2, i.e. R^2 2^-32 at most in r^2.  Coordinate differences of
 // the float32 x / l carry 2 r |x / l| 2^-25, which is more than that at r ~ 1
-// up to R = kSplitMaxRadius, the limit of this form.
+// up to R = kSplitMaxRadius, the limit of this form.  u is chosen so that the
+// scale from r^2 / u^2 to the exponent's argument is a power of two: the
+// argument takes no further rounding, and no constant's.
 // Not for Matern-1/2, whose value falls linearly in r at r = 0, where an
 // absolute error of r^2 would be magnified.
 //
