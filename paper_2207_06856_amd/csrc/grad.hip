@@ -46,6 +46,7 @@
 #include <algorithm>
 
 #include "device_common.h"
+#include "grad_internal.h"
 #include "internal.h"
 
 namespace gpmi {
@@ -57,8 +58,8 @@ typedef float gf4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
 constexpr int kStage = 64;        // columns per LDS stage
-constexpr int kDiagRows = 4096;   // rows per diagonal-term chunk
-constexpr int kColmaxRows = 256;  // rows per column-maximum work group
+constexpr int kDiagRows = 512;    // rows per diagonal-term chunk
+constexpr int kColmaxRows = 512;  // rows per column-maximum work group
 
 // exp(-x) from the hardware exp2 (v_exp_f32): relative error about
 // 1 ulp + x log2(e) 2^-24 ln 2, below 2e-6 for x <= 20 and negligible beside
@@ -107,22 +108,25 @@ __device__ __forceinline__ float cval(const float* __restrict__ U, const float* 
 }
 
 // cmax[c] = max_i |U_ic|, cmax[64 + c] = max_i |C_ic| as float bits (cleared
-// to zero before); one work group per kColmaxRows rows, thread t takes column
-// t % 64 of every fourth row.
+// to zero before); one work group per kColmaxRows rows, whose U and B entries
+// its first 256 / r * r threads read in order, each thread one column.
 __global__ __launch_bounds__(256) void colmax_kernel(const float* __restrict__ U,
                                                      const float* __restrict__ B, int64_t n, int r,
                                                      float inv2m, uint32_t* __restrict__ cmax) {
   __shared__ uint32_t sm[2 * 64];
   for (int e = threadIdx.x; e < 2 * 64; e += 256) sm[e] = 0u;
   __syncthreads();
-  const int c = threadIdx.x & 63, rg = threadIdx.x >> 6;
+  const int rows = 256 / r;
+  const int c = threadIdx.x % r, rg = threadIdx.x / r;
   const int64_t c0 = (int64_t)blockIdx.x * kColmaxRows;
   const int64_t c1 = std::min<int64_t>(n, c0 + kColmaxRows);
-  if (c < r) {
+  if (rg < rows) {
     float mu = 0.0f, mc = 0.0f;
-    for (int64_t i = c0 + rg; i < c1; i += 4) {
-      mu = fmaxf(mu, fabsf(U[i * r + c]));
-      mc = fmaxf(mc, fabsf(cval(U, B, i, c, r, inv2m)));
+#pragma unroll 8
+    for (int64_t i = c0 + rg; i < c1; i += rows) {
+      const float u = U[i * r + c];
+      mu = fmaxf(mu, fabsf(u));
+      mc = fmaxf(mc, c == 0 ? fabsf(-0.5f * u) : fabsf(inv2m * B[i * r + c]));
     }
     atomicMax(&sm[c], __float_as_uint(mu));
     atomicMax(&sm[64 + c], __float_as_uint(mc));
@@ -137,8 +141,11 @@ __global__ __launch_bounds__(256) void colmax_kernel(const float* __restrict__ U
 // Column c gets U_c 2^(e_c + gam), C_c 2^(gam - e_c) with e_c the rounded
 // half of log2(max |C_c| / max |U_c|) (balanced largest entries, each within
 // 2^0.5 of m_c = sqrt(max |U_c| max |C_c|)), and gam puts the largest m_c at or
-// below 2^14.
-__global__ void scale_kernel(const uint32_t* __restrict__ cmax, int r, float* __restrict__ scl) {
+// below 2^14; where the split form runs (info->ok), the largest entry that W~ can
+// have times the largest G (3) at or below 2^15 instead, since it rounds
+// P = G W~ to binary16 parts.
+__global__ void scale_kernel(const uint32_t* __restrict__ cmax, int r,
+                             const split::Info* __restrict__ info, float* __restrict__ scl) {
   __shared__ float sm[64];
   __shared__ int sgam;
   const int c = threadIdx.x;
@@ -156,7 +163,12 @@ __global__ void scale_kernel(const uint32_t* __restrict__ cmax, int r, float* __
   if (c == 0) {
     float mx = 0.0f;
     for (int k = 0; k < 64; ++k) mx = fmaxf(mx, sm[k]);
-    const int gam = mx > 0.0f ? 14 - (int)ceilf(log2f(mx)) : 0;
+    int gam = mx > 0.0f ? 14 - (int)ceilf(log2f(mx)) : 0;
+    if (info && info->ok && mx > 0.0f) {
+      double w = 0.0;
+      for (int k = 0; k < 64; ++k) w += (double)sm[k] * (double)sm[k];
+      gam = (int)floor(0.5 * (15.0 - ceil(log2(6.0 * w))));
+    }
     sgam = max(-60, min(60, gam));
     scl[128] = ldexpf(1.0f, -2 * sgam);
   }
@@ -177,7 +189,9 @@ __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ X,
                                                     float inv2m, KParams kp,
                                                     const float* __restrict__ scl,
                                                     float* __restrict__ Xs, float* __restrict__ nrm,
-                                                    _Float16* __restrict__ H) {
+                                                    _Float16* __restrict__ H,
+                                                    const split::Info* __restrict__ skip) {
+  if (skip && skip->ok) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   float acc = 0.0f;
@@ -257,7 +271,9 @@ __global__ __launch_bounds__(256) void grad_kernel(const float* __restrict__ Xs,
                                                    const _Float16* __restrict__ H,
                                                    const float* __restrict__ scl, int64_t n,
                                                    int64_t i0, int64_t i1,
-                                                   double* __restrict__ part, int nsplit) {
+                                                   double* __restrict__ part, int nsplit,
+                                                   const split::Info* __restrict__ skip) {
+  if (skip && skip->ok) return;
   constexpr int NCH = RP / 16;                  // 16-column chunks of U
   constexpr int NACC = ISO ? 1 : DM;
   constexpr int RB = 64 * NSUB;                 // rows per work group
@@ -478,44 +494,58 @@ __global__ __launch_bounds__(256) void diag_kernel(const float* __restrict__ U,
   }
 }
 
-// One work group: fixed-order float64 sums of the partials and the final
-// gradient out[0..nl) = dL/dl, out[nl] = dL/da^2, out[nl + 1] = dL/ds^2,
-// out[nl + 2] = 1/2 y^T u_0.
-__global__ __launch_bounds__(256) void finish_kernel(const double* __restrict__ part, int nblk,
-                                                     int nacc, const double* __restrict__ dpart,
-                                                     int nchunk, KParams kp, int ard,
-                                                     double* __restrict__ out) {
+// Group k: fixed-order float64 sum of component k over the work groups'
+// partials (k <= nacc), or of a diagonal term over its chunks.  With info, the
+// partials are the split form's (spart) where it ran.
+__global__ __launch_bounds__(256) void sums_kernel(const double* __restrict__ part, int nblk,
+                                                   int nacc, const double* __restrict__ spart,
+                                                   int snblk, int snacc,
+                                                   const split::Info* __restrict__ info,
+                                                   const double* __restrict__ dpart, int nchunk,
+                                                   double* __restrict__ sums) {
   __shared__ double sv[256];
-  __shared__ double sums[kMaxDim + 3];
-  for (int k = 0; k < nacc + 1 + 2; ++k) {
-    double acc = 0.0;
-    if (k <= nacc) {
-      for (int b = threadIdx.x; b < nblk; b += 256) acc += part[(int64_t)b * (nacc + 1) + k];
-    } else {
-      for (int b = threadIdx.x; b < nchunk; b += 256) acc += dpart[2 * b + (k - nacc - 1)];
-    }
-    sv[threadIdx.x] = acc;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-      if (threadIdx.x < h) sv[threadIdx.x] += sv[threadIdx.x + h];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) sums[k] = sv[0];
+  if (info && info->ok) {
+    part = spart;
+    nblk = snblk;
+    nacc = snacc;
+  }
+  const int k = blockIdx.x;
+  double acc = 0.0;
+  if (k <= nacc) {
+#pragma unroll 8
+    for (int b = threadIdx.x; b < nblk; b += 256) acc += part[(int64_t)b * (nacc + 1) + k];
+  } else if (k < nacc + 3) {
+    for (int b = threadIdx.x; b < nchunk; b += 256) acc += dpart[2 * b + (k - nacc - 1)];
+  }
+  sv[threadIdx.x] = acc;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if ((int)threadIdx.x < h) sv[threadIdx.x] += sv[threadIdx.x + h];
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const double a2 = kp.a2;
-    int nl;
-    if (ard) {
-      nl = kp.d;
-      for (int m = 0; m < kp.d; ++m) out[m] = a2 * sums[m] / (double)kp.ls[m];
-    } else {
-      nl = 1;
-      double s = 0.0;
-      for (int m = 0; m < nacc; ++m) s += sums[m];
-      out[0] = a2 * s / (double)kp.ls[0];
-    }
-    out[nl] = sums[nacc];
+  if (threadIdx.x == 0) sums[k] = sv[0];
+}
+
+// The gradient from the sums: out[0..nl) = dL/dl, out[nl] = dL/da^2,
+// out[nl + 1] = dL/ds^2, out[nl + 2] = 1/2 y^T u_0.
+__global__ void finish_kernel(const double* __restrict__ sums, int nacc, int snacc,
+                              const split::Info* __restrict__ info, KParams kp, int ard,
+                              double* __restrict__ out) {
+  const bool split_form = info && info->ok;
+  if (split_form) nacc = snacc;
+  const int m = threadIdx.x;
+  const double a2 = kp.a2;
+  const int nl = ard ? kp.d : 1;
+  if (ard) {
+    if (m < kp.d) out[m] = a2 * sums[m] / (double)kp.ls[m];
+  } else if (m == 0) {
+    double s = 0.0;
+    for (int k = 0; k < nacc; ++k) s += sums[k];
+    out[0] = a2 * s / (double)kp.ls[0];
+  }
+  if (m == 0) {
+    // the split form's kernel sum leaves out the diagonal, kappa(0) W_ii = W_ii
+    out[nl] = split_form ? sums[nacc] + sums[nacc + 1] : sums[nacc];
     out[nl + 1] = sums[nacc + 1];
     out[nl + 2] = 0.5 * sums[nacc + 2];
   }
@@ -531,6 +561,8 @@ struct Work {
   _Float16* H;        // n x 4 x RP binary16 split of U and C
   uint32_t* cmax;     // 128 column maxima
   float* scl;         // 129 scales
+  double* sums;       // component sums
+  const split::Info* skip;   // nothing runs when its ok is set (null: always run)
 };
 
 template <int KIND, int DM, int RP, bool ISO>
@@ -538,21 +570,16 @@ gp_status launch_t(const KParams& kp, const float* X, int64_t n, const float* U,
                    int r, float inv2m, int64_t i0, int64_t i1, double* part, int nsplit,
                    const Work& w, hipStream_t s) {
   constexpr int NSUB = nsub_for<DM>();
-  GP_TRY(fill_f32(reinterpret_cast<float*>(w.cmax), 128, 0.0f, s));
-  colmax_kernel<<<(unsigned)ceil_div(n, kColmaxRows), 256, 0, s>>>(U, B, n, r, inv2m, w.cmax);
-  GP_HIP(hipGetLastError());
-  scale_kernel<<<1, 64, 0, s>>>(w.cmax, r, w.scl);
-  GP_HIP(hipGetLastError());
   split_kernel<DM, RP><<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(X, U, B, n, r, inv2m, kp, w.scl,
-                                                                  w.Xs, w.nr, w.H);
+                                                                  w.Xs, w.nr, w.H, w.skip);
   GP_HIP(hipGetLastError());
   const int64_t blocks = ceil_div(i1 - i0, (int64_t)64 * NSUB) * nsplit;
   if (i0 == 0 && i1 == n)
     grad_kernel<KIND, DM, RP, ISO, NSUB, true><<<(unsigned)blocks, 256, 0, s>>>(
-        w.Xs, w.nr, w.H, w.scl, n, i0, i1, part, nsplit);
+        w.Xs, w.nr, w.H, w.scl, n, i0, i1, part, nsplit, w.skip);
   else
     grad_kernel<KIND, DM, RP, ISO, NSUB, false><<<(unsigned)blocks, 256, 0, s>>>(
-        w.Xs, w.nr, w.H, w.scl, n, i0, i1, part, nsplit);
+        w.Xs, w.nr, w.H, w.scl, n, i0, i1, part, nsplit, w.skip);
   GP_HIP(hipGetLastError());
   return GP_OK;
 }
@@ -598,11 +625,17 @@ int choose_splits(int64_t rows, int64_t n, int d) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(want, nstage));
 }
 
-size_t workspace_bytes(int64_t rows, int64_t n, int d, int r) {
+size_t workspace_bytes(int64_t rows, int64_t n, int kind, int d, bool ard, int r) {
   const int64_t nblk = row_blocks(rows, d) * choose_splits(rows, n, d);
   const int64_t nchunk = ceil_div(std::max<int64_t>(rows, 1), kDiagRows);
-  return 8 * (size_t)nblk * (kMaxDim + 1) + 16 * (size_t)nchunk + 4 * (size_t)n * (dm_of(d) + 1) +
-         2 * (size_t)n * 4 * rp_of(r) + 4 * 128 + 4 * 129 + 8 * 256;
+  size_t b = 8 * (size_t)nblk * (kMaxDim + 1) + 16 * (size_t)nchunk +
+             4 * (size_t)n * (dm_of(d) + 1) + 2 * (size_t)n * 4 * rp_of(r) + 4 * 128 + 4 * 129 +
+             8 * (kMaxDim + 3) + 9 * 256;
+  if (use_split(kind, n, d, !ard, r, rows)) {
+    const SplitWork w = split_plan(n, d, !ard);
+    b += split_bytes(w, d) + 8 * (size_t)(w.rblocks * w.nsplit) * (d + 1) + 256;
+  }
+  return b;
 }
 
 gp_status launch(const KParams& kp, bool ard, const float* X, int64_t n, const float* U,
@@ -613,19 +646,41 @@ gp_status launch(const KParams& kp, bool ard, const float* X, int64_t n, const f
   const int64_t nblk = rows > 0 ? row_blocks(rows, kp.d) * nsplit : 0;
   const int64_t nchunk = ceil_div(rows, kDiagRows);
   const int nacc = ard ? dm_of(kp.d) : 1;
+  const bool iso = !ard;
   double* part = ar.take<double>((size_t)std::max<int64_t>(nblk, 1) * (nacc + 1));
   double* dpart = ar.take<double>((size_t)std::max<int64_t>(nchunk, 1) * 2);
-  Work w;
+  Work w{};
   w.Xs = ar.take<float>((size_t)n * dm_of(kp.d));
   w.nr = ar.take<float>((size_t)n);
   w.H = ar.take<_Float16>((size_t)n * 4 * rp_of(r));
   w.cmax = ar.take<uint32_t>(128);
   w.scl = ar.take<float>(129);
-  if (!part || !dpart || !w.Xs || !w.nr || !w.H || !w.cmax || !w.scl)
+  w.sums = ar.take<double>(kMaxDim + 3);
+  if (!part || !dpart || !w.Xs || !w.nr || !w.H || !w.cmax || !w.scl || !w.sums)
     return set_error(GP_ERR_NOMEM, "internal: gradient workspace sizing");
   const float inv2m = (float)(0.5 / (double)(r - 1));
-  const bool iso = !ard;
+  const bool split_form = use_split(kp.kind, n, kp.d, iso, r, rows);
+  SplitWork sw{};
+  double* spart = nullptr;
+  int64_t snblk = 0;
+  const int snacc = ard ? kp.d : 1;
+  if (split_form) {
+    sw = split_plan(n, kp.d, iso);
+    GP_TRY(split_carve(sw, kp.d, ar));
+    snblk = sw.rblocks * sw.nsplit;
+    spart = ar.take<double>((size_t)snblk * (snacc + 1));
+    if (!spart) return set_error(GP_ERR_NOMEM, "internal: gradient workspace sizing");
+    GP_TRY(split::prepare(sw.p, kp, X, n, X, n, s));
+    w.skip = sw.p.info;
+  }
   if (rows > 0) {
+    GP_TRY(fill_f32(reinterpret_cast<float*>(w.cmax), 128, 0.0f, s));
+    colmax_kernel<<<(unsigned)ceil_div(n, kColmaxRows), 256, 0, s>>>(U, B, n, r, inv2m, w.cmax);
+    GP_HIP(hipGetLastError());
+    scale_kernel<<<1, 64, 0, s>>>(w.cmax, r, w.skip, w.scl);
+    GP_HIP(hipGetLastError());
+    if (split_form)
+      GP_TRY(split_launch(sw, kp, iso, X, n, U, B, r, inv2m, w.scl, spart, s));
     gp_status st;
     switch (kp.kind) {
       case GP_KERNEL_RBF:
@@ -647,7 +702,10 @@ gp_status launch(const KParams& kp, bool ard, const float* X, int64_t n, const f
     diag_kernel<<<(unsigned)nchunk, 256, 0, s>>>(U, B, r, inv2m, i0, i1, dpart);
     GP_HIP(hipGetLastError());
   }
-  finish_kernel<<<1, 256, 0, s>>>(part, (int)nblk, nacc, dpart, (int)nchunk, kp, ard ? 1 : 0, out);
+  sums_kernel<<<(unsigned)(std::max(nacc, snacc) + 3), 256, 0, s>>>(
+      part, (int)nblk, nacc, spart, (int)snblk, snacc, w.skip, dpart, (int)nchunk, w.sums);
+  GP_HIP(hipGetLastError());
+  finish_kernel<<<1, 64, 0, s>>>(w.sums, nacc, snacc, w.skip, kp, ard ? 1 : 0, out);
   GP_HIP(hipGetLastError());
   return GP_OK;
 }

@@ -392,14 +392,19 @@ __global__ __launch_bounds__(256) void main_kernel(const _Float16* __restrict__ 
         parts3(k, kp);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-          f4 t = acc[q][rb];
+          // 32 columns from zero, smallest products first, then one vector add:
+          // an MFMA cuts the low bits of products far below its accumulator, so
+          // a long chain on one accumulator falls short of a same-sign sum
+          // (2e-6 of it over 40,000 columns; 3% of the launch buys that back)
+          f4 t = f4{0.f, 0.f, 0.f, 0.f};
           t = f16::mfma32<__bf16>(kp[2], bf[rb], t);
           t = f16::mfma32<__bf16>(kp[1], bv[rb][1], t);
           t = f16::mfma32<__bf16>(kp[0], bv[rb][2], t);
           t = f16::mfma32<__bf16>(kp[1], bf[rb], t);
           t = f16::mfma32<__bf16>(kp[0], bv[rb][1], t);
           t = f16::mfma32<__bf16>(kp[0], bv[rb][0], t);
-          acc[q][rb] = t;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[q][rb][v] += t[v];
         }
       }
     }
