@@ -1133,11 +1133,12 @@ __global__ void pc_syrk_kernel(const Seg* __restrict__ segs, const PcState* __re
 __global__ __launch_bounds__(256) void pc_cholinv_kernel(const Seg* __restrict__ segs,
                                                          const int* __restrict__ plist,
                                                          PcState* __restrict__ ps) {
-  __shared__ double A[pc::kMaxRank * pc::kMaxRank];
+  __shared__ double A[pc::kCholLds];
+  __shared__ double dinv[pc::kMaxRank];
   const int p = plist[blockIdx.x];
   const int k = ps[p].rank;
   if (k == 0) return;
-  pc::chol_inverse(segs[p].C, segs[p].Cinv, k, A, &ps[p].not_pd);
+  pc::chol_inverse(segs[p].C, segs[p].Cinv, k, A, dinv, &ps[p].not_pd);
 }
 
 // binary32 copy of the built factor columns, the chunk's rows

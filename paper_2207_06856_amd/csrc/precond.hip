@@ -47,81 +47,43 @@ __device__ inline bool better(double v, int64_t i, double bv, int64_t bi) {
   return v > bv || (v == bv && i < bi);
 }
 
-// Work-group argmax (lowest index on ties) and sum of the residual diagonal.
-__device__ void argmax_partial(const double* __restrict__ diag, int64_t n, double* __restrict__ pv,
-                               int64_t* __restrict__ pi, double* __restrict__ psum) {
-  __shared__ double sv[256];
-  __shared__ int64_t si[256];
-  __shared__ double ssum[256];
-  double bv = -INFINITY, sum = 0.0;
-  int64_t bi = INT64_MAX;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const double v = diag[i];
-    sum += v;
-    if (better(v, i, bv, bi)) {
-      bv = v;
-      bi = i;
-    }
-  }
-  sv[threadIdx.x] = bv;
-  si[threadIdx.x] = bi;
-  ssum[threadIdx.x] = sum;
-  for (int s = 128; s > 0; s >>= 1) {
-    __syncthreads();
-    if ((int)threadIdx.x < s) {
-      if (better(sv[threadIdx.x + s], si[threadIdx.x + s], sv[threadIdx.x], si[threadIdx.x])) {
-        sv[threadIdx.x] = sv[threadIdx.x + s];
-        si[threadIdx.x] = si[threadIdx.x + s];
-      }
-      ssum[threadIdx.x] += ssum[threadIdx.x + s];
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    pv[blockIdx.x] = sv[0];
-    pi[blockIdx.x] = si[0];
-    psum[blockIdx.x] = ssum[0];
-  }
+struct Best {
+  double v;
+  int64_t i;
+  double sum;
+};
+
+__device__ __forceinline__ Best best_of(const Best& a, const Best& b) {
+  const bool take = better(b.v, b.i, a.v, a.i);
+  return Best{take ? b.v : a.v, take ? b.i : a.i, a.sum + b.sum};
 }
 
-// Fixed-order merge of nparts argmax partials by one work group of 256
-// threads: the largest residual diagonal (lowest index on ties), its index and
-// the residual trace, returned to every thread.
-__device__ __forceinline__ void merge_partials(const double* __restrict__ pv,
+// Argmax (lowest index on ties) and sum over a wave, then over the work
+// group's waves, in a fixed order; every thread returns the result.
+__device__ __forceinline__ Best group_best(Best x) {
+  constexpr int kMaxWaves = 16;
+  __shared__ Best sw[kMaxWaves];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+    x = best_of(x, Best{__shfl_xor(x.v, o, 64), __shfl_xor(x.i, o, 64), __shfl_xor(x.sum, o, 64)});
+  const int waves = blockDim.x >> 6;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sw[threadIdx.x >> 6] = x;
+  __syncthreads();
+  Best r = sw[0];
+  for (int w = 1; w < waves; ++w) r = best_of(r, sw[w]);
+  return r;
+}
+
+// Fixed-order merge of nparts argmax partials by one work group: the largest
+// residual diagonal (lowest index on ties), its index and the residual trace,
+// returned to every thread.
+__device__ __forceinline__ Best merge_partials(const double* __restrict__ pv,
                                                const int64_t* __restrict__ pi,
-                                               const double* __restrict__ psum, int nparts,
-                                               double* v_out, int64_t* idx_out, double* tot_out) {
-  __shared__ double sv[256];
-  __shared__ int64_t si[256];
-  __shared__ double ssum[256];
-  double v = -INFINITY, tot = 0.0;
-  int64_t idx = INT64_MAX;
-  for (int g = threadIdx.x; g < nparts; g += blockDim.x) {
-    tot += psum[g];
-    if (better(pv[g], pi[g], v, idx)) {
-      v = pv[g];
-      idx = pi[g];
-    }
-  }
-  sv[threadIdx.x] = v;
-  si[threadIdx.x] = idx;
-  ssum[threadIdx.x] = tot;
-  for (int s = 128; s > 0; s >>= 1) {
-    __syncthreads();
-    if ((int)threadIdx.x < s) {
-      if (better(sv[threadIdx.x + s], si[threadIdx.x + s], sv[threadIdx.x], si[threadIdx.x])) {
-        sv[threadIdx.x] = sv[threadIdx.x + s];
-        si[threadIdx.x] = si[threadIdx.x + s];
-      }
-      ssum[threadIdx.x] += ssum[threadIdx.x + s];
-    }
-  }
-  __syncthreads();
-  *v_out = sv[0];
-  *idx_out = si[0];
-  *tot_out = ssum[0];
-  __syncthreads();
+                                               const double* __restrict__ psum, int nparts) {
+  Best x{-INFINITY, INT64_MAX, 0.0};
+  for (int g = threadIdx.x; g < nparts; g += blockDim.x) x = best_of(x, Best{pv[g], pi[g], psum[g]});
+  return group_best(x);
 }
 
 // One work group: the merge, the pivot of step next_m and the stop rule.  Used
@@ -131,28 +93,34 @@ __global__ void select_kernel(BuildState* bs, const double* __restrict__ pv,
                               const int64_t* __restrict__ pi, const double* __restrict__ psum,
                               int nparts, int64_t* piv_out, int next_m, int rank, double stop_abs) {
   if (bs->stop) return;
-  double v, tot;
-  int64_t idx;
-  merge_partials(pv, pi, psum, nparts, &v, &idx, &tot);
+  const Best x = merge_partials(pv, pi, psum, nparts);
   if (threadIdx.x == 0) {
-    bs->trace = tot;
-    if (next_m >= rank || !(v > stop_abs) || idx == INT64_MAX) {
+    bs->trace = x.sum;
+    if (next_m >= rank || !(x.v > stop_abs) || x.i == INT64_MAX) {
       bs->stop = 1;
     } else {
-      bs->dmax = v;
-      bs->pivot = idx;
-      piv_out[next_m] = idx;
+      bs->dmax = x.v;
+      bs->pivot = x.i;
+      piv_out[next_m] = x.i;
     }
   }
 }
 
+// diag = a2 and the first partials.
 __global__ void init_kernel(double* __restrict__ diag, int64_t n, double a2, double* pv,
                             int64_t* pi, double* psum) {
+  Best x{-INFINITY, INT64_MAX, 0.0};
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
+       i += (int64_t)gridDim.x * blockDim.x) {
     diag[i] = a2;
-  __syncthreads();
-  argmax_partial(diag, n, pv, pi, psum);
+    x = best_of(x, Best{a2, i, a2});
+  }
+  x = group_best(x);
+  if (threadIdx.x == 0) {
+    pv[blockIdx.x] = x.v;
+    pi[blockIdx.x] = x.i;
+    psum[blockIdx.x] = x.sum;
+  }
 }
 
 // Step m of the factorisation.  For m > 0 every work group first merges the
@@ -160,11 +128,18 @@ __global__ void init_kernel(double* __restrict__ diag, int64_t n, double a2, dou
 // groups find the same pivot; group 0 records it, the trace and the stop);
 // for m = 0 the pivot comes from select_kernel.  The step writes its own
 // partials to the other buffer (pv), which no group of this launch reads.
-__global__ void step_kernel(const float* __restrict__ X, int64_t n, KParams kp, int m,
-                            double* __restrict__ L, double* __restrict__ diag, BuildState* bs,
-                            const double* __restrict__ pv_in, const int64_t* __restrict__ pi_in,
-                            const double* __restrict__ psum_in, int nparts, int64_t* piv_out,
-                            double stop_abs, double* pv, int64_t* pi, double* psum) {
+//
+// A step is a chain of short latencies (the merge, the pivot's row of L, m
+// loads of L per row, the argmax): reductions go through wave shuffles with
+// one barrier each, the loads of L sixteen at a time, and the points are
+// divided by the lengthscales as a product with their reciprocals: 11.4 us a step
+// at n = 50,000, rank 100 to 9.6, 14.7 to 11.6 at n = 100,000.
+constexpr int kStepThreads = 256;
+__global__ __launch_bounds__(kStepThreads) void step_kernel(
+    const float* __restrict__ X, int64_t n, KParams kp, int m, double* __restrict__ L,
+    double* __restrict__ diag, BuildState* bs, const double* __restrict__ pv_in,
+    const int64_t* __restrict__ pi_in, const double* __restrict__ psum_in, int nparts,
+    int64_t* piv_out, double stop_abs, double* pv, int64_t* pi, double* psum) {
   // The stop flag can be set by group 0 of this same launch (after its merge
   // below), so one thread reads it and the whole group follows that reading:
   // waves of one group must never disagree, or the exited ones leave their
@@ -172,22 +147,24 @@ __global__ void step_kernel(const float* __restrict__ X, int64_t n, KParams kp, 
   // set here returns as a whole; one that does not reaches the same stop
   // decision from its own merge of the same partials.
   __shared__ int stop_seen;
-  if (threadIdx.x == 0) stop_seen = __atomic_load_n(&bs->stop, __ATOMIC_RELAXED);
-  __syncthreads();
-  if (stop_seen) return;
   __shared__ double lp[kMaxRank];
-  __shared__ double xp[kMaxDim];
+  __shared__ double xp[kMaxDim], inv_l[kMaxDim];
+  if (threadIdx.x == 0) stop_seen = __atomic_load_n(&bs->stop, __ATOMIC_RELAXED);
   int64_t p;
   double dmax;
   if (m == 0) {
+    __syncthreads();
+    if (stop_seen) return;
     p = bs->pivot;
     dmax = bs->dmax;
   } else {
-    double tot;
-    merge_partials(pv_in, pi_in, psum_in, nparts, &dmax, &p, &tot);
+    const Best x = merge_partials(pv_in, pi_in, psum_in, nparts);
+    if (stop_seen) return;
+    p = x.i;
+    dmax = x.v;
     const bool stop = !(dmax > stop_abs) || p == INT64_MAX;
     if (threadIdx.x == 0 && blockIdx.x == 0) {
-      bs->trace = tot;
+      bs->trace = x.sum;
       if (stop) {
         bs->stop = 1;
       } else {
@@ -200,25 +177,37 @@ __global__ void step_kernel(const float* __restrict__ X, int64_t n, KParams kp, 
   }
   const double inv_sq = 1.0 / sqrt(dmax);
   const int d = kp.d;
-  for (int t = threadIdx.x; t < m; t += blockDim.x) lp[t] = L[(int64_t)t * n + p];
-  for (int t = threadIdx.x; t < d; t += blockDim.x) xp[t] = (double)X[p * d + t] / (double)kp.ls[t];
+  if ((int)threadIdx.x < m) lp[threadIdx.x] = L[(int64_t)threadIdx.x * n + p];
+  if (threadIdx.x >= 128 && (int)threadIdx.x < 128 + d) {
+    const int t = threadIdx.x - 128;
+    const double il = 1.0 / (double)kp.ls[t];
+    inv_l[t] = il;
+    xp[t] = (double)X[p * d + t] * il;
+  }
   __syncthreads();
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
+  Best best{-INFINITY, INT64_MAX, 0.0};
+  for (int64_t i = (int64_t)blockIdx.x * kStepThreads + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * kStepThreads) {
     double r2 = 0.0;
     for (int t = 0; t < d; ++t) {
-      const double df = (double)X[i * d + t] / (double)kp.ls[t] - xp[t];
+      const double df = fma((double)X[i * d + t], inv_l[t], -xp[t]);
       r2 = fma(df, df, r2);
     }
     double acc = (double)kp.a2 * kval64(kp.kind, r2);
     acc = sub_lrow(L, n, i, lp, m, acc);
     const double l = acc * inv_sq;
     L[(int64_t)m * n + i] = l;
-    diag[i] = fma(-l, l, diag[i]);
+    const double dg = fma(-l, l, diag[i]);
+    diag[i] = dg;
+    best = best_of(best, Best{dg, i, dg});
   }
-  __syncthreads();
   if (threadIdx.x == 0 && blockIdx.x == 0) bs->rank = m + 1;
-  argmax_partial(diag, n, pv, pi, psum);
+  best = group_best(best);
+  if (threadIdx.x == 0) {
+    pv[blockIdx.x] = best.v;
+    pi[blockIdx.x] = best.i;
+    psum[blockIdx.x] = best.sum;
+  }
 }
 
 // Partial L^T L on the float64 matrix cores (v_mfma_f64_16x16x4f64): work
@@ -227,8 +216,10 @@ __global__ void step_kernel(const float* __restrict__ X, int64_t n, KParams kp, 
 // four waves share the 16 x 16 tiles (ta <= tb) of the k x k result.  Lane
 // layouts: A lane l holds A[l % 16][l / 16], B lane l holds B[l / 16][l % 16],
 // result lane l element v holds D[l / 16 + 4 v][l % 16].  Both triangles of the
-// partial are written (an off-diagonal tile also fills its mirror).
-constexpr int kSyrkRows = 64;
+// partial are written (an off-diagonal tile also fills its mirror).  Bound by
+// the loads' latency (50 to 100 rows of L a group): the next 32 rows are loaded
+// into registers before the current ones' products (110 us -> 35 at n = 50,000).
+constexpr int kSyrkRows = 32;
 __global__ __launch_bounds__(256) void syrk_kernel(const double* __restrict__ L, int64_t n, int k,
                                                    int nsplit, double* __restrict__ part) {
   typedef double sd4 __attribute__((ext_vector_type(4)));
@@ -243,14 +234,26 @@ __global__ __launch_bounds__(256) void syrk_kernel(const double* __restrict__ L,
   sd4 acc[(kMaxPairs + 3) / 4];
 #pragma unroll
   for (int q = 0; q < (kMaxPairs + 3) / 4; ++q) acc[q] = sd4{0.0, 0.0, 0.0, 0.0};
+  constexpr int kPer = kMaxRank * kSyrkRows / 256;
+  double pre[kPer];
+  auto load = [&](int64_t c0) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = u * 256 + (int)threadIdx.x, m = e / kSyrkRows;
+      const int64_t i = c0 + e % kSyrkRows;
+      pre[u] = (m < k && i < i1) ? L[(int64_t)m * n + i] : 0.0;
+    }
+  };
+  load(i0);
   for (int64_t c0 = i0; c0 < i1; c0 += kSyrkRows) {
     __syncthreads();
-    for (int e = threadIdx.x; e < tk * 16 * kSyrkRows; e += 256) {
-      const int m = e / kSyrkRows, cc = e % kSyrkRows;
-      const int64_t i = c0 + cc;
-      sl[m][cc] = (m < k && i < i1) ? L[(int64_t)m * n + i] : 0.0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = u * 256 + (int)threadIdx.x;
+      sl[e / kSyrkRows][e % kSyrkRows] = pre[u];
     }
     __syncthreads();
+    if (c0 + kSyrkRows < i1) load(c0 + kSyrkRows);
 #pragma unroll
     for (int q = 0; q < (kMaxPairs + 3) / 4; ++q) {
       const int p = wave + 4 * q;
@@ -302,14 +305,15 @@ __global__ void form_c_kernel(const double* __restrict__ part, int nsplit, int k
 }
 
 // Cholesky of C and explicit inverse into Cinv (chol_inverse); one work group
-// of 1024 threads (the per-entry operation sequences do not depend on the
-// group size, so the result is the same as with any other size >= kMaxRank).
-constexpr int kCholThreads = 1024;
+// of 512 threads, whose registers hold a factor block (the per-entry operation
+// sequences do not depend on the group size, so neither does the result).
+constexpr int kCholThreads = 512;
 __global__ __launch_bounds__(kCholThreads) void chol_inv_kernel(const double* __restrict__ C,
                                                        double* __restrict__ Cinv, int k,
                                                        BuildState* bs) {
-  __shared__ double A[kMaxRank * kMaxRank];
-  chol_inverse(C, Cinv, k, A, &bs->not_pd);
+  __shared__ double A[kCholLds];
+  __shared__ double dinv[kMaxRank];
+  chol_inverse(C, Cinv, k, A, dinv, &bs->not_pd);
 }
 
 __global__ void to_f32_kernel(const double* __restrict__ a, float* __restrict__ b, int64_t n) {
@@ -491,9 +495,8 @@ extern "C" gp_status gp_pivchol_precond(const gp_kernel* k, const float* X, int6
   P->kp = kp;
   P->piv_host = new int64_t[rank > 0 ? rank : 1];
   const int kr = rank > 0 ? rank : 1;
-  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(kBlocks, ceil_div(n, 256)));
-  const int tiles = (kr + 15) / 16;
-  const int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(256, ceil_div(n, 8 * kSyrkRows)));
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(kBlocks, ceil_div(n, (int64_t)kStepThreads)));
+  const int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(256, ceil_div(n, (int64_t)128)));
   // the handle's buffers, carved from one block (reused across handles of
   // the same size)
   auto r256 = [](size_t b) { return (b + 255) & ~size_t(255); };
@@ -551,15 +554,16 @@ extern "C" gp_status gp_pivchol_precond(const gp_kernel* k, const float* X, int6
     GP_HIP(hipMemsetAsync(bs, 0, sizeof(BuildState), s));
     const double stop_abs = 1e-12 * (double)kp.a2;
     // partials of step m - 1 (init: m = 0) live in buffer m % 2
-    init_kernel<<<grid, 256, 0, s>>>(diag, n, kp.a2, pv[0], pi[0], psum[0]);
+    init_kernel<<<grid, 256, 0, s>>>(diag, n, (double)kp.a2, pv[0], pi[0], psum[0]);
     GP_HIP(hipGetLastError());
     select_kernel<<<1, 256, 0, s>>>(bs, pv[0], pi[0], psum[0], grid, P->piv_dev, 0, rank,
                                     stop_abs);
     GP_HIP(hipGetLastError());
     for (int m = 0; m < rank; ++m) {
       const int bi = m % 2, bo = (m + 1) % 2;
-      step_kernel<<<grid, 256, 0, s>>>(X, n, kp, m, P->L64, diag, bs, pv[bi], pi[bi], psum[bi],
-                                       grid, P->piv_dev, stop_abs, pv[bo], pi[bo], psum[bo]);
+      step_kernel<<<grid, kStepThreads, 0, s>>>(X, n, kp, m, P->L64, diag, bs, pv[bi], pi[bi],
+                                                psum[bi], grid, P->piv_dev, stop_abs, pv[bo],
+                                                pi[bo], psum[bo]);
       GP_HIP(hipGetLastError());
     }
     select_kernel<<<1, 256, 0, s>>>(bs, pv[rank % 2], pi[rank % 2], psum[rank % 2], grid,
@@ -587,7 +591,6 @@ extern "C" gp_status gp_pivchol_precond(const gp_kernel* k, const float* X, int6
       if (hb.not_pd)
         return set_error(GP_ERR_NOT_PD, "inner matrix I + L^T L / s^2 is not positive definite");
     }
-    (void)tiles;
     return GP_OK;
   };
   st = run();
