@@ -228,6 +228,13 @@ gp_status quantise(Plan& p, const float* v, bool pow2_from_colmax, const int* li
 // it: 0-based iteration index (the basis holds at most it + 1 pairs).
 gp_status iteration(Plan& p, int it, hipStream_t s) {
   const int* live = &p.st->nactive;
+  if (!p.fp16 && !p.f32_split && !p.o.P && cg::fused_step_fits(p.dm, p.reorth, it + 2)) {
+    GP_TRY(valu::launch_partial(p.kp, p.X, p.n, p.X, p.n, p.d, p.r, p.part32, false, p.nsplit32,
+                                live, s));
+    return cg::fused_step(p.part32, p.nsplit32, p.kp.a2, p.kp.s2, p.U, p.rr, p.d, p.Ub, p.st,
+                          p.gram, p.max_basis, p.reorth, p.lse, p.o.tol, p.o.min_iter, p.history,
+                          p.dm, s);
+  }
   GP_TRY(product(p, p.d, p.q, live, s));
   GP_TRY(cg::dq_step(p.d, p.q, p.st, p.lse, p.pm, p.ps, p.pd, p.dm, s));
   GP_TRY(cg::update_step(p.U, p.rr, p.d, p.q, p.st, p.dm, s));

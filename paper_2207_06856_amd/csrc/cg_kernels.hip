@@ -1016,6 +1016,349 @@ gp_status direction_step(const float* z, float* d, const float* rr, float* U, fl
   return GP_OK;
 }
 
+// ---- a3-a7 of a small unpreconditioned solve in one launch ------------------------
+// Everything between two float32 products by one work group of 16 waves: the
+// product's split sums, d^T K d and alpha, the update, CGS2 through the Gram
+// matrix, gamma, beta, convergence, the next direction and the basis append.
+// A solve this small spends its iteration on launches and on the latency of
+// their first loads (ten of them, 50 us at n = 2000, R = 1, 8.5 of which is the
+// product); here a phase costs a barrier: 28 us and the product's 8.3, the
+// solve of 60 iterations 3.45 -> 2.50 ms.  Bound by the latency of its chain of
+// loads, reductions and float64 scalars.  Thread (row lane, column) as in the
+// kernels above; each thread keeps its KE entries of d, q and r in registers (16
+// loads in flight; 32 spill at 1024 threads, 39 us), r and the newest basis
+// vector also lie in LDS for the sweep, in which every wave takes whole basis
+// vectors.
+// Where the line lies: one compute unit reads the split sums and the basis at
+// 100 to 150 GB/s.  Two entries a thread: n = 2040, R = 1 3.35 -> 2.52 ms, n = 256,
+// R = 8 2.25 -> 1.53 ms.  Four: n = 250, R = 16 3.10 -> 2.11 ms, n = 2040, R = 2 4.14
+// -> 3.65 ms, but n = 4090, R = 1, whose product has more splits, 4.69 -> 4.94 ms.
+// Eight: n = 4000, R = 2 6.59 -> 7.00 ms.  393216 stored floats are 96 pairs of 4096:
+// n = 2040, R = 2, 70 iterations 4.24 -> 3.58 ms, 3.70 at 64 pairs, 3.83 at 32.
+constexpr int kFusedThreads = 1024;
+constexpr int kFusedRows = 2048;                                     // n at most
+constexpr int kFusedMax = 4 * kFusedThreads;                         // n * rp2 at most
+constexpr int kFusedCoef = 2048;                                     // stored pairs * r at most
+constexpr int64_t kFusedBasis = 393216;                              // stored pairs * n * r at most
+
+bool fused_step_fits(const Dims& dm, bool reorth, int pairs) {
+  if (dm.n > kFusedRows || dm.n * dm.rp2 > kFusedMax) return false;
+  return !reorth || (pairs * dm.r <= kFusedCoef && pairs * dm.n * dm.r <= kFusedBasis);
+}
+
+// Per-column reductions over the group's row lanes: across the lanes of a wave
+// that share a column, then over the 16 waves in order; every thread returns
+// its column's result.
+__device__ __forceinline__ float fused_sum(float v, int rp2, float (*buf)[kMaxR]) {
+  for (int o = 32; o >= rp2; o >>= 1) v += __shfl_xor(v, o, 64);
+  const int lane = threadIdx.x & 63;
+  __syncthreads();
+  if (lane < rp2) buf[threadIdx.x >> 6][lane] = v;
+  __syncthreads();
+  float t = buf[0][threadIdx.x % rp2];
+#pragma unroll
+  for (int w = 1; w < 16; ++w) t += buf[w][threadIdx.x % rp2];
+  return t;
+}
+__device__ __forceinline__ void fused_lse(float& m, float& S, int rp2, float (*bm)[kMaxR],
+                                          float (*bs)[kMaxR]) {
+  for (int o = 32; o >= rp2; o >>= 1) {
+    const float m2 = __shfl_xor(m, o, 64), S2 = __shfl_xor(S, o, 64);
+    // the lower lane's pair first, so that both lanes form the same value
+    float ma = (threadIdx.x & o) ? m2 : m, Sa = (threadIdx.x & o) ? S2 : S;
+    const float mb = (threadIdx.x & o) ? m : m2, Sb = (threadIdx.x & o) ? S : S2;
+    lse_merge(ma, Sa, mb, Sb);
+    m = ma;
+    S = Sa;
+  }
+  const int lane = threadIdx.x & 63;
+  __syncthreads();
+  if (lane < rp2) {
+    bm[threadIdx.x >> 6][lane] = m;
+    bs[threadIdx.x >> 6][lane] = S;
+  }
+  __syncthreads();
+  m = -INFINITY;
+  S = 0.0f;
+  for (int w = 0; w < 16; ++w) lse_merge(m, S, bm[w][threadIdx.x % rp2], bs[w][threadIdx.x % rp2]);
+}
+
+template <bool LSE, int KE>
+__global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
+    const float* __restrict__ part, int nsplit, float a2, float s2, float* __restrict__ x,
+    float* __restrict__ rr, float* __restrict__ d, float* __restrict__ U, State* st,
+    float* __restrict__ gram, int max_basis, int reorth, double tol, int min_iter,
+    float* __restrict__ history, int n, int r, int rp2) {
+  if (st->nactive == 0) return;
+  __shared__ float sR[KE * kFusedThreads], sU[KE * kFusedThreads];
+  __shared__ float sc1[kFusedCoef], scoef[kFusedCoef];
+  __shared__ float bm[16][kMaxR], bs[16][kMaxR];
+  __shared__ float s_alpha[kMaxR], s_beta[kMaxR], s_sg[kMaxR];
+  __shared__ int s_act[kMaxR], s_live;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = tid % rp2, ty = tid / rp2, tys = kFusedThreads / rp2;
+  const int nr = n * r;
+  const int nb = reorth ? min(st->nbasis, max_basis) : 0;
+  float dv[KE], qv[KE], rv[KE];
+
+  // q = K~ d and d^T q
+  float m = -INFINITY, S = 0.0f;
+  int at[KE];                               // entries; a valid one where there is none
+  bool in[KE];
+#pragma unroll
+  for (int k = 0; k < KE; ++k) {
+    const int i = ty + k * tys;
+    in[k] = i < n && c < r;
+    at[k] = in[k] ? i * r + c : 0;
+    dv[k] = in[k] ? d[at[k]] : 0.0f;
+    qv[k] = 0.0f;
+  }
+  // the split sums in split order, 16 loads in flight
+  constexpr int kAhead = 16 / KE;
+  for (int p0 = 0; p0 < nsplit; p0 += kAhead) {
+    float t[kAhead][KE];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+      for (int k = 0; k < KE; ++k) t[u][k] = part[min(p0 + u, nsplit - 1) * nr + at[k]];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+      for (int k = 0; k < KE; ++k)
+        if (p0 + u < nsplit) qv[k] += t[u][k];
+  }
+#pragma unroll
+  for (int k = 0; k < KE; ++k) qv[k] = in[k] ? fmaf(s2, dv[k], a2 * qv[k]) : 0.0f;
+#pragma unroll
+  for (int k = 0; k < KE; ++k) {
+    if (in[k]) {
+      if (LSE)
+        lse_push(m, S, dv[k], qv[k]);
+      else
+        S = fmaf(dv[k], qv[k], S);
+    }
+  }
+  if (LSE)
+    fused_lse(m, S, rp2, bm, bs);
+  else
+    S = fused_sum(S, rp2, bs);
+  if (wave == 0) {
+    const int kk = st->k + 1;
+    int act = 0;
+    if (lane < r) {
+      double alpha = 0.0;
+      act = st->active[lane];
+      if (act) {
+        bool ok;
+        if (LSE) {
+          const double l = lse_value(m, S);      // lane < rp2: its own column's
+          ok = isfinite(l);
+          if (ok) alpha = exp(st->lg[lane] - l);
+        } else {
+          ok = isfinite((double)S) && S > 0.0f;
+          if (ok) alpha = st->lg[lane] / (double)S;
+        }
+        if (!ok || !isfinite(alpha)) {
+          alpha = 0.0;
+          st->breakdown[lane] = 1;
+          st->active[lane] = 0;
+          act = 0;
+        }
+      }
+      st->alpha[lane] = alpha;
+      s_alpha[lane] = (float)alpha;
+      s_act[lane] = act;
+      if (act) st->iters[lane] = kk;
+    }
+    const uint64_t live = __ballot(act != 0);
+    if (lane == 0) {
+      st->k = kk;
+      st->nactive = s_live = __popcll(live);
+    }
+  }
+  __syncthreads();
+  if (s_live == 0) return;
+
+  // x += alpha d, r += alpha q (active columns)
+  bool act = c < r && s_act[c];
+#pragma unroll
+  for (int k = 0; k < KE; ++k) {
+    rv[k] = 0.0f;
+    if (in[k]) {
+      const int e = at[k];
+      rv[k] = rr[e];
+      if (act) {
+        x[e] = fmaf(s_alpha[c], dv[k], x[e]);
+        rv[k] = fmaf(s_alpha[c], qv[k], rv[k]);
+      }
+    }
+  }
+  if (nb > 0) {
+    // c1_j = u_j^T r and the newest Gram column u_j^T u_new, one wave per j
+    const float* Un = U + (nb - 1) * nr;
+#pragma unroll
+    for (int k = 0; k < KE; ++k) {
+      if (in[k]) {
+        sR[at[k]] = rv[k];
+        sU[at[k]] = Un[at[k]];
+      }
+    }
+    __syncthreads();
+    const int lc = lane % rp2, lr = lane / rp2, step = 64 / rp2;
+    for (int j = wave; j < nb; j += 16) {
+      const float* Uj = U + j * nr;
+      float a = 0.0f, b = 0.0f;
+      if (lc < r) {
+        int i = lr;
+        for (; i < n; i += 8 * step) {
+          float u[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) u[q] = i + q * step < n ? Uj[(i + q * step) * r + lc] : 0.0f;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const int e = i + q * step < n ? (i + q * step) * r + lc : 0;
+            a = fmaf(u[q], sR[e], a);
+            b = fmaf(u[q], sU[e], b);
+          }
+        }
+      }
+      for (int o = 32; o >= rp2; o >>= 1) {
+        a += __shfl_xor(a, o, 64);
+        b += __shfl_xor(b, o, 64);
+      }
+      if (lane < r) {
+        sc1[j * r + lane] = a;
+        gram[((int64_t)j * max_basis + nb - 1) * r + lane] = b;
+        gram[((int64_t)(nb - 1) * max_basis + j) * r + lane] = b;
+      }
+    }
+    __syncthreads();
+    // coef = 2 c1 - G c1 in float64, eight lanes per entry
+    for (int o0 = 0; o0 < nb * r; o0 += kFusedThreads / 8) {
+      const int o = o0 + tid / 8, q = tid & 7;
+      const bool on = o < nb * r;
+      const int j = on ? o / r : 0, cc = on ? o % r : 0;
+      double acc = 0.0;
+      if (on) {
+        const float* Gj = gram + (int64_t)j * max_basis * r + cc;
+#pragma unroll 4
+        for (int k = q; k < nb; k += 8) acc = fma((double)Gj[(int64_t)k * r], (double)sc1[k * r + cc], acc);
+      }
+#pragma unroll
+      for (int s = 1; s < 8; s <<= 1) acc += __shfl_xor(acc, s, 64);
+      if (on && q == 0) scoef[o] = (float)(2.0 * (double)sc1[o] - acc);
+    }
+    __syncthreads();
+    if (act) {
+      for (int j0 = 0; j0 < nb; j0 += kAhead) {
+        float u[kAhead][KE];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q)
+#pragma unroll
+          for (int k = 0; k < KE; ++k) u[q][k] = U[min(j0 + q, nb - 1) * nr + at[k]];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+          const float cf = j0 + q < nb ? -scoef[(j0 + q) * r + c] : 0.0f;
+#pragma unroll
+          for (int k = 0; k < KE; ++k)
+            if (j0 + q < nb && in[k]) rv[k] = fmaf(cf, u[q][k], rv[k]);
+        }
+      }
+    }
+  }
+
+  // ||r||, gamma, beta, convergence (z = r)
+  float q2 = 0.0f;
+  m = -INFINITY;
+  S = 0.0f;
+#pragma unroll
+  for (int k = 0; k < KE; ++k) {
+    if (in[k]) {
+      if (act) rr[at[k]] = rv[k];
+      q2 = fmaf(rv[k], rv[k], q2);
+      if (LSE) lse_push(m, S, rv[k], rv[k]);
+    }
+  }
+  const float rr2 = fused_sum(q2, rp2, bs);
+  if (LSE)
+    fused_lse(m, S, rp2, bm, bs);
+  else
+    S = rr2;
+  const int slot = st->nbasis;
+  __syncthreads();
+  if (wave == 0) {
+    const int kk = st->k;
+    int on = 0;
+    if (lane < r) {
+      double g;
+      bool ok;
+      if (LSE) {
+        g = lse_value(m, S);
+        ok = isfinite(g);
+      } else {
+        g = (double)S;
+        ok = isfinite(g) && g > 0.0;
+      }
+      on = st->active[lane];
+      float relc = st->rel[lane];
+      if (on) {
+        const double rel = sqrt((double)rr2 / st->bnorm2[lane]);
+        relc = (float)rel;
+        st->rel[lane] = relc;
+        if (kk >= min_iter && rel <= tol) {
+          st->converged[lane] = 1;
+          st->active[lane] = 0;
+          on = 0;
+        } else if (!ok) {
+          st->breakdown[lane] = 1;
+          st->active[lane] = 0;
+          on = 0;
+        } else {
+          const double beta = LSE ? exp(g - st->lg[lane]) : g / st->lg[lane];
+          const float sg = (float)(LSE ? exp(-0.5 * g) : 1.0 / sqrt(g));
+          st->beta[lane] = beta;
+          st->lg[lane] = g;
+          st->inv_sqrt_g[lane] = sg;
+          s_beta[lane] = (float)beta;
+          s_sg[lane] = sg;
+        }
+      }
+      s_act[lane] = on;
+      if (history) history[(int64_t)kk * r + lane] = relc;
+    }
+    const uint64_t live = __ballot(on != 0);
+    if (lane == 0) {
+      st->nactive = s_live = __popcll(live);
+      st->append_slot = slot;
+      if (reorth && s_live) st->nbasis = slot + 1;
+    }
+  }
+  __syncthreads();
+
+  // d = -r + beta d, basis append
+  act = c < r && s_act[c];
+  if (!act) return;
+#pragma unroll
+  for (int k = 0; k < KE; ++k) {
+    if (!in[k]) continue;
+    d[at[k]] = fmaf(s_beta[c], dv[k], -rv[k]);
+    if (reorth) U[slot * nr + at[k]] = rv[k] * s_sg[c];
+  }
+}
+
+gp_status fused_step(const float* part, int nsplit, float a2, float s2, float* x, float* rr,
+                     float* d, float* U, State* st, float* gram, int max_basis, bool reorth,
+                     bool lse, double tol, int min_iter, float* history, const Dims& dm,
+                     hipStream_t s) {
+  const bool two = dm.n * dm.rp2 <= 2 * kFusedThreads;
+  auto fn = lse ? (two ? &fused_step_kernel<true, 2> : &fused_step_kernel<true, 4>)
+                : (two ? &fused_step_kernel<false, 2> : &fused_step_kernel<false, 4>);
+  fn<<<1, kFusedThreads, 0, s>>>(part, nsplit, a2, s2, x, rr, d, U, st, gram, max_basis,
+                                 reorth ? 1 : 0, tol, min_iter, history, (int)dm.n, dm.r, dm.rp2);
+  GP_HIP(hipGetLastError());
+  return GP_OK;
+}
+
 // ---- a8: true residual from float64-accumulated partial products -------------------
 __global__ void true_res_kernel(const double* __restrict__ part, int nsplit,
                                 const float* __restrict__ B, const float* __restrict__ x,

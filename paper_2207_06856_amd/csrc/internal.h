@@ -345,6 +345,15 @@ gp_status rz_step(const float* rr, const float* z, State* st, bool lse, bool ini
 gp_status direction_step(const float* z, float* d, const float* rr, float* U, float* W,
                          State* st, bool init, bool reorth, uint32_t* colmax, const Dims& dm,
                          hipStream_t s);
+// The step between two float32 products of a small unpreconditioned solve in
+// one launch: from the product's split sums part[nsplit][n][r] of d to the next
+// direction (dq_step .. direction_step with z = r).  `pairs`: an upper bound on
+// the stored pairs.
+bool fused_step_fits(const Dims& dm, bool reorth, int pairs);
+gp_status fused_step(const float* part, int nsplit, float a2, float s2, float* x, float* rr,
+                     float* d, float* U, State* st, float* gram, int max_basis, bool reorth,
+                     bool lse, double tol, int min_iter, float* history, const Dims& dm,
+                     hipStream_t s);
 // true residual: res = b - (a2 * sum + s2 * x) from float64 partials; sets st->true_rel
 gp_status true_residual_finish(const double* part, int nsplit, const float* B, const float* x,
                                float a2, float s2, State* st, double* pd, const Dims& dm,
