@@ -200,29 +200,26 @@ gp_status product(Plan& p, const float* v, float* out, const int* live, hipStrea
   return valu::launch_reduce32(p.part32, p.nsplit32, p.n, p.r, p.kp.a2, p.kp.s2, v, out, live, s);
 }
 
-gp_status quantise(Plan& p, const float* v, bool pow2_from_colmax, const int* live, hipStream_t s) {
-  if (!p.fp16) return GP_OK;
-  if (p.bf16) {
-    __bf16* Vt = as_bf16(p.Vt);
-    if (p.o.scale_mode == 1)
-      return f16::quant_rhs(v, p.n, p.r, p.r, p.rp, p.n_pad, 1, (float)(1.0 / sqrt((double)p.n)),
-                            (float)sqrt((double)p.n), p.colmax, Vt, p.scale, p.inv_scale, s);
-    if (pow2_from_colmax)
-      return f16::quant_only(v, p.n, p.r, p.r, p.rp, p.n_pad, p.colmax, Vt, p.scale, p.inv_scale,
-                             live, s);
-    return f16::quant_rhs(v, p.n, p.r, p.r, p.rp, p.n_pad, 0, 1.0f, 1.0f, p.colmax, Vt, p.scale,
-                          p.inv_scale, s);
-  }
+template <typename T>
+gp_status quantise_t(Plan& p, const float* v, T* Vt, bool pow2_from_colmax, const int* live,
+                     hipStream_t s) {
   const float fs = (float)(1.0 / sqrt((double)p.n));
   const float fi = (float)sqrt((double)p.n);
-  if (p.o.scale_mode == 1)
-    return f16::quant_rhs(v, p.n, p.r, p.r, p.rp, p.n_pad, 1, fs, fi, p.colmax, p.Vt, p.scale,
-                          p.inv_scale, s);
-  if (pow2_from_colmax)
-    return f16::quant_only(v, p.n, p.r, p.r, p.rp, p.n_pad, p.colmax, p.Vt, p.scale, p.inv_scale,
-                           live, s);
-  return f16::quant_rhs(v, p.n, p.r, p.r, p.rp, p.n_pad, 0, fs, fi, p.colmax, p.Vt, p.scale,
-                        p.inv_scale, s);
+  const bool ready = p.o.scale_mode == 0 && pow2_from_colmax;
+  // maxima not taken by the step lie in the partial sums' block until the product
+  // writes it
+  uint32_t* pmax =
+      ready ? p.colmax : reinterpret_cast<uint32_t*>(p.sym ? p.sp.rowpart : p.part16);
+  const f16::Rhs<T> q{v, p.n, p.r, p.r, p.rp, p.n_pad, p.o.scale_mode, fs, fi, pmax, Vt, p.scale,
+                      p.inv_scale};
+  if (ready) return f16::quant(q, 1, live, s);
+  return f16::operands<T>(nullptr, 0, 0, nullptr, nullptr, 0, 0, nullptr, p.kp, &q, s);
+}
+
+gp_status quantise(Plan& p, const float* v, bool pow2_from_colmax, const int* live, hipStream_t s) {
+  if (!p.fp16) return GP_OK;
+  return p.bf16 ? quantise_t(p, v, as_bf16(p.Vt), pow2_from_colmax, live, s)
+                : quantise_t(p, v, p.Vt, pow2_from_colmax, live, s);
 }
 
 // it: 0-based iteration index (the basis holds at most it + 1 pairs).
@@ -371,11 +368,11 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
   GP_TRY(cg::init_state(p.st, B, n, r, p.pd, s, p.dm));
   int mvms = 0;
   if (p.bf16) {
-    GP_TRY(f16::prep_points_bf16(X, n, p.n_pad, p.kp, 0, as_bf16(p.Xr), s));
-    GP_TRY(f16::prep_points_bf16(X, n, p.n_pad, p.kp, 1, as_bf16(p.Xc), s));
+    GP_TRY(f16::operands(X, n, p.n_pad, as_bf16(p.Xr), X, n, p.n_pad, as_bf16(p.Xc), p.kp,
+                         (const f16::Rhs<__bf16>*)nullptr, s));
   } else if (p.fp16) {
-    GP_TRY(f16::prep_points(X, n, p.n_pad, p.kp, 0, p.Xr, s));
-    GP_TRY(f16::prep_points(X, n, p.n_pad, p.kp, 1, p.Xc, s));
+    GP_TRY(f16::operands(X, n, p.n_pad, p.Xr, X, n, p.n_pad, p.Xc, p.kp,
+                         (const f16::Rhs<_Float16>*)nullptr, s));
   } else if (p.f32_split) {
     GP_TRY(split::prepare(p.f32p, p.kp, X, n, X, n, s));
   }

@@ -33,7 +33,7 @@ struct ScratchSource {
 // Scratch bytes of the 16-bit product for a split count.
 static size_t f16_bytes(int64_t n1_pad, int64_t n2_pad, int w, int rp_max, int nsplit) {
   return 2 * (size_t)n1_pad * w + 2 * (size_t)n2_pad * w + 2 * (size_t)rp_max * n2_pad +
-         4 * (size_t)nsplit * n1_pad * rp_max + 12 * (size_t)rp_max + 8 * 256;
+         4 * (size_t)nsplit * n1_pad * rp_max + 8 * (size_t)rp_max + 8 * 256;
 }
 
 // The split count of the rule, or with a fixed block the largest count up to
@@ -73,7 +73,7 @@ static gp_status kmvm_f16_sym(const KParams& kp, const float* X, int64_t n, cons
   const int64_t n_pad = f16::sym_pad(n);
   f16::SymPlan pl = f16::sym_plan(n_pad);
   const size_t bytes = 2 * 2 * (size_t)n_pad * w + 2 * 16 * (size_t)n_pad + f16::sym_bytes(pl) +
-                       12 * 16 + 8 * 256;
+                       8 * 16 + 8 * 256;
   Arena ar;
   *no_room = false;
   if (workspace_get(s, bytes, &ar) == GP_ERR_NOMEM) {
@@ -84,18 +84,17 @@ static gp_status kmvm_f16_sym(const KParams& kp, const float* X, int64_t n, cons
   _Float16* Xr = ar.take<_Float16>((size_t)n_pad * w);
   _Float16* Xc = ar.take<_Float16>((size_t)n_pad * w);
   _Float16* Vt = ar.take<_Float16>((size_t)16 * n_pad);
-  uint32_t* colmax = ar.take<uint32_t>(16);
   float* scale = ar.take<float>(16);
   float* inv_scale = ar.take<float>(16);
   if (!inv_scale) return set_error(GP_ERR_NOMEM, "internal: workspace sizing");
   GP_TRY(f16::sym_carve(pl, ar));
   GP_TRY(f16::sym_prepare(pl, s));
-  GP_TRY(f16::prep_points(X, n, n_pad, kp, 0, Xr, s));
-  GP_TRY(f16::prep_points(X, n, n_pad, kp, 1, Xc, s));
+  // the maxima lie in the partial sums' block: read before the product writes it
+  uint32_t* pmax = reinterpret_cast<uint32_t*>(pl.rowpart);
   const float fs = (float)(1.0 / sqrt((double)n));
   const float fi = (float)sqrt((double)n);
-  GP_TRY(f16::quant_rhs(V, n, r, r, 16, n_pad, scale_mode, fs, fi, colmax, Vt, scale, inv_scale,
-                        s));
+  const f16::Rhs<_Float16> q{V, n, r, r, 16, n_pad, scale_mode, fs, fi, pmax, Vt, scale, inv_scale};
+  GP_TRY(f16::operands(X, n, n_pad, Xr, X, n, n_pad, Xc, kp, &q, s));
   GP_TRY(f16::sym_launch(kp.kind, pl, Xr, Xc, Vt, nullptr, (double)n * (double)n, s));
   return f16::sym_reduce(pl, n, r, inv_scale, kp.a2, kp.s2, add_noise ? V : nullptr, r, out, r,
                          nullptr, s);
@@ -126,21 +125,24 @@ static gp_status kmvm_f16(const KParams& kp, const float* X1, int64_t n1, const 
   _Float16* Xc = ar.take<_Float16>((size_t)n2_pad * w);
   _Float16* Vt = ar.take<_Float16>((size_t)rp_max * n2_pad);
   float* part = ar.take<float>((size_t)nsplit * n1_pad * rp_max);
-  uint32_t* colmax = ar.take<uint32_t>(rp_max);
+  // the maxima lie in the partial sums' block (at least 256 rows of rp_max): read
+  // before a product writes it, written after the sums before it are reduced
+  uint32_t* pmax = reinterpret_cast<uint32_t*>(part);
   float* scale = ar.take<float>(rp_max);
   float* inv_scale = ar.take<float>(rp_max);
   if (!inv_scale) return set_error(GP_ERR_NOMEM, "internal: workspace sizing");
 
-  GP_TRY(f16::prep_points(X1, n1, n1_pad, kp, 0, Xr, s));
-  GP_TRY(f16::prep_points(X2, n2, n2_pad, kp, 1, Xc, s));
   const float fs = (float)(1.0 / sqrt((double)std::max<int64_t>(n2, 1)));
   const float fi = (float)sqrt((double)std::max<int64_t>(n2, 1));
   for (int c0 = 0; c0 < r; c0 += 64) {
     const int rc = std::min(64, r - c0);
     const int rb = (int)ceil_div(rc, 16);
     const int rp = 16 * rb;
-    GP_TRY(f16::quant_rhs(V + c0, n2, rc, r, rp, n2_pad, scale_mode, fs, fi, colmax, Vt, scale,
-                          inv_scale, s));
+    const bool first = c0 == 0;
+    const f16::Rhs<_Float16> q{V + c0, n2, rc, r, rp, n2_pad, scale_mode, fs, fi, pmax, Vt,
+                             scale, inv_scale};
+    GP_TRY(f16::operands(X1, n1, n1_pad, first ? Xr : nullptr, X2, n2, n2_pad,
+                         first ? Xc : nullptr, kp, &q, s));
     GP_TRY(f16::launch_main(kp.kind, kc, rb, Xr, Xc, Vt, part, n1_pad, n2_pad, nsplit, nullptr,
                              (double)n1 * (double)n2, s));
     GP_TRY(f16::launch_reduce(part, nsplit, n1, n1_pad, rc, rp, inv_scale, kp.a2, kp.s2,
@@ -169,21 +171,24 @@ static gp_status kmvm_bf16(const KParams& kp, const float* X1, int64_t n1, const
   __bf16* Xc = ar.take<__bf16>((size_t)n2_pad * w);
   __bf16* Vt = ar.take<__bf16>((size_t)rp_max * n2_pad);
   float* part = ar.take<float>((size_t)nsplit * n1_pad * rp_max);
-  uint32_t* colmax = ar.take<uint32_t>(rp_max);
+  // the maxima lie in the partial sums' block (at least 256 rows of rp_max): read
+  // before a product writes it, written after the sums before it are reduced
+  uint32_t* pmax = reinterpret_cast<uint32_t*>(part);
   float* scale = ar.take<float>(rp_max);
   float* inv_scale = ar.take<float>(rp_max);
   if (!inv_scale) return set_error(GP_ERR_NOMEM, "internal: workspace sizing");
 
-  GP_TRY(f16::prep_points_bf16(X1, n1, n1_pad, kp, 0, Xr, s));
-  GP_TRY(f16::prep_points_bf16(X2, n2, n2_pad, kp, 1, Xc, s));
   const float fs = (float)(1.0 / sqrt((double)std::max<int64_t>(n2, 1)));
   const float fi = (float)sqrt((double)std::max<int64_t>(n2, 1));
   for (int c0 = 0; c0 < r; c0 += 64) {
     const int rc = std::min(64, r - c0);
     const int rb = (int)ceil_div(rc, 16);
     const int rp = 16 * rb;
-    GP_TRY(f16::quant_rhs(V + c0, n2, rc, r, rp, n2_pad, scale_mode, fs, fi, colmax, Vt, scale,
-                          inv_scale, s));
+    const bool first = c0 == 0;
+    const f16::Rhs<__bf16> q{V + c0, n2, rc, r, rp, n2_pad, scale_mode, fs, fi, pmax, Vt,
+                             scale, inv_scale};
+    GP_TRY(f16::operands(X1, n1, n1_pad, first ? Xr : nullptr, X2, n2, n2_pad,
+                         first ? Xc : nullptr, kp, &q, s));
     GP_TRY(f16::launch_main_bf16(kp.kind, kc, rb, Xr, Xc, Vt, part, n1_pad, n2_pad, nsplit, nullptr,
                                  (double)n1 * (double)n2, s));
     GP_TRY(f16::launch_reduce(part, nsplit, n1, n1_pad, rc, rp, inv_scale, kp.a2, kp.s2,

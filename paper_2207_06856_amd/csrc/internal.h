@@ -111,24 +111,38 @@ constexpr int kStageCols = 128;      // columns per LDS stage
 inline int aug_width(int d) { return (int)round_up(2 * d + 4, 32); }
 inline int aug_width_bf16(int d) { return (int)round_up(3 * d + 6, 32); }
 
-// Prepared operands of one point set: augmented binary16 rows.
-gp_status prep_points(const float* X, int64_t n, int64_t n_pad, const KParams& kp, int side,
-                      _Float16* out, hipStream_t s);
+// Right-hand sides V (n x r, row stride ld) and their scaled, transposed 16-bit
+// copy Vt (rp x n_pad, rp <= 64) with the per-column scales.  scale_mode 0: power
+// of two from the column maxima; 1: fixed_scale for every column.  pmax: scratch
+// for the maxima, kMaxGroups x r uint32.
+constexpr int kMaxGroups = 256;
+template <typename T>
+struct Rhs {
+  const float* V;
+  int64_t n;
+  int r;
+  int64_t ld;
+  int rp;
+  int64_t n_pad;
+  int scale_mode;
+  float fixed_scale, fixed_inv;
+  uint32_t* pmax;
+  T* Vt;
+  float* scale;
+  float* inv_scale;
+};
 
-// Scaled, transposed binary16 copy of V (n x r, row stride ld) as Vt
-// (rp x n_pad) and per-column scales.  colmax must hold rp uint32 (cleared
-// here).  scale_mode 0: power of two; 1: fixed_scale for every column.
-gp_status quant_rhs(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                    int scale_mode, float fixed_scale, float fixed_inv, uint32_t* colmax,
-                    _Float16* Vt, float* scale, float* inv_scale, hipStream_t s);
-gp_status quant_rhs(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                    int scale_mode, float fixed_scale, float fixed_inv, uint32_t* colmax,
-                    __bf16* Vt, float* scale, float* inv_scale, hipStream_t s);
-
-// bfloat16 operands: inputs divided by the lengthscale rounded to bfloat16,
-// column-side factors in three bfloat16 parts (width aug_width_bf16(d)).
-gp_status prep_points_bf16(const float* X, int64_t n, int64_t n_pad, const KParams& kp, int side,
-                           __bf16* out, hipStream_t s);
+// The operands of a product (T = _Float16 or __bf16): the augmented rows of
+// either side (null: left out) and, if given, the right-hand sides.  bfloat16
+// operands: inputs divided by the lengthscale rounded to bfloat16, column-side
+// factors in three bfloat16 parts (width aug_width_bf16(d)).
+template <typename T>
+gp_status operands(const float* X1, int64_t n1, int64_t n1_pad, T* Xr, const float* X2, int64_t n2,
+                   int64_t n2_pad, T* Xc, const KParams& kp, const Rhs<T>* rhs, hipStream_t s);
+// The right-hand sides alone, from `groups` rows of maxima in pmax.  A launch
+// with *live == 0 does nothing.
+template <typename T>
+gp_status quant(const Rhs<T>& q, int groups, const int* live, hipStream_t s);
 
 // The fused product with bfloat16 operands (no stage lists).
 gp_status launch_main_bf16(int kind, int kc, int rb, const __bf16* Xr, const __bf16* Xc,
@@ -153,15 +167,6 @@ gp_status launch_main(int kind, int kc, int rb, const _Float16* Xr, const _Float
                       const _Float16* Vt, float* part, int64_t n1_pad, int64_t n2_pad,
                       int nsplit, const int* live, double entries, hipStream_t s,
                       const StageLists* sl = nullptr);
-
-// Quantise V with the per-column maxima already in colmax (no clearing, no
-// max pass): the solver's direction kernel produces colmax itself.
-gp_status quant_only(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                     const uint32_t* colmax, _Float16* Vt, float* scale, float* inv_scale,
-                     const int* live, hipStream_t s);
-gp_status quant_only(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                     const uint32_t* colmax, __bf16* Vt, float* scale, float* inv_scale,
-                     const int* live, hipStream_t s);
 
 // out[i][c] = a2 * inv_scale[c] * sum_x part[x][i][c] + s2 * V[i][c] (V may be
 // null); V and out have row strides ldv and ldo.

@@ -26,77 +26,6 @@
 namespace gpmi {
 namespace f16 {
 
-typedef Vec<__bf16>::v8 b8;
-
-__device__ __forceinline__ float bf_round(float x) { return (float)(__bf16)x; }
-
-// One thread writes 8 consecutive elements of one augmented row.
-__global__ void prep_points_bf16_kernel(const float* __restrict__ X, int64_t n, int64_t n_pad,
-                                        KParams kp, int side, int kp_width, float alpha,
-                                        float beta, __bf16* __restrict__ out) {
-  const int chunks = kp_width / 8;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_pad * chunks) return;
-  const int64_t i = t / chunks;
-  const int c = (int)(t % chunks);
-  b8 o;
-  for (int q = 0; q < 8; ++q) o[q] = (__bf16)0.0f;
-  if (i < n) {
-    const int d = kp.d;
-    const float* x = X + i * d;
-    float nrm = 0.0f;
-    for (int m = 0; m < d; ++m) {
-      const float h = bf_round(x[m] / kp.ls[m]);
-      nrm = fmaf(h, h, nrm);
-    }
-    const float bn = beta * nrm;
-    const float bn0 = bf_round(bn);
-    const float bn1 = bf_round(bn - bn0);
-    const float bn2 = bf_round(bn - bn0 - bn1);
-    for (int q = 0; q < 8; ++q) {
-      const int p = c * 8 + q;
-      float v = 0.0f;
-      if (p < 3 * d) {
-        const int part = p / d, m = p % d;
-        const float h = bf_round(x[m] / kp.ls[m]);
-        if (side == 0) {
-          v = h;
-        } else {
-          const float ax = alpha * h;
-          const float a0 = bf_round(ax);
-          const float a1 = bf_round(ax - a0);
-          v = part == 0 ? a0 : part == 1 ? a1 : ax - a0 - a1;
-        }
-      } else if (p < 3 * d + 6) {
-        const int e = p - 3 * d;       // 0..5
-        const bool norm_slot = side == 1 ? e < 3 : e >= 3;
-        if (norm_slot) {
-          const int part = e % 3;
-          v = part == 0 ? bn0 : part == 1 ? bn1 : bn2;
-        } else {
-          v = 1.0f;
-        }
-      }
-      o[q] = (__bf16)v;
-    }
-  }
-  *reinterpret_cast<b8*>(out + i * kp_width + c * 8) = o;
-}
-
-gp_status prep_points_bf16(const float* X, int64_t n, int64_t n_pad, const KParams& kp, int side,
-                           __bf16* out, hipStream_t s) {
-  const int w = aug_width_bf16(kp.d);
-  const float c = arg_scale(kp.kind);
-  const float alpha = kp.kind == GP_KERNEL_RBF ? c : -2.0f * c;
-  const float beta = kp.kind == GP_KERNEL_RBF ? -0.5f * c : c;
-  const int64_t total = n_pad * (w / 8);
-  if (total == 0) return GP_OK;
-  prep_points_bf16_kernel<<<(unsigned)ceil_div(total, 256), 256, 0, s>>>(X, n, n_pad, kp, side, w,
-                                                                         alpha, beta, out);
-  GP_HIP(hipGetLastError());
-  return GP_OK;
-}
-
 template <int KIND, int KC, int RB>
 __global__ __launch_bounds__(256) void kmvm_bf16_main(const __bf16* __restrict__ Xr,
                                                       const __bf16* __restrict__ Xc,

@@ -8,7 +8,7 @@
 //   acc_I += K_IJ V_J.
 // Both contractions run on v_mfma_f32_16x16x32_f16 with float32 accumulation.
 // The exponent argument is produced by the first MFMA directly: the operands
-// are augmented rows (built once by prep_points) whose dot product is
+// are augmented rows (built once by operands) whose dot product is
 //   alpha * <x_i, x_j> + beta * (n_i + n_j),        n = ||x_hat||^2,
 // with (alpha, beta) = (c, -c/2) for the RBF kernel (so S = -c r^2 / 2 and
 // K = exp2(S), c = log2 e) and (-2c, c) for the Matern family (S = c r^2 with
@@ -38,98 +38,94 @@
 namespace gpmi {
 namespace f16 {
 
-// ---- a1: augmented binary16 operands ------------------------------------
-// One thread writes 8 consecutive halfs of one row.  side 0 = row points (B
-// operand of the first MFMA), side 1 = column points (A operand).
-//   side 1: [hi(alpha x), lo(alpha x), hi(beta n), lo(beta n), 1, 1, 0...]
-//   side 0: [x, x, 1, 1, hi(beta n), lo(beta n), 0...]
-__global__ void prep_points_kernel(const float* __restrict__ X, int64_t n, int64_t n_pad,
-                                   KParams kp, int side, int kp_width, float alpha, float beta,
-                                   _Float16* __restrict__ out) {
-  const int chunks = kp_width / 8;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_pad * chunks) return;
-  const int64_t i = t / chunks;
-  const int c = (int)(t % chunks);
-  h8 o;
-  for (int q = 0; q < 8; ++q) o[q] = (_Float16)0.0f;
-  if (i < n) {
-    const int d = kp.d;
-    const float* x = X + i * d;
+// ---- a1: augmented 16-bit operands --------------------------------------
+// Side 0 = row points (B operand of the first MFMA), side 1 = column points (A
+// operand), ax = alpha x, bn = beta n:
+//   binary16, side 1: [hi(ax), lo(ax), hi(bn), lo(bn), 1, 1, 0...]
+//   binary16, side 0: [x, x, 1, 1, hi(bn), lo(bn), 0...]
+//   bfloat16: three parts instead of two, widths as in kmvm_bf16.hip.
+//
+// The two sides and the right-hand sides' column maxima do not depend on each
+// other: work groups of one launch take them.  A product of a few hundred
+// points costs its launches (seven took 34 us, three take 20), and a row's
+// inputs are divided by the lengthscales once per side, not once per 16-byte
+// chunk: at 10,000 points, d = 16, R = 8, 5.8 us for the 12.2 + 5.0 + 2.9 of
+// separate sides, maxima and clearing.  Bound by latency: one pass of loads,
+// the serial norm, the stores.
+// Points: kPrepRows rows a group, scaled inputs and norm parts in LDS, then one
+// thread per 16-byte chunk.  Maxima: each group writes its own row of pmax,
+// folded by quant_kernel, so that nothing is cleared first; of few right-hand
+// sides every group takes them all, and no second launch is needed.
+constexpr int kPrepRows = 32;
+
+template <typename T>
+__device__ __forceinline__ float round_to(float x) { return (float)(T)x; }
+
+struct PrepSide {
+  const float* X;
+  int64_t n;
+  int groups;        // of kPrepRows padded rows
+  void* out;
+};
+
+template <typename T>
+__device__ __forceinline__ void prep_rows(const PrepSide& ps, const KParams& kp, int side, int w,
+                                          float alpha, float beta, int64_t r0,
+                                          float (*sh)[kMaxDim + 1], float (*sn)[3]) {
+  typedef typename Vec<T>::v8 v8;
+  constexpr int NP = __is_same(T, _Float16) ? 2 : 3;   // parts of a column-side factor
+  const int d = kp.d, tid = threadIdx.x;
+  for (int e = tid; e < kPrepRows * d; e += 256) {
+    const int row = e / d, m = e - row * d;
+    sh[row][m] = r0 + row < ps.n ? round_to<T>(ps.X[r0 * d + e] / kp.ls[m]) : 0.0f;
+  }
+  __syncthreads();
+  if (tid < kPrepRows) {
     float nrm = 0.0f;
-    for (int m = 0; m < d; ++m) {
-      const float h = (float)(_Float16)(x[m] / kp.ls[m]);
-      nrm = fmaf(h, h, nrm);
-    }
-    const float bn = beta * nrm;
-    const _Float16 bn_hi = (_Float16)bn;
-    const _Float16 bn_lo = (_Float16)(bn - (float)bn_hi);
-    for (int q = 0; q < 8; ++q) {
-      const int p = c * 8 + q;
-      _Float16 v = (_Float16)0.0f;
-      if (p < 2 * d) {
-        const int m = p < d ? p : p - d;
-        const float h = (float)(_Float16)(x[m] / kp.ls[m]);
-        if (side == 0) {
-          v = (_Float16)h;
-        } else {
-          const float ax = alpha * h;
-          const _Float16 hi = (_Float16)ax;
-          v = p < d ? hi : (_Float16)(ax - (float)hi);
-        }
-      } else if (p < 2 * d + 4) {
-        const int e = p - 2 * d;       // 0..3
-        if (side == 1)
-          v = e == 0 ? bn_hi : e == 1 ? bn_lo : (_Float16)1.0f;
-        else
-          v = e < 2 ? (_Float16)1.0f : e == 2 ? bn_hi : bn_lo;
-      }
-      o[q] = v;
+    for (int m = 0; m < d; ++m) nrm = fmaf(sh[tid][m], sh[tid][m], nrm);
+    float rest = beta * nrm;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      sn[tid][q] = round_to<T>(rest);
+      rest -= sn[tid][q];
     }
   }
-  *reinterpret_cast<h8*>(out + i * kp_width + c * 8) = o;
-}
-
-gp_status prep_points(const float* X, int64_t n, int64_t n_pad, const KParams& kp, int side,
-                      _Float16* out, hipStream_t s) {
-  const int w = aug_width(kp.d);
-  const float c = arg_scale(kp.kind);
-  const float alpha = kp.kind == GP_KERNEL_RBF ? c : -2.0f * c;
-  const float beta = kp.kind == GP_KERNEL_RBF ? -0.5f * c : c;
-  const int64_t total = n_pad * (w / 8);
-  if (total == 0) return GP_OK;
-  const int threads = 256;
-  prep_points_kernel<<<(unsigned)ceil_div(total, threads), threads, 0, s>>>(X, n, n_pad, kp, side,
-                                                                            w, alpha, beta, out);
-  GP_HIP(hipGetLastError());
-  return GP_OK;
+  __syncthreads();
+  const int chunks = w / 8;
+  T* out = static_cast<T*>(ps.out);
+  for (int e = tid; e < kPrepRows * chunks; e += 256) {
+    const int row = e / chunks, c = e - row * chunks;
+    v8 o;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int p = c * 8 + q;
+      float v = 0.0f;
+      if (p < NP * d) {
+        const int part = p < d ? 0 : p < 2 * d ? 1 : 2;
+        const float h = sh[row][p - part * d];
+        if (side == 0) {
+          v = h;
+        } else {
+          const float ax = alpha * h;
+          const float a0 = round_to<T>(ax);
+          v = part == 0 ? a0 : ax - a0;
+          if (part == 2) v -= round_to<T>(v);
+        }
+      } else if (p < NP * d + 2 * NP) {
+        const int f = p - NP * d;
+        const bool norm_slot = (f < NP) == (side == 1);
+        v = norm_slot ? sn[row][f < NP ? f : f - NP] : 1.0f;
+      }
+      o[q] = (T)v;
+    }
+    if (r0 + row >= ps.n)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) o[q] = (T)0.0f;
+    *reinterpret_cast<v8*>(out + (r0 + row) * w + c * 8) = o;
+  }
 }
 
 // ---- right-hand-side quantisation -----------------------------------------
-__global__ void fill_u32_kernel(uint32_t* p, int n, uint32_t v) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
-// Per-column max |v| as float bits (non-negative floats order like uint32).
-__global__ void colmax_kernel(const float* __restrict__ V, int64_t n, int r, int64_t ld,
-                              uint32_t* __restrict__ colmax) {
-  extern __shared__ uint32_t smax[];
-  for (int c = threadIdx.x; c < r; c += blockDim.x) smax[c] = 0u;
-  __syncthreads();
-  const int64_t total = n * r;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e / r;
-    const int c = (int)(e % r);
-    const uint32_t b = __float_as_uint(fabsf(V[i * ld + c]));
-    atomicMax(&smax[c], b);
-  }
-  __syncthreads();
-  for (int c = threadIdx.x; c < r; c += blockDim.x)
-    if (smax[c]) atomicMax(&colmax[c], smax[c]);
-}
-
 __device__ inline void pow2_scale(uint32_t maxbits, float* s, float* inv) {
   const float m = __uint_as_float(maxbits);
   if (!(m > 0.0f) || !isfinite(m)) {
@@ -143,38 +139,57 @@ __device__ inline void pow2_scale(uint32_t maxbits, float* s, float* inv) {
   *inv = ldexpf(1.0f, e - 15);
 }
 
+// Per-column max |v| as float bits (non-negative floats order like uint32) of
+// the rows group g of `groups` strides over, in smax; r <= 64, so that each
+// thread keeps a column.
+__device__ __forceinline__ void group_max(const float* __restrict__ V, int64_t n, int r,
+                                          int64_t ld, int g, int groups, uint32_t* smax) {
+  const int tid = threadIdx.x;
+  if (tid < 64) smax[tid] = 0u;
+  __syncthreads();
+  const int per = 256 / r, c = tid % r, row = tid / r;
+  uint32_t m = 0u;
+  if (row < per) {
+    const int64_t step = (int64_t)groups * per;
+    for (int64_t i = (int64_t)g * per + row; i < n; i += 8 * step) {
+      uint32_t x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int64_t k = i + u * step;
+        x[u] = __float_as_uint(fabsf(V[(k < n ? k : i) * ld + c]));
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) m = max(m, x[u]);
+    }
+    if (m) atomicMax(&smax[c], m);
+  }
+  __syncthreads();
+}
+
 // Vt[c][i] = T(V[i][c] * s_c) for c < r, i < n; zero padding elsewhere (T is
-// binary16 or bfloat16).  A tiled transpose: a work group reads kQRows rows of
-// V (all rp columns, row-contiguous) into LDS, then each thread writes eight
-// consecutive rows of one column.  rp <= 64.
+// binary16 or bfloat16), s_c from the maxima in smax.  A tiled transpose: a work
+// group reads kQRows rows of V (all rp columns, row-contiguous) into LDS, then
+// each thread writes eight consecutive rows of one column.  rp <= 64.
 constexpr int kQRows = 128;
 template <typename T>
-__global__ __launch_bounds__(256) void quant_kernel(const float* __restrict__ V, int64_t n, int r,
-                                                    int64_t ld, int rp, int64_t n_pad,
-                                                    int scale_mode, float fixed_scale,
-                                                    float fixed_inv,
-                                                    const uint32_t* __restrict__ colmax,
-                                                    T* __restrict__ Vt, float* __restrict__ scale,
-                                                    float* __restrict__ inv_scale,
-                                                    const int* __restrict__ live) {
-  typedef typename Vec<T>::v8 h8;
-  if (live && *live == 0) return;
-  __shared__ float sv[kQRows][64 + 1];
-  __shared__ float ss[64];
-  const int64_t r0 = (int64_t)blockIdx.x * kQRows;
+__device__ __forceinline__ void quant_rows(const Rhs<T>& q, int g, const uint32_t* smax,
+                                           float (*sv)[64 + 1], float* ss) {
+  typedef typename Vec<T>::v8 v8;
+  const int64_t r0 = (int64_t)g * kQRows;
+  const int rp = q.rp, r = q.r;
   if ((int)threadIdx.x < rp) {
     const int c = threadIdx.x;
     float sc = 1.0f, inv = 1.0f;
     if (c < r) {
-      if (scale_mode == 1) {
-        sc = fixed_scale;
-        inv = fixed_inv;
+      if (q.scale_mode == 1) {
+        sc = q.fixed_scale;
+        inv = q.fixed_inv;
       } else {
-        pow2_scale(colmax[c], &sc, &inv);
+        pow2_scale(smax[c], &sc, &inv);
       }
-      if (blockIdx.x == 0) {
-        scale[c] = sc;
-        inv_scale[c] = inv;
+      if (g == 0) {
+        q.scale[c] = sc;
+        q.inv_scale[c] = inv;
       }
     }
     ss[c] = sc;
@@ -183,81 +198,125 @@ __global__ __launch_bounds__(256) void quant_kernel(const float* __restrict__ V,
   for (int e = threadIdx.x; e < kQRows * rp; e += 256) {
     const int row = e / rp, c = e % rp;
     const int64_t i = r0 + row;
-    sv[row][c] = (c < r && i < n) ? V[i * ld + c] * ss[c] : 0.0f;
+    sv[row][c] = (c < r && i < q.n) ? q.V[i * q.ld + c] * ss[c] : 0.0f;
   }
   __syncthreads();
   for (int e = threadIdx.x; e < (kQRows / 8) * rp; e += 256) {
     const int c = e / (kQRows / 8), q0 = (e % (kQRows / 8)) * 8;
     const int64_t i0 = r0 + q0;
-    if (i0 >= n_pad) continue;
-    h8 o;
+    if (i0 >= q.n_pad) continue;
+    v8 o;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) o[q] = (T)sv[q0 + q][c];
-    *reinterpret_cast<h8*>(Vt + (int64_t)c * n_pad + i0) = o;
+    for (int u = 0; u < 8; ++u) o[u] = (T)sv[q0 + u][c];
+    *reinterpret_cast<v8*>(q.Vt + (int64_t)c * q.n_pad + i0) = o;
   }
 }
 
+// Each group folds the `groups` rows of maxima (scale_mode 0) first.
 template <typename T>
-static gp_status quant_rhs_t(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                             int scale_mode, float fixed_scale, float fixed_inv, uint32_t* colmax,
-                             T* Vt, float* scale, float* inv_scale, hipStream_t s) {
-  if (scale_mode == 0) {
-    fill_u32_kernel<<<(unsigned)ceil_div(r, 256), 256, 0, s>>>(colmax, r, 0u);
-    GP_HIP(hipGetLastError());
-    if (n > 0) {
-      const int64_t total = n * r;
-      const int blocks = (int)std::min<int64_t>(1024, ceil_div(total, 256));
-      colmax_kernel<<<blocks, 256, r * sizeof(uint32_t), s>>>(V, n, r, ld, colmax);
-      GP_HIP(hipGetLastError());
+__global__ __launch_bounds__(256) void quant_kernel(Rhs<T> q, int groups,
+                                                    const int* __restrict__ live) {
+  if (live && *live == 0) return;
+  __shared__ float sv[kQRows][64 + 1];
+  __shared__ float ss[64];
+  __shared__ uint32_t smax[64];
+  if (q.scale_mode == 0) {
+    if (threadIdx.x < 64) smax[threadIdx.x] = 0u;
+    __syncthreads();
+    const int per = 256 / q.r, c = threadIdx.x % q.r, g0 = threadIdx.x / q.r;
+    uint32_t m = 0u;
+    if (g0 < per) {
+#pragma unroll 8
+      for (int g = g0; g < groups; g += per) m = max(m, q.pmax[g * q.r + c]);
+      if (m) atomicMax(&smax[c], m);
     }
+    __syncthreads();
   }
-  if (rp > 64) return set_error(GP_ERR_ARG, "internal: %d padded right-hand sides (max 64)", rp);
-  if (n_pad > 0 && rp > 0) {
-    quant_kernel<T><<<(unsigned)ceil_div(n_pad, (int64_t)kQRows), 256, 0, s>>>(
-        V, n, r, ld, rp, n_pad, scale_mode, fixed_scale, fixed_inv, colmax, Vt, scale, inv_scale,
-        nullptr);
-    GP_HIP(hipGetLastError());
-  }
-  return GP_OK;
+  quant_rows(q, (int)blockIdx.x, smax, sv, ss);
 }
 
-gp_status quant_rhs(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                    int scale_mode, float fixed_scale, float fixed_inv, uint32_t* colmax,
-                    _Float16* Vt, float* scale, float* inv_scale, hipStream_t s) {
-  return quant_rhs_t(V, n, r, ld, rp, n_pad, scale_mode, fixed_scale, fixed_inv, colmax, Vt, scale,
-                     inv_scale, s);
+// SMALL: right-hand sides of at most kSmallRhs entries, whose every group takes
+// all the maxima itself and quantises kQRows rows at once.
+template <typename T, bool SMALL>
+__global__ __launch_bounds__(256) void operands_kernel(PrepSide rows, PrepSide cols, KParams kp,
+                                                       int w, float alpha, float beta, Rhs<T> q,
+                                                       int vgroups) {
+  __shared__ float sh[kPrepRows][kMaxDim + 1], sn[kPrepRows][3];
+  __shared__ uint32_t smax[64];
+  int b = blockIdx.x;
+  if (b < vgroups) {
+    if constexpr (SMALL) {
+      __shared__ float sv[kQRows][64 + 1];
+      __shared__ float ss[64];
+      if (q.scale_mode == 0) group_max(q.V, q.n, q.r, q.ld, 0, 1, smax);
+      quant_rows(q, b, smax, sv, ss);
+    } else {
+      group_max(q.V, q.n, q.r, q.ld, b, vgroups, smax);
+      if ((int)threadIdx.x < q.r) q.pmax[(int64_t)b * q.r + threadIdx.x] = smax[threadIdx.x];
+    }
+    return;
+  }
+  b -= vgroups;
+  if (b < rows.groups)
+    prep_rows<T>(rows, kp, 0, w, alpha, beta, (int64_t)b * kPrepRows, sh, sn);
+  else
+    prep_rows<T>(cols, kp, 1, w, alpha, beta, (int64_t)(b - rows.groups) * kPrepRows, sh, sn);
 }
 
-gp_status quant_rhs(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                    int scale_mode, float fixed_scale, float fixed_inv, uint32_t* colmax,
-                    __bf16* Vt, float* scale, float* inv_scale, hipStream_t s) {
-  return quant_rhs_t(V, n, r, ld, rp, n_pad, scale_mode, fixed_scale, fixed_inv, colmax, Vt, scale,
-                     inv_scale, s);
-}
+// Where the line lies: every group reads all of them, 64 loads a thread here.  One
+// launch instead of two: n = 1000, R = 16 22.8 -> 20.3 us, n = 16,000, R = 1 51.8 ->
+// 49.4; at 64,000 entries n = 4000, R = 16 22.4 -> 24.4, n = 16,000, R = 4 52.2 -> 58.2.
+constexpr int64_t kSmallRhs = 16384;
 
 template <typename T>
-static gp_status quant_only_t(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                              const uint32_t* colmax, T* Vt, float* scale, float* inv_scale,
-                              const int* live, hipStream_t s) {
-  if (rp > 64) return set_error(GP_ERR_ARG, "internal: %d padded right-hand sides (max 64)", rp);
-  if (n_pad == 0 || rp == 0) return GP_OK;
-  quant_kernel<T><<<(unsigned)ceil_div(n_pad, (int64_t)kQRows), 256, 0, s>>>(
-      V, n, r, ld, rp, n_pad, 0, 1.0f, 1.0f, colmax, Vt, scale, inv_scale, live);
+gp_status quant(const Rhs<T>& q, int groups, const int* live, hipStream_t s) {
+  if (q.rp > 64 || q.r < 1 || q.r > q.rp)
+    return set_error(GP_ERR_ARG, "internal: %d padded right-hand sides (max 64)", q.rp);
+  if (q.n_pad == 0) return GP_OK;
+  quant_kernel<T><<<(unsigned)ceil_div(q.n_pad, (int64_t)kQRows), 256, 0, s>>>(q, groups, live);
   GP_HIP(hipGetLastError());
   return GP_OK;
 }
 
-gp_status quant_only(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                     const uint32_t* colmax, _Float16* Vt, float* scale, float* inv_scale,
-                     const int* live, hipStream_t s) {
-  return quant_only_t(V, n, r, ld, rp, n_pad, colmax, Vt, scale, inv_scale, live, s);
+template <typename T>
+gp_status operands(const float* X1, int64_t n1, int64_t n1_pad, T* Xr, const float* X2, int64_t n2,
+                   int64_t n2_pad, T* Xc, const KParams& kp, const Rhs<T>* rhs, hipStream_t s) {
+  const Rhs<T> q = rhs ? *rhs : Rhs<T>{};
+  if (rhs && (q.rp > 64 || q.r < 1 || q.r > q.rp))
+    return set_error(GP_ERR_ARG, "internal: %d padded right-hand sides (max 64)", q.rp);
+  if ((Xr && n1_pad % kPrepRows) || (Xc && n2_pad % kPrepRows))
+    return set_error(GP_ERR_ARG, "internal: operand rows not padded");
+  const int w = __is_same(T, _Float16) ? aug_width(kp.d) : aug_width_bf16(kp.d);
+  const float c = arg_scale(kp.kind);
+  const float alpha = kp.kind == GP_KERNEL_RBF ? c : -2.0f * c;
+  const float beta = kp.kind == GP_KERNEL_RBF ? -0.5f * c : c;
+  const PrepSide rows{X1, n1, Xr ? (int)(n1_pad / kPrepRows) : 0, Xr};
+  const PrepSide cols{X2, n2, Xc ? (int)(n2_pad / kPrepRows) : 0, Xc};
+  const bool small = rhs && q.n * q.r <= kSmallRhs;
+  // maxima: eight loads a thread, at most one group per compute unit
+  const int vgroups =
+      !rhs ? 0
+      : small ? (int)ceil_div(q.n_pad, (int64_t)kQRows)
+      : q.scale_mode == 0 ? (int)std::min<int64_t>(kMaxGroups, ceil_div(q.n * q.r, 2048)) : 0;
+  const unsigned grid = (unsigned)(rows.groups + cols.groups + vgroups);
+  if (grid > 0) {
+    if (small)
+      operands_kernel<T, true><<<grid, 256, 0, s>>>(rows, cols, kp, w, alpha, beta, q, vgroups);
+    else
+      operands_kernel<T, false><<<grid, 256, 0, s>>>(rows, cols, kp, w, alpha, beta, q, vgroups);
+    GP_HIP(hipGetLastError());
+  }
+  return rhs && !small ? quant(q, vgroups, nullptr, s) : GP_OK;
 }
 
-gp_status quant_only(const float* V, int64_t n, int r, int64_t ld, int rp, int64_t n_pad,
-                     const uint32_t* colmax, __bf16* Vt, float* scale, float* inv_scale,
-                     const int* live, hipStream_t s) {
-  return quant_only_t(V, n, r, ld, rp, n_pad, colmax, Vt, scale, inv_scale, live, s);
-}
+template gp_status quant<_Float16>(const Rhs<_Float16>&, int, const int*, hipStream_t);
+template gp_status quant<__bf16>(const Rhs<__bf16>&, int, const int*, hipStream_t);
+template gp_status operands<_Float16>(const float*, int64_t, int64_t, _Float16*, const float*,
+                                      int64_t, int64_t, _Float16*, const KParams&,
+                                      const Rhs<_Float16>*, hipStream_t);
+template gp_status operands<__bf16>(const float*, int64_t, int64_t, __bf16*, const float*, int64_t,
+                                    int64_t, __bf16*, const KParams&, const Rhs<__bf16>*,
+                                    hipStream_t);
 
 // ---- a2: fused product ------------------------------------------------------
 // First position p in [0, cnt) with list[p] >= v (list increasing).
@@ -372,19 +431,32 @@ gp_status launch_main(int kind, int kc, int rb, const _Float16* Xr, const _Float
   return st;
 }
 
-__global__ void reduce_kernel(const float* __restrict__ part, int nsplit, int64_t n1,
-                              int64_t n1_pad, int r, int rp, const float* __restrict__ inv_scale,
-                              float a2, float s2, const float* __restrict__ V, int64_t ldv,
-                              float* __restrict__ out, int64_t ldo, const int* __restrict__ live) {
+// One thread per output, the split sums in split order with 16 loads in flight
+// (the sum of many splits is otherwise as many dependent trips to memory: 56 of
+// 10,000 x 8, 37 MB with the padding, 16.1 -> 7.5 us).
+__global__ __launch_bounds__(256) void reduce_kernel(
+    const float* __restrict__ part, int nsplit, int64_t n1, int64_t n1_pad, int r, int rp,
+    const float* __restrict__ inv_scale, float a2, float s2, const float* __restrict__ V,
+    int64_t ldv, float* __restrict__ out, int64_t ldo, const int* __restrict__ live) {
   if (live && *live == 0) return;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n1 * r) return;
   const int64_t i = e / r;
   const int c = (int)(e % r);
+  const float vi = V ? V[i * ldv + c] : 0.0f, inv = inv_scale[c];
+  const float* p = part + i * rp + c;
+  const int64_t step = n1_pad * rp;
   float acc = 0.0f;
-  for (int x = 0; x < nsplit; ++x) acc += part[((int64_t)x * n1_pad + i) * rp + c];
-  float o = (a2 * inv_scale[c]) * acc;
-  if (V) o = fmaf(s2, V[i * ldv + c], o);
+  for (int x = 0; x < nsplit; x += 16) {
+    float t[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) t[u] = x + u < nsplit ? p[(x + u) * step] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (x + u < nsplit) acc += t[u];
+  }
+  float o = (a2 * inv) * acc;
+  if (V) o = fmaf(s2, vi, o);
   out[i * ldo + c] = o;
 }
 
@@ -407,6 +479,13 @@ int choose_splits(int64_t n1_pad, int64_t n2_pad) {
   int64_t want = ceil_div(2048, std::max<int64_t>(rblocks, 1));
   want = round_up(std::max<int64_t>(want, 8), 8);
   want = std::min<int64_t>(want, 64);
+  // but no shorter than 8 stages while 512 groups remain: a group's start (row
+  // operands, first stage) takes as long as two stages, and its sums are written
+  // and read once per split.  n = 8000, R = 16: 63 splits 33.5 us, 16 27.6; n = 10000,
+  // R = 8: 56 splits 38.8, 16 34.7 (256 groups: 8 splits 36.8); at 50,000 points 16
+  // splits 608 us, 8 645.
+  want = std::min(want, std::max(round_up(ceil_div(512, std::max<int64_t>(rblocks, 1)), 8),
+                                 nstage / 64 * 8));
   const int rule = (int)std::max<int64_t>(1, std::min<int64_t>(want, nstage));
   return tune::f16_splits(n1_pad, n2_pad, rule);
 }

@@ -245,13 +245,13 @@ extern "C" gp_status gp_kmvm_summation(const gp_kernel* k, const float* X1, int6
   const int64_t n2_pad = round_up(n2, hsum::kStage);
   constexpr int kRc = 16;
   const size_t bytes = 4 * (size_t)n1_pad * dm + 4 * (size_t)n2_pad * dm +
-                       2 * (size_t)kRc * n2_pad + 12 * (size_t)kRc + 8 * 256;
+                       2 * (size_t)kRc * n2_pad + 4 * (size_t)(f16::kMaxGroups + 2) * kRc + 8 * 256;
   Arena ar;
   GP_TRY(workspace_get(s, bytes, &ar));
   float* Xh1 = ar.take<float>((size_t)n1_pad * dm);
   float* Xh2 = ar.take<float>((size_t)n2_pad * dm);
   _Float16* Vt = ar.take<_Float16>((size_t)kRc * n2_pad);
-  uint32_t* colmax = ar.take<uint32_t>(kRc);
+  uint32_t* pmax = ar.take<uint32_t>(f16::kMaxGroups * kRc);
   float* scale = ar.take<float>(kRc);
   float* inv_scale = ar.take<float>(kRc);
   if (!inv_scale) return set_error(GP_ERR_NOMEM, "internal: workspace sizing");
@@ -267,8 +267,9 @@ extern "C" gp_status gp_kmvm_summation(const gp_kernel* k, const float* X1, int6
   for (int c0 = 0; c0 < r; c0 += kRc) {
     const int rc = std::min(kRc, r - c0);
     const int rcmax = rc == 1 ? 1 : rc <= 4 ? 4 : 16;
-    GP_TRY(f16::quant_rhs(V + c0, n2, rc, r, rcmax, n2_pad, scale_mode, fs, fi, colmax, Vt, scale,
-                          inv_scale, s));
+    const f16::Rhs<_Float16> q{V + c0, n2, rc, r, rcmax, n2_pad, scale_mode, fs, fi, pmax, Vt,
+                               scale, inv_scale};
+    GP_TRY(f16::operands<_Float16>(nullptr, 0, 0, nullptr, nullptr, 0, 0, nullptr, kp, &q, s));
     hsum::Args a{Xh1, Xh2, n1, n2, n2_pad, Vt, rc, block, inv_scale, kp.a2, kp.s2,
                  add_noise ? V + c0 : nullptr, r, out + c0, r};
     GP_TRY(hsum::launch(kp.kind, scheme, rcmax, dm, a, s));

@@ -314,7 +314,7 @@ extern "C" gp_status gp_kmvm_truncated(const gp_kernel* k, const float* X1, int6
                        4 * (size_t)n1 * r + 2 * (size_t)n1_pad * w + 2 * (size_t)n2_pad * w +
                        2 * (size_t)rp_max * n2_pad + 4 * (size_t)nsplit * n1_pad * rp_max +
                        8 * (size_t)(nrb + nstage) * d + 4 * (size_t)nrb * nstage + 4 * (size_t)nrb +
-                       12 * (size_t)rp_max + 32 * 256;
+                       8 * (size_t)rp_max + 32 * 256;
   Arena ar;
   GP_TRY(workspace_get(s, bytes, &ar));
   int* perm1 = ar.take<int>((size_t)n1);
@@ -331,7 +331,6 @@ extern "C" gp_status gp_kmvm_truncated(const gp_kernel* k, const float* X1, int6
   float* cbox = ar.take<float>((size_t)nstage * 2 * d);
   int* lists = ar.take<int>((size_t)nrb * nstage);
   int* counts = ar.take<int>((size_t)nrb);
-  uint32_t* colmax = ar.take<uint32_t>(rp_max);
   float* scale = ar.take<float>(rp_max);
   float* inv_scale = ar.take<float>(rp_max);
   if (!perm2 || !X2s || !Vs || !outs || !Xr || !Xc || !Vt || !part || !rbox || !cbox || !lists ||
@@ -349,8 +348,6 @@ extern "C" gp_status gp_kmvm_truncated(const gp_kernel* k, const float* X1, int6
   }
   trunc::gather_kernel<<<(unsigned)ceil_div(n2 * r, 256), 256, 0, s>>>(V, perm2, n2, r, Vs);
   GP_HIP(hipGetLastError());
-  GP_TRY(f16::prep_points(X1s, n1, n1_pad, kp, 0, Xr, s));
-  GP_TRY(f16::prep_points(X2s, n2, n2_pad, kp, 1, Xc, s));
 
   // 2-3. boxes and stage lists
   trunc::box_kernel<<<(unsigned)nrb, 256, 0, s>>>(X1s, n1, kp, f16::kRowsPerBlock, rbox);
@@ -368,8 +365,13 @@ extern "C" gp_status gp_kmvm_truncated(const gp_kernel* k, const float* X1, int6
     const int rc = std::min(64, r - c0);
     const int rb = (int)ceil_div(rc, 16);
     const int rp = 16 * rb;
-    GP_TRY(f16::quant_rhs(Vs + c0, n2, rc, r, rp, n2_pad, 0, 1.0f, 1.0f, colmax, Vt, scale,
-                          inv_scale, s));
+    const bool first = c0 == 0;
+    // the maxima lie in the partial sums' block until the product writes it
+    uint32_t* pmax = reinterpret_cast<uint32_t*>(part);
+    const f16::Rhs<_Float16> q{Vs + c0, n2, rc, r, rp, n2_pad, 0, 1.0f, 1.0f, pmax, Vt, scale,
+                               inv_scale};
+    GP_TRY(f16::operands(X1s, n1, n1_pad, first ? Xr : nullptr, X2s, n2, n2_pad,
+                         first ? Xc : nullptr, kp, &q, s));
     GP_TRY(f16::launch_main(kp.kind, kc, rb, Xr, Xc, Vt, part, n1_pad, n2_pad, nsplit, nullptr,
                              (double)n1 * (double)n2, s, &sl));
     GP_TRY(f16::launch_reduce(part, nsplit, n1, n1_pad, rc, rp, inv_scale, kp.a2, kp.s2,
