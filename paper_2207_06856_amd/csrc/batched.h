@@ -18,8 +18,9 @@
 namespace gpmi {
 namespace bt {
 
-constexpr int kChunkRows = 512;    // rows per reduction / elementwise chunk
-constexpr int kJGroup = 8;         // basis vectors per re-orthogonalisation work group
+constexpr int kChunkRows = 512;    // rows per reduction chunk
+constexpr int kSub = 4;            // quarters of a chunk, for work that no sum crosses
+constexpr int kJGroup = 4;         // basis vectors per re-orthogonalisation work group
 
 // vector selectors (Seg::v)
 enum : int { VB = 0, VX = 1, VR = 2, VZ = 3, VD = 4, VQ = 5, kNumVec = 6 };
@@ -53,9 +54,9 @@ struct Seg {
   float* c1;             // (max_iter + 1) x r first-pass coefficients
   float* gram;           // (max_iter + 1)^2 x r basis Gram matrix w_j^T u_k
   float* ltpart;         // nchunk x rank x r
-  double* pv;            // nchunk argmax value
-  double* psum;          // nchunk diagonal sum
-  int64_t* pi;           // nchunk argmax index
+  double* pv;            // 2 x quarter chunks: argmax value (by step parity)
+  double* psum;          // 2 x quarter chunks: diagonal sum
+  int64_t* pi;           // 2 x quarter chunks: argmax index
   int64_t n, n_pad_r, n_pad_c;
   double tol;
   int r, rb, rp, d, w, kc, kind, nsplit, nsplit64, rank, nchunk, max_iter, min_iter;

@@ -24,6 +24,25 @@ namespace bt {
 using cg::kMaxR;
 using cg::State;
 
+// Rows of a chunk in quarters, for work that no sum crosses: block b of a launch
+// of kSub x nchunks takes quarter b % kSub of chunk b / kSub, k its index among the
+// problem's quarters (empty past the problem's end: i0 >= i1).  Dozens of problems
+// of a few thousand rows give too few chunks to hide the latency of their loads
+// (48 problems, 250,000 rows: 500), while a chunk's float32 sums keep the order
+// that 512 rows give them.
+constexpr int kSubRows = kChunkRows / kSub;
+__device__ __forceinline__ Chunk sub_chunk(const Chunk* __restrict__ chunks, int b) {
+  Chunk ck = chunks[b / kSub];
+  const int q = b % kSub;
+  ck.k = ck.k * kSub + q;
+  ck.i0 += q * kSubRows;
+  ck.i1 = min(ck.i1, ck.i0 + kSubRows);
+  return ck;
+}
+__host__ __device__ __forceinline__ int sub_chunks_of(int64_t n) {
+  return (int)ceil_div(n, (int64_t)kSubRows);
+}
+
 __device__ __forceinline__ int pow2_at_least(int r) {
   int p = 1;
   while (p < r) p <<= 1;
@@ -36,7 +55,8 @@ __device__ __forceinline__ int pow2_at_least(int r) {
 // binary16, so that one binary16 product gives the kernel argument.  Both
 // sides of a chunk's rows; the last chunk also writes the zero padding.
 __global__ void prep_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks) {
-  const Chunk ck = chunks[blockIdx.x];
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   const Seg& sg = segs[ck.p];
   const int w = sg.w;
   const int g8 = w / 8;
@@ -99,7 +119,8 @@ __global__ void quant_kernel(const Seg* __restrict__ segs, const Chunk* __restri
                              int vsel, const uint32_t* __restrict__ colmax, int scale_mode,
                              float* __restrict__ scale, float* __restrict__ inv_scale,
                              const int* __restrict__ live) {
-  const Chunk ck = chunks[blockIdx.x];
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   if (live && live[ck.p] == 0) return;
   const Seg& sg = segs[ck.p];
   __shared__ float ss[kMaxR];
@@ -262,7 +283,8 @@ __global__ void reset_counter_kernel(int* counter) { *counter = 0; }
 __global__ void reduce_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks,
                               const float* __restrict__ inv_scale, int vsel, int osel,
                               const int* __restrict__ live) {
-  const Chunk ck = chunks[blockIdx.x];
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   if (live && live[ck.p] == 0) return;
   const Seg& sg = segs[ck.p];
   const int r = sg.r;
@@ -299,13 +321,24 @@ __global__ void colred_kernel(const Seg* __restrict__ segs, const Chunk* __restr
   const float* a = sg.v[asel];
   const float* b = sg.v[bsel];
   if (c < r)
-    for (int64_t i = ck.i0 + ty; i < ck.i1; i += tys) {
-      const float x = a[i * r + c], y = b[i * r + c];
-      q2 = fmaf(x, x, q2);
-      if (LSE)
-        lse_push(m, S, x, y);
-      else
-        S = fmaf(x, y, S);
+    for (int64_t i = ck.i0 + ty; i < ck.i1; i += 8 * tys) {
+      // sixteen loads in flight
+      float x[8], y[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int64_t k = i + u * tys < ck.i1 ? i + u * tys : i;
+        x[u] = a[k * r + c];
+        y[u] = b[k * r + c];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (i + u * tys >= ck.i1) break;
+        q2 = fmaf(x[u], x[u], q2);
+        if (LSE)
+          lse_push(m, S, x[u], y[u]);
+        else
+          S = fmaf(x[u], y[u], S);
+      }
     }
   sm[threadIdx.x] = m;
   ss[threadIdx.x] = S;
@@ -504,7 +537,8 @@ __global__ void init_finish_kernel(const Seg* __restrict__ segs, const int* __re
 // r = q - b (x0 given) or r = -b, x = 0; frozen columns x = r = 0
 __global__ void init_residual_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks,
                                      const State* __restrict__ st, int x0_given) {
-  const Chunk ck = chunks[blockIdx.x];
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   const Seg& sg = segs[ck.p];
   const State& S = st[ck.p];
   const int r = sg.r;
@@ -528,7 +562,8 @@ __global__ void init_residual_kernel(const Seg* __restrict__ segs, const Chunk* 
 
 __global__ void update_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks,
                               const State* __restrict__ st, const int* __restrict__ live) {
-  const Chunk ck = chunks[blockIdx.x];
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   if (live[ck.p] == 0) return;
   const Seg& sg = segs[ck.p];
   const State& S = st[ck.p];
@@ -548,9 +583,10 @@ __global__ void update_kernel(const Seg* __restrict__ segs, const Chunk* __restr
 
 // d = -z + beta d (init: d = -z), basis append, column maxima of |d|.
 __global__ void direction_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks,
-                                 const State* __restrict__ st, const int* __restrict__ live,
+                                 State* __restrict__ st, const int* __restrict__ live,
                                  int init, int reorth, uint32_t* __restrict__ colmax) {
-  const Chunk ck = chunks[blockIdx.x];
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   if (live[ck.p] == 0) return;
   const Seg& sg = segs[ck.p];
   const State& S = st[ck.p];
@@ -594,15 +630,9 @@ __global__ void direction_kernel(const Seg* __restrict__ segs, const Chunk* __re
   __syncthreads();
   for (int cc = threadIdx.x; cc < r; cc += blockDim.x)
     if (smax[cc]) atomicMax(&colmax[ck.p * kMaxR + cc], smax[cc]);
-}
-
-__global__ void bump_basis_kernel(const int* __restrict__ plist, int nsel, State* __restrict__ st,
-                                  const int* __restrict__ live) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nsel) return;
-  const int p = plist[t];
-  if (live[p] == 0) return;
-  st[p].nbasis = st[p].append_slot + 1;
+  // the appended pair counts from the next re-orthogonalisation on (no group of
+  // this kernel reads nbasis)
+  if (reorth && ck.k == 0 && threadIdx.x == 0) st[ck.p].nbasis = slot + 1;
 }
 
 // ---- a5: re-orthogonalisation ----------------------------------------------------
@@ -641,15 +671,27 @@ __global__ void reorth_coef_kernel(const Seg* __restrict__ segs, const Chunk* __
 #pragma unroll
   for (int q = 0; q < kJGroup; ++q) acc[q] = accg[q] = 0.0f;
   if (c < r)
-    for (int64_t i = ck.i0 + ty; i < ck.i1; i += tys) {
-      const float rv = Rv[i * r + c], uv = Un[i * r + c];
+    for (int64_t i = ck.i0 + ty; i < ck.i1; i += 4 * tys) {
+      // four rows' loads in flight
+      float rv[4], uv[4], w[4][kJGroup];
 #pragma unroll
-      for (int q = 0; q < kJGroup; ++q)
-        if (q < jn) {
-          const float w = Wb[q * nr + i * r + c];
-          acc[q] = fmaf(w, rv, acc[q]);
-          accg[q] = fmaf(w, uv, accg[q]);
-        }
+      for (int u = 0; u < 4; ++u) {
+        const int64_t e = (i + u * tys < ck.i1 ? i + u * tys : i) * r + c;
+        rv[u] = Rv[e];
+        uv[u] = Un[e];
+#pragma unroll
+        for (int q = 0; q < kJGroup; ++q) w[u][q] = q < jn ? Wb[q * nr + e] : 0.0f;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (i + u * tys >= ck.i1) break;
+#pragma unroll
+        for (int q = 0; q < kJGroup; ++q)
+          if (q < jn) {
+            acc[q] = fmaf(w[u][q], rv[u], acc[q]);
+            accg[q] = fmaf(w[u][q], uv[u], accg[q]);
+          }
+      }
     }
 #pragma unroll
   for (int q = 0; q < kJGroup; ++q) {
@@ -751,7 +793,8 @@ __global__ void reorth_gram_kernel(const Seg* __restrict__ segs, const int* __re
 template <bool USE_LDS>
 __global__ void reorth_apply_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks,
                                     const State* __restrict__ st, const int* __restrict__ live) {
-  const Chunk ck = chunks[blockIdx.x];
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   if (live[ck.p] == 0) return;
   const Seg& sg = segs[ck.p];
   const State& S = st[ck.p];
@@ -786,15 +829,15 @@ __global__ void reorth_apply_kernel(const Seg* __restrict__ segs, const Chunk* _
 
 // ---- a6: preconditioner apply (Woodbury form) ---------------------------------------
 // chunk partial of L^T r (rank x r) on the matrix cores
+template <int CT>
 __global__ __launch_bounds__(256) void lt_partial_kernel(const Seg* __restrict__ segs,
                                                          const Chunk* __restrict__ chunks,
                                                          const int* __restrict__ live) {
   const Chunk ck = chunks[blockIdx.x];
   const Seg& sg = segs[ck.p];
   if (live[ck.p] == 0 || sg.rank == 0) return;
-  __shared__ pc::LtLds sm;
-  pc::lt_chunk_mfma(sg.L32, sg.n, sg.rank, sg.v[VR], sg.r, ck.i0, ck.i1,
-                    sg.ltpart + (int64_t)ck.k * sg.rank * sg.r, sm);
+  pc::lt_chunk_mfma<CT>(sg.L32, sg.n, sg.rank, sg.v[VR], sg.r, ck.i0, ck.i1,
+                    sg.ltpart + (int64_t)ck.k * sg.rank * sg.r);
 }
 
 // T = sum of the chunk partials (float64, chunk order); grid (slot, 64 entries),
@@ -835,10 +878,11 @@ __global__ void lt_solve_kernel(const Seg* __restrict__ segs, const int* __restr
 }
 
 // z = s^-2 r - s^-4 L y (rank > 0), z = r (rank 0: no preconditioner);
-// block per chunk, one thread per row.
-__global__ void z_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks,
+// block per chunk, two threads per row (z_row).
+__global__ __launch_bounds__(256) void z_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks,
                          const int* __restrict__ live) {
-  const Chunk ck = chunks[blockIdx.x];
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   if (live[ck.p] == 0) return;
   const Seg& sg = segs[ck.p];
   const int r = sg.r, k = sg.rank;
@@ -854,8 +898,8 @@ __global__ void z_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__
   __syncthreads();
   const float inv_s2 = 1.0f / sg.s2;
   const float inv_s4 = inv_s2 * inv_s2;
-  for (int64_t i = ck.i0 + threadIdx.x; i < ck.i1; i += blockDim.x)
-    pc::z_row(sg.L32, sg.n, k, sy, rp, R, Z, r, i, inv_s2, inv_s4);
+  for (int64_t i = ck.i0 + threadIdx.x / 2; i < ck.i1; i += 128)
+    pc::z_row(sg.L32, sg.n, k, sy, rp, R, Z, r, i, 8 * (threadIdx.x & 1), inv_s2, inv_s4);
 }
 
 // ---- a8: true residual (float64 accumulation on the matrix cores) -------------------
@@ -954,178 +998,188 @@ __global__ void trueres_finish_kernel(const Seg* __restrict__ segs, const int* _
 }
 
 // ---- a9: pivoted Cholesky, all problems of a set per step ----------------------------
-__device__ inline bool better(double v, int64_t i, double bv, int64_t bi) {
-  if (isnan(v)) return false;
-  if (isnan(bv)) return true;
-  return v > bv || (v == bv && i < bi);
-}
-
-// Chunk argmax (lowest index on ties) and sum of the residual diagonal.
-__device__ void chunk_argmax(const Seg& sg, const Chunk& ck) {
-  __shared__ double sv[256];
-  __shared__ int64_t si[256];
-  __shared__ double ssum[256];
-  double bv = -INFINITY, sum = 0.0;
-  int64_t bi = INT64_MAX;
-  for (int64_t i = ck.i0 + threadIdx.x; i < ck.i1; i += blockDim.x) {
-    const double v = sg.diag[i];
-    sum += v;
-    if (better(v, i, bv, bi)) {
-      bv = v;
-      bi = i;
-    }
-  }
-  sv[threadIdx.x] = bv;
-  si[threadIdx.x] = bi;
-  ssum[threadIdx.x] = sum;
-  for (int s = 128; s > 0; s >>= 1) {
-    __syncthreads();
-    if ((int)threadIdx.x < s) {
-      if (better(sv[threadIdx.x + s], si[threadIdx.x + s], sv[threadIdx.x], si[threadIdx.x])) {
-        sv[threadIdx.x] = sv[threadIdx.x + s];
-        si[threadIdx.x] = si[threadIdx.x + s];
-      }
-      ssum[threadIdx.x] += ssum[threadIdx.x + s];
-    }
-  }
-  __syncthreads();
+// A chunk's argmax partial of step parity h.
+__device__ __forceinline__ void put_best(const Seg& sg, const Chunk& ck, int h, pc::Best x) {
+  x = pc::group_best(x);
   if (threadIdx.x == 0) {
-    sg.pv[ck.k] = sv[0];
-    sg.pi[ck.k] = si[0];
-    sg.psum[ck.k] = ssum[0];
+    const int64_t o = (int64_t)h * sub_chunks_of(sg.n) + ck.k;
+    sg.pv[o] = x.v;
+    sg.pi[o] = x.i;
+    sg.psum[o] = x.sum;
   }
 }
 
-__global__ void pc_init_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks) {
-  const Chunk ck = chunks[blockIdx.x];
+// The build's state, the residual diagonal a^2 and its partials.
+__global__ __launch_bounds__(256) void pc_init_kernel(const Seg* __restrict__ segs,
+                                                      const Chunk* __restrict__ chunks,
+                                                      PcState* __restrict__ ps) {
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   const Seg& sg = segs[ck.p];
-  if (sg.rank == 0) return;
-  for (int64_t i = ck.i0 + threadIdx.x; i < ck.i1; i += blockDim.x) sg.diag[i] = sg.a2;
-  __syncthreads();
-  chunk_argmax(sg, ck);
-}
-
-// Pivot of step m for every problem still running; a problem still running at
-// step m has built columns 0..m-1.
-__global__ void pc_select_kernel(const Seg* __restrict__ segs, const int* __restrict__ plist,
-                                 int nsel, PcState* __restrict__ ps, int m) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nsel) return;
-  const int p = plist[t];
-  const Seg& sg = segs[p];
-  PcState& S = ps[p];
-  if (m == 0) {
-    S.stop = 0;
+  if (ck.k == 0 && threadIdx.x == 0) {
+    PcState& S = ps[ck.p];
+    S.rank = 0;
+    S.stop = sg.rank == 0;
     S.not_pd = 0;
     S.trace = 0.0;
   }
+  if (sg.rank == 0) return;
+  const double a2 = sg.a2;
+  pc::Best x{-INFINITY, INT64_MAX, 0.0};
+  for (int64_t i = ck.i0 + threadIdx.x; i < ck.i1; i += blockDim.x) {
+    sg.diag[i] = a2;
+    x = pc::best_of(x, pc::Best{a2, i, a2});
+  }
+  put_best(sg, ck, 0, x);
+}
+
+// The stop rule from the merged partials before step m.
+__device__ __forceinline__ bool pc_stops(const Seg& sg, const pc::Best& x, int m) {
+  return m >= sg.rank || !(x.v > 1e-12 * (double)sg.a2) || x.i == INT64_MAX;
+}
+
+// Trace and rank of the problems still running after the last step (m: steps
+// done); block per problem.
+__global__ __launch_bounds__(256) void pc_finish_kernel(const Seg* __restrict__ segs,
+                                                        const int* __restrict__ plist,
+                                                        PcState* __restrict__ ps, int m) {
+  const int p = plist[blockIdx.x];
+  const Seg& sg = segs[p];
+  PcState& S = ps[p];
   if (S.stop) return;
-  S.rank = m;
-  if (sg.rank == 0) {
+  const int parts = sub_chunks_of(sg.n);
+  const int64_t h = (int64_t)(m & 1) * parts;
+  const pc::Best x = pc::merge_partials(sg.pv + h, sg.pi + h, sg.psum + h, parts);
+  if (threadIdx.x == 0) {
+    S.trace = x.sum;
     S.stop = 1;
-    return;
-  }
-  double v = -INFINITY, tot = 0.0;
-  int64_t idx = INT64_MAX;
-  for (int k = 0; k < sg.nchunk; ++k) {
-    tot += sg.psum[k];
-    if (better(sg.pv[k], sg.pi[k], v, idx)) {
-      v = sg.pv[k];
-      idx = sg.pi[k];
-    }
-  }
-  S.trace = tot;
-  if (m >= sg.rank || !(v > 1e-12 * (double)sg.a2) || idx == INT64_MAX) {
-    S.stop = 1;
-  } else {
-    S.dmax = v;
-    S.pivot = idx;
-    sg.piv[m] = idx;
   }
 }
 
-__global__ void pc_step_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks,
-                               const PcState* __restrict__ ps, int m) {
-  const Chunk ck = chunks[blockIdx.x];
+// Step m for every problem still running.  Every group of a problem merges the
+// partials of step m - 1 (one fixed order: all find the same pivot and stop
+// decision), chunk 0's records them, and the step's own partials go to the other
+// half of the buffers; a launch per step saved, 9 us of one thread's chain over
+// the chunks and its gap.  One thread reads the stop flag, which chunk 0 may set
+// in this same launch, for its whole group: a group that sees it returns, one
+// that does not comes to the same decision by itself.
+__global__ __launch_bounds__(256) void pc_step_kernel(const Seg* __restrict__ segs,
+                                                      const Chunk* __restrict__ chunks,
+                                                      PcState* __restrict__ ps, int m) {
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   const Seg& sg = segs[ck.p];
-  const PcState& S = ps[ck.p];
-  if (S.stop) return;
+  PcState& S = ps[ck.p];
+  __shared__ int stop_seen;
   __shared__ double lp[pc::kMaxRank];
-  __shared__ double xp[kMaxDim];
+  __shared__ double xp[kMaxDim], inv_l[kMaxDim];
+  if (threadIdx.x == 0) stop_seen = __atomic_load_n(&S.stop, __ATOMIC_RELAXED);
+  __syncthreads();
+  if (stop_seen) return;
+  const int parts = sub_chunks_of(sg.n);
+  const int64_t h = (int64_t)(m & 1) * parts;
+  const pc::Best x = pc::merge_partials(sg.pv + h, sg.pi + h, sg.psum + h, parts);
+  const bool stop = pc_stops(sg, x, m);
+  if (ck.k == 0 && threadIdx.x == 0) {
+    S.trace = x.sum;
+    if (stop) {
+      __atomic_store_n(&S.stop, 1, __ATOMIC_RELAXED);
+    } else {
+      S.dmax = x.v;
+      S.pivot = x.i;
+      S.rank = m + 1;
+      sg.piv[m] = x.i;
+    }
+  }
+  if (stop) return;
   const int64_t n = sg.n;
-  const int64_t p = S.pivot;
-  const double inv_sq = 1.0 / sqrt(S.dmax);
+  const int64_t p = x.i;
+  const double inv_sq = 1.0 / sqrt(x.v);
   const int d = sg.d;
   double* L = sg.L64;
   for (int t = threadIdx.x; t < m; t += blockDim.x) lp[t] = L[(int64_t)t * n + p];
-  for (int t = threadIdx.x; t < d; t += blockDim.x) xp[t] = (double)sg.X[p * d + t] / (double)sg.ls[t];
+  for (int t = threadIdx.x; t < d; t += blockDim.x) {
+    const double il = 1.0 / (double)sg.ls[t];
+    inv_l[t] = il;
+    xp[t] = (double)sg.X[p * d + t] * il;
+  }
   __syncthreads();
+  pc::Best best{-INFINITY, INT64_MAX, 0.0};
   for (int64_t i = ck.i0 + threadIdx.x; i < ck.i1; i += blockDim.x) {
     double r2 = 0.0;
     for (int t = 0; t < d; ++t) {
-      const double df = (double)sg.X[i * d + t] / (double)sg.ls[t] - xp[t];
+      const double df = fma((double)sg.X[i * d + t], inv_l[t], -xp[t]);
       r2 = fma(df, df, r2);
     }
     double acc = (double)sg.a2 * kval64(sg.kind, r2);
     acc = pc::sub_lrow(L, n, i, lp, m, acc);
     const double l = acc * inv_sq;
     L[(int64_t)m * n + i] = l;
-    sg.diag[i] = fma(-l, l, sg.diag[i]);
+    const double dg = fma(-l, l, sg.diag[i]);
+    sg.diag[i] = dg;
+    best = pc::best_of(best, pc::Best{dg, i, dg});
   }
-  __syncthreads();
-  chunk_argmax(sg, ck);
+  put_best(sg, ck, (m + 1) & 1, best);
 }
 
-// C = I + s^-2 L^T L for every problem: block per (problem, 16 x 16 tile).
-__global__ void pc_syrk_kernel(const Seg* __restrict__ segs, const PcState* __restrict__ ps,
-                               const int4* __restrict__ tiles) {
-  // tile (p, ta, tb) with ta <= tb; the (tb, ta) tile is its mirror image
-  // (the products commute, so the mirrored sums are the same numbers)
-  constexpr int kStep = 128;
+// C = I + s^-2 L^T L for every problem: block per (problem, 16 x 16 tile (ta <=
+// tb)); the (tb, ta) tile is its mirror image (the products commute, so the
+// mirrored sums are the same numbers).  On the float64 matrix cores: lane (row or
+// column l % 16, group l / 16) of wave w takes rows 8 (16 s + w) + 2 (l / 16) and
+// the next of every step s, two loads of 16 bytes and two MFMAs, eight steps in
+// flight, with no LDS and no barrier before the waves' sums are added.  Through
+// LDS with 256 threads a tile's chain over its problem's rows was the whole
+// launch: 537 us at 20,000 rows, 147 now (one work group reads a whole factor).
+constexpr int kSyrkThreads = 1024;
+__global__ __launch_bounds__(kSyrkThreads) void pc_syrk_kernel(const Seg* __restrict__ segs,
+                                                               const PcState* __restrict__ ps,
+                                                               const int4* __restrict__ tiles) {
+  typedef double d4 __attribute__((ext_vector_type(4)));
+  constexpr int kW = kSyrkThreads / 64;
   const int4 t = tiles[blockIdx.x];
   const Seg& sg = segs[t.x];
   const int k = ps[t.x].rank;
   if (t.y * 16 >= k || t.z * 16 >= k) return;
-  __shared__ double la[16][kStep + 1];
-  __shared__ double lb[16][kStep + 1];
-  const int a = threadIdx.x / 16, b = threadIdx.x % 16;
-  const double* L = sg.L64;
+  __shared__ double red[kW][256];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
   const int64_t n = sg.n;
-  // four interleaved partial sums (columns cc = q mod 4), added in a fixed
-  // order at the end
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t c0 = 0; c0 < n; c0 += kStep) {
-    __syncthreads();
-    // the step's 16 staging loads per thread in flight at once
-    double va[8], vb[8];
+  const int ra = t.y * 16 + l16, rb = t.z * 16 + l16;
+  const bool diag = t.y == t.z;
+  const double* La = sg.L64 + (int64_t)min(ra, k - 1) * n;   // rows past k: unused entries of C
+  const double* Lb = sg.L64 + (int64_t)min(rb, k - 1) * n;
+  d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+  constexpr int kSteps = 4;
+  for (int64_t i0 = 8 * wave + 2 * g; i0 - 2 * g < n; i0 += 8 * kW * kSteps) {
+    double a[kSteps][2], b[kSteps][2];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = u * 256 + (int)threadIdx.x;
-      const int rr = e / kStep, cc = e % kStep;
-      const int64_t i = c0 + cc;
-      const int ra = t.y * 16 + rr, rb = t.z * 16 + rr;
-      va[u] = (i < n && ra < k) ? L[(int64_t)ra * n + i] : 0.0;
-      vb[u] = (i < n && rb < k) ? L[(int64_t)rb * n + i] : 0.0;
-    }
+    for (int u = 0; u < kSteps; ++u)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = u * 256 + (int)threadIdx.x;
-      la[e / kStep][e % kStep] = va[u];
-      lb[e / kStep][e % kStep] = vb[u];
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int cc = 0; cc < kStep; cc += 4) {
+      for (int v = 0; v < 2; ++v) {
+        const int64_t i = i0 + 8 * kW * u + v;
+        const int64_t ic = i < n ? i : n - 1;
+        const double x = La[ic], y = diag ? x : Lb[ic];
+        a[u][v] = i < n ? x : 0.0;
+        b[u][v] = i < n ? y : 0.0;
+      }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q] = fma(la[a][cc + q], lb[b][cc + q], acc[q]);
-    }
+    for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][v], b[u][v], acc, 0, 0, 0);
   }
-  const double sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  const int ga = t.y * 16 + a, gb = t.z * 16 + b;
-  if (ga < k && gb < k) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wave][(g + 4 * v) * 16 + l16] = acc[v];
+  __syncthreads();
+  if (threadIdx.x >= 256) return;
+  double sum = 0.0;
+#pragma unroll
+  for (int w = 0; w < kW; ++w) sum += red[w][threadIdx.x];
+  const int ga = t.y * 16 + threadIdx.x / 16, gb = t.z * 16 + threadIdx.x % 16;
+  // a diagonal tile's lower triangle is written from its upper one
+  if (ga < k && gb < k && ga <= gb) {
     const double v = (ga == gb ? 1.0 : 0.0) + sum / (double)sg.s2;
     sg.C[ga * k + gb] = v;
-    if (t.y != t.z) sg.C[gb * k + ga] = v;
+    sg.C[gb * k + ga] = v;
   }
 }
 
@@ -1144,7 +1198,8 @@ __global__ __launch_bounds__(256) void pc_cholinv_kernel(const Seg* __restrict__
 // binary32 copy of the built factor columns, the chunk's rows
 __global__ void to_f32_kernel(const Seg* __restrict__ segs, const Chunk* __restrict__ chunks,
                               const PcState* __restrict__ ps) {
-  const Chunk ck = chunks[blockIdx.x];
+  const Chunk ck = sub_chunk(chunks, blockIdx.x);
+  if (ck.i0 >= ck.i1) return;
   const Seg& sg = segs[ck.p];
   const int k = ps[ck.p].rank;
   const int64_t rows = ck.i1 - ck.i0;
@@ -1167,7 +1222,7 @@ static inline unsigned blocks_for(int64_t n, int t = 256) { return (unsigned)cei
 
 static gp_status launch_quant(const Dev& D, const Tab& T, int vsel, int scale_mode, const int* live,
                               hipStream_t s) {
-  quant_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, vsel, D.colmax, scale_mode, D.scale,
+  quant_kernel<<<T.nchunks * kSub, 256, 0, s>>>(D.segs, T.chunks, vsel, D.colmax, scale_mode, D.scale,
                                          D.inv_scale, live);
   BT_LAUNCH_CHECK();
   return GP_OK;
@@ -1218,7 +1273,7 @@ static gp_status launch_product(const Dev& D, const Tab& T, int vsel, int osel, 
   else
     GP_TRY(launch_fused<4>(D, T, live, s));
   prof::end(tok, s, T.entries, -1);
-  reduce_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.inv_scale, vsel, osel, live);
+  reduce_kernel<<<T.nchunks * kSub, 256, 0, s>>>(D.segs, T.chunks, D.inv_scale, vsel, osel, live);
   BT_LAUNCH_CHECK();
   return GP_OK;
 }
@@ -1235,7 +1290,10 @@ static gp_status launch_colred(const Dev& D, const Tab& T, int asel, int bsel, b
 
 static gp_status launch_precond(const Dev& D, const Tab& T, hipStream_t s) {
   if (T.max_rank > 0) {
-    lt_partial_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.live);
+    auto lt = T.max_r <= 16   ? &lt_partial_kernel<1>
+              : T.max_r <= 32 ? &lt_partial_kernel<2>
+                              : &lt_partial_kernel<4>;
+    lt<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.live);
     BT_LAUNCH_CHECK();
     const int kr = T.max_rank * T.max_r;
     lt_sum_kernel<<<dim3(T.nsel, (unsigned)ceil_div(kr, 64)), 256, 0, s>>>(D.segs, T.plist, D.live);
@@ -1244,7 +1302,7 @@ static gp_status launch_precond(const Dev& D, const Tab& T, hipStream_t s) {
                                                                                D.live);
     BT_LAUNCH_CHECK();
   }
-  z_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.live);
+  z_kernel<<<T.nchunks * kSub, 256, 0, s>>>(D.segs, T.chunks, D.live);
   BT_LAUNCH_CHECK();
   return GP_OK;
 }
@@ -1259,13 +1317,9 @@ static gp_status launch_rz(const Dev& D, const Tab& T, bool lse, bool init, hipS
 
 static gp_status launch_direction(const Dev& D, const Tab& T, bool init, bool reorth,
                                   hipStream_t s) {
-  direction_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.st, D.live, init ? 1 : 0,
+  direction_kernel<<<T.nchunks * kSub, 256, 0, s>>>(D.segs, T.chunks, D.st, D.live, init ? 1 : 0,
                                              reorth ? 1 : 0, D.colmax);
   BT_LAUNCH_CHECK();
-  if (reorth) {
-    bump_basis_kernel<<<blocks_for(T.nsel), 256, 0, s>>>(T.plist, T.nsel, D.st, D.live);
-    BT_LAUNCH_CHECK();
-  }
   return GP_OK;
 }
 
@@ -1282,9 +1336,9 @@ static gp_status launch_reorth(const Dev& D, const Tab& T, hipStream_t s) {
                        256, 0, s>>>(D.segs, T.plist, D.st, D.live);
   BT_LAUNCH_CHECK();
   if (lds <= 48 * 1024)
-    reorth_apply_kernel<true><<<T.nchunks, 256, lds, s>>>(D.segs, T.chunks, D.st, D.live);
+    reorth_apply_kernel<true><<<T.nchunks * kSub, 256, lds, s>>>(D.segs, T.chunks, D.st, D.live);
   else
-    reorth_apply_kernel<false><<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.st, D.live);
+    reorth_apply_kernel<false><<<T.nchunks * kSub, 256, 0, s>>>(D.segs, T.chunks, D.st, D.live);
   BT_LAUNCH_CHECK();
   return GP_OK;
 }
@@ -1295,26 +1349,25 @@ gp_status seq_prepare(const Dev& D, const Tab& T, hipStream_t s) {
   (void)persistent_grid<1>();
   (void)persistent_grid<2>();
   (void)persistent_grid<4>();
-  prep_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks);
+  prep_kernel<<<T.nchunks * kSub, 256, 0, s>>>(D.segs, T.chunks);
   BT_LAUNCH_CHECK();
-  // pivoted Cholesky: one select + one column step per pivot for the whole set
-  pc_init_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks);
+  // pivoted Cholesky: one column step per pivot for the whole set
+  pc_init_kernel<<<T.nchunks * kSub, kSubRows, 0, s>>>(D.segs, T.chunks, D.pcs);
   BT_LAUNCH_CHECK();
-  for (int m = 0; m <= T.max_rank; ++m) {
-    pc_select_kernel<<<blocks_for(T.nsel, 64), 64, 0, s>>>(D.segs, T.plist, T.nsel, D.pcs, m);
-    BT_LAUNCH_CHECK();
-    if (m == T.max_rank) break;
-    pc_step_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.pcs, m);
+  for (int m = 0; m < T.max_rank; ++m) {
+    pc_step_kernel<<<T.nchunks * kSub, kSubRows, 0, s>>>(D.segs, T.chunks, D.pcs, m);
     BT_LAUNCH_CHECK();
   }
   if (T.max_rank > 0) {
+    pc_finish_kernel<<<T.nsel, 256, 0, s>>>(D.segs, T.plist, D.pcs, T.max_rank);
+    BT_LAUNCH_CHECK();
     if (T.ntiles > 0) {
-      pc_syrk_kernel<<<T.ntiles, 256, 0, s>>>(D.segs, D.pcs, T.tiles);
+      pc_syrk_kernel<<<T.ntiles, kSyrkThreads, 0, s>>>(D.segs, D.pcs, T.tiles);
       BT_LAUNCH_CHECK();
     }
     pc_cholinv_kernel<<<T.nsel, 256, 0, s>>>(D.segs, T.plist, D.pcs);
     BT_LAUNCH_CHECK();
-    to_f32_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.pcs);
+    to_f32_kernel<<<T.nchunks * kSub, 256, 0, s>>>(D.segs, T.chunks, D.pcs);
     BT_LAUNCH_CHECK();
   }
   return GP_OK;
@@ -1336,7 +1389,7 @@ gp_status seq_start(const Dev& D, const Tab& T, const RunOpts& o, bool x0_given,
     GP_TRY(launch_quant(D, T, VX, o.scale_mode, nullptr, s));
     GP_TRY(launch_product(D, T, VX, VQ, nullptr, s));
   }
-  init_residual_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.st, x0_given ? 1 : 0);
+  init_residual_kernel<<<T.nchunks * kSub, 256, 0, s>>>(D.segs, T.chunks, D.st, x0_given ? 1 : 0);
   BT_LAUNCH_CHECK();
   GP_TRY(launch_precond(D, T, s));
   GP_TRY(launch_rz(D, T, o.lse, true, s));
@@ -1350,7 +1403,7 @@ gp_status seq_iteration(const Dev& D, const Tab& T, const RunOpts& o, hipStream_
   GP_TRY(launch_colred(D, T, VD, VQ, o.lse, false, s));
   dq_finish_kernel<<<T.nsel, 64, 0, s>>>(D.segs, T.plist, D.st, D.live, o.lse ? 1 : 0);
   BT_LAUNCH_CHECK();
-  update_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks, D.st, D.live);
+  update_kernel<<<T.nchunks * kSub, 256, 0, s>>>(D.segs, T.chunks, D.st, D.live);
   BT_LAUNCH_CHECK();
   if (o.reorth) GP_TRY(launch_reorth(D, T, s));
   GP_TRY(launch_precond(D, T, s));

@@ -40,52 +40,6 @@ struct BuildState {
   unsigned pad;
 };
 
-// (value, index) argmax with the lowest index winning ties; NaN never wins.
-__device__ inline bool better(double v, int64_t i, double bv, int64_t bi) {
-  if (isnan(v)) return false;
-  if (isnan(bv)) return true;
-  return v > bv || (v == bv && i < bi);
-}
-
-struct Best {
-  double v;
-  int64_t i;
-  double sum;
-};
-
-__device__ __forceinline__ Best best_of(const Best& a, const Best& b) {
-  const bool take = better(b.v, b.i, a.v, a.i);
-  return Best{take ? b.v : a.v, take ? b.i : a.i, a.sum + b.sum};
-}
-
-// Argmax (lowest index on ties) and sum over a wave, then over the work
-// group's waves, in a fixed order; every thread returns the result.
-__device__ __forceinline__ Best group_best(Best x) {
-  constexpr int kMaxWaves = 16;
-  __shared__ Best sw[kMaxWaves];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-    x = best_of(x, Best{__shfl_xor(x.v, o, 64), __shfl_xor(x.i, o, 64), __shfl_xor(x.sum, o, 64)});
-  const int waves = blockDim.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sw[threadIdx.x >> 6] = x;
-  __syncthreads();
-  Best r = sw[0];
-  for (int w = 1; w < waves; ++w) r = best_of(r, sw[w]);
-  return r;
-}
-
-// Fixed-order merge of nparts argmax partials by one work group: the largest
-// residual diagonal (lowest index on ties), its index and the residual trace,
-// returned to every thread.
-__device__ __forceinline__ Best merge_partials(const double* __restrict__ pv,
-                                               const int64_t* __restrict__ pi,
-                                               const double* __restrict__ psum, int nparts) {
-  Best x{-INFINITY, INT64_MAX, 0.0};
-  for (int g = threadIdx.x; g < nparts; g += blockDim.x) x = best_of(x, Best{pv[g], pi[g], psum[g]});
-  return group_best(x);
-}
-
 // One work group: the merge, the pivot of step next_m and the stop rule.  Used
 // once before the first step and once after the last (trace and stop); the
 // steps in between merge their predecessor's partials themselves.
@@ -334,15 +288,15 @@ int lt_chunks(int64_t n) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(kLtResidentChunks, ceil_div(n, kLtChunkRows)));
 }
 
+template <int CT>
 __global__ __launch_bounds__(256) void lt_partial_kernel(const float* __restrict__ L32,
                                                          const float* __restrict__ w, int64_t n,
                                                          int k, int r, int nchunk,
                                                          float* __restrict__ part,
                                                          const int* __restrict__ live) {
   if (live && *live == 0) return;
-  __shared__ LtLds sm;
   const int64_t i0 = blockIdx.x * n / nchunk, i1 = (blockIdx.x + 1) * n / nchunk;
-  lt_chunk_mfma(L32, n, k, w, r, i0, i1, part + (int64_t)blockIdx.x * k * r, sm);
+  lt_chunk_mfma<CT>(L32, n, k, w, r, i0, i1, part + (int64_t)blockIdx.x * k * r);
 }
 
 // Sixteen threads per entry, each adding a sixteenth of the chunk partials in
@@ -381,9 +335,7 @@ __global__ void lt_solve_kernel(const double* __restrict__ T64, const double* __
   Y32[o] = (float)acc;
 }
 
-// Two threads per row, each taking eight of every sixteen right-hand sides:
-// twice the waves of one thread per row, so twice the L loads in flight (the
-// pair's loads of L[m][i] are one address).
+// Two threads per row (z_row).
 __global__ void z_kernel(const float* __restrict__ L32, const float* __restrict__ Y32,
                          const float* __restrict__ w, float* __restrict__ z, int64_t n, int k,
                          int r, float inv_s2, float inv_s4, const int* __restrict__ live) {
@@ -393,38 +345,7 @@ __global__ void z_kernel(const float* __restrict__ L32, const float* __restrict_
   stage_y(Y32, k, r, rp, sy);
   __syncthreads();
   const int64_t i = (int64_t)blockIdx.x * (blockDim.x / 2) + threadIdx.x / 2;
-  const int h = threadIdx.x & 1;
-  if (i >= n) return;
-  for (int c0 = 8 * h; c0 < rp; c0 += 16) {
-    float acc[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] = 0.0f;
-    auto step = [&](float l, int m) {
-      const pf4* y4 = reinterpret_cast<const pf4*>(sy + m * rp + c0);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const pf4 y = y4[q];
-        acc[4 * q + 0] = fmaf(l, y[0], acc[4 * q + 0]);
-        acc[4 * q + 1] = fmaf(l, y[1], acc[4 * q + 1]);
-        acc[4 * q + 2] = fmaf(l, y[2], acc[4 * q + 2]);
-        acc[4 * q + 3] = fmaf(l, y[3], acc[4 * q + 3]);
-      }
-    };
-    int m = 0;
-    for (; m + 16 <= k; m += 16) {
-      float l[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) l[u] = L32[(int64_t)(m + u) * n + i];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) step(l[u], m + u);
-    }
-    for (; m < k; ++m) step(L32[(int64_t)m * n + i], m);
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int cc = c0 + c;
-      if (cc < r) z[i * r + cc] = inv_s2 * w[i * r + cc] - inv_s4 * acc[c];
-    }
-  }
+  if (i < n) z_row(L32, n, k, sy, rp, w, z, r, i, 8 * (threadIdx.x & 1), inv_s2, inv_s4);
 }
 
 __global__ void scale_kernel(const float* __restrict__ w, float* __restrict__ z, int64_t total,
@@ -447,8 +368,8 @@ gp_status apply(const gp_precond* P, const float* rr, float* z, const cg::Dims& 
   const int kr = P->rank * dm.r;
   float* part = reinterpret_cast<float*>(P->scratch);
   double* T64 = P->scratch + (size_t)kLtMaxChunks * kMaxRank * 64 / 2;
-  lt_partial_kernel<<<(unsigned)nchunk, 256, 0, s>>>(P->L32, rr, dm.n, P->rank, dm.r, nchunk, part,
-                                                     live);
+  auto lt = dm.r <= 16 ? &lt_partial_kernel<1> : dm.r <= 32 ? &lt_partial_kernel<2> : &lt_partial_kernel<4>;
+  lt<<<(unsigned)nchunk, 256, 0, s>>>(P->L32, rr, dm.n, P->rank, dm.r, nchunk, part, live);
   GP_HIP(hipGetLastError());
   lt_sum_kernel<<<(unsigned)ceil_div(kr, 256 / kLtSumLanes), 256, 0, s>>>(part, P->rank, dm.r,
                                                                          nchunk, T64, live);

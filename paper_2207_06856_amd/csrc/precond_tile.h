@@ -18,85 +18,71 @@ constexpr int kLtChunkRows = 128;   // rows per chunk of the single-problem L^T 
 constexpr int kLtResidentChunks = 512;  // 2 work groups x 256 compute units
 
 // Work group (256 threads): out[m * r + c] = sum_{i0 <= i < i1} L[m][i] w[i][c]
-// for m < k, c < r.  Rows go in tiles of 32: the group stages the tile of L
-// (k x 32) and of w (32 x r) in LDS with coalesced loads, then wave w runs the
-// 16-pivot tiles w, w + 4, ... as 8 steps of a 16x16x4 product per column
-// tile.  A operand (lane l): L[tile + l % 16][row], B operand:
-// w[row][ctile + l % 16], row = 4 * step + l / 16; D: lane l, element v holds
-// pivot tile + 4 * (l / 16) + v, column ctile + l % 16.
-constexpr int kLtTile = 32;
-struct LtLds {
-  float L[kMaxRank][kLtTile + 1];
-  float W[kLtTile][64 + 1];
-};
-
+// for m < k, c < r, in 16x16x4 products, wave w owning pivot tiles w and w + 4.
+// Operands come straight from memory.  A operand (lane l): L[tile + l % 16][row],
+// B operand: w[row][ctile + l % 16], row = t0 + 4 * u + l / 16 for product u; D:
+// lane l, element v holds pivot tile + 4 * (l / 16) + v, column ctile + l % 16.
+// The loads of the next 4 U rows are issued before the products of the current
+// ones.  Bound by the loads' latency: staged through LDS in 32-row tiles, two
+// barriers each, 48 problems of rank 20 and 250,000 rows (20 MB of L) took 34 us,
+// 17 now; 100,000 rows at rank 100, R = 16 (40 MB) 25 us both ways.  Eight rows in a
+// row per lane would take 12 and 17, but sum in another order, and a float32 ulp
+// of z flips binary16 roundings of the next direction.
+// CT: column tiles (1, 2 or 4; r <= 16 CT).
+template <int CT>
 __device__ __forceinline__ void lt_chunk_mfma(const float* __restrict__ L, int64_t n, int k,
                                               const float* __restrict__ w, int r, int64_t i0,
-                                              int64_t i1, float* __restrict__ out, LtLds& sm) {
+                                              int64_t i1, float* __restrict__ out) {
+  constexpr int U = CT == 1 ? 16 : 8;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, g = lane >> 4;
-  const int kt = (k + 15) / 16, ct = (r + 15) / 16;
-  pf4 acc[2][4];
+  const int kt = (k + 15) / 16;
+  if (wave >= kt) return;
+  pf4 acc[2][CT];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[a][t] = pf4{0.f, 0.f, 0.f, 0.f};
-  // The next tile's staging loads are issued into registers before the
-  // current tile's products, so their latency overlaps the matrix work (every
-  // load of a tile in flight at once: k * 64 / 256 <= 32 of L and at most 16
-  // of w per thread).
-  constexpr int kPerL = kMaxRank * kLtTile / 256;
-  constexpr int kPerW = kLtTile * 64 / 256;
-  float bufL[kPerL], bufW[kPerW];
-  auto load_tile = [&](int64_t t0) {
-    const int rows = (int)min<int64_t>(kLtTile, i1 - t0);
-#pragma unroll
-    for (int u = 0; u < kPerL; ++u) {
-      const int e = u * 256 + threadIdx.x;
-      const int m = e / kLtTile, ii = e % kLtTile;
-      bufL[u] = (e < k * kLtTile && ii < rows) ? L[(int64_t)m * n + t0 + ii] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < kPerW; ++u) {
-      const int e = u * 256 + threadIdx.x;
-      const int ii = e / r, c = e % r;
-      bufW[u] = (e < kLtTile * r && ii < rows) ? w[(t0 + ii) * r + c] : 0.0f;
-    }
-  };
-  if (i0 < i1) load_tile(i0);
-  for (int64_t t0 = i0; t0 < i1; t0 += kLtTile) {
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kPerL; ++u) {
-      const int e = u * 256 + threadIdx.x;
-      if (e < k * kLtTile) sm.L[e / kLtTile][e % kLtTile] = bufL[u];
-    }
-#pragma unroll
-    for (int u = 0; u < kPerW; ++u) {
-      const int e = u * 256 + threadIdx.x;
-      if (e < kLtTile * r) sm.W[e / r][e % r] = bufW[u];
-    }
-    for (int e = threadIdx.x; e < kLtTile * (ct * 16 - r); e += 256) {
-      const int span = ct * 16 - r;
-      sm.W[e / span][r + e % span] = 0.0f;   // zero column padding
-    }
-    __syncthreads();
-    if (t0 + kLtTile < i1) load_tile(t0 + kLtTile);
+    for (int t = 0; t < CT; ++t) acc[a][t] = pf4{0.f, 0.f, 0.f, 0.f};
+  float la[2][U], lw[CT][U];
+  auto load = [&](int64_t t0) {
+    const bool full = t0 + 4 * U <= i1;                // the same for the whole wave
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
-      const int mt = wave + 4 * a;
-      if (mt < kt) {
-        const int m = mt * 16 + l16;
-#pragma unroll 4
-        for (int st = 0; st < kLtTile / 4; ++st) {
-          const int row = 4 * st + g;
-          const float av = m < k ? sm.L[m][row] : 0.0f;
+      if (wave + 4 * a >= kt) continue;
+      const int m = 16 * (wave + 4 * a) + l16;
+      const float* p = L + (int64_t)(m < k ? m : k - 1) * n + t0 + g;  // past k: unused sums
 #pragma unroll
-          for (int t = 0; t < 4; ++t)
-            if (t < ct)
-              acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, sm.W[row][t * 16 + l16], acc[a][t], 0, 0, 0);
-        }
-      }
+      for (int u = 0; u < U; ++u) la[a][u] = full || t0 + g + 4 * u < i1 ? p[4 * u] : 0.0f;
+    }
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+      const int c = 16 * t + l16;
+      const float* p = w + (t0 + g) * r + c;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        lw[t][u] = c < r && (full || t0 + g + 4 * u < i1) ? p[4 * u * r] : 0.0f;
+    }
+  };
+  if (i0 < i1) load(i0);
+  for (int64_t t0 = i0; t0 < i1;) {
+    float ca[2][U], cw[CT][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int a = 0; a < 2; ++a) ca[a][u] = la[a][u];
+#pragma unroll
+      for (int t = 0; t < CT; ++t) cw[t][u] = lw[t][u];
+    }
+    t0 += 4 * U;
+    if (t0 < i1) load(t0);
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      if (wave + 4 * a >= kt) continue;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+          acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ca[a][u], cw[t][u], acc[a][t], 0, 0, 0);
     }
   }
 #pragma unroll
@@ -104,14 +90,12 @@ __device__ __forceinline__ void lt_chunk_mfma(const float* __restrict__ L, int64
     const int mt = wave + 4 * a;
     if (mt >= kt) continue;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (t < ct) {
-        const int c = t * 16 + l16;
+    for (int t = 0; t < CT; ++t) {
+      const int c = t * 16 + l16;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int mm = mt * 16 + 4 * g + v;
-          if (mm < k && c < r) out[mm * r + c] = acc[a][t][v];
-        }
+      for (int v = 0; v < 4; ++v) {
+        const int mm = mt * 16 + 4 * g + v;
+        if (mm < k && c < r) out[mm * r + c] = acc[a][t][v];
       }
     }
   }
@@ -132,6 +116,52 @@ __device__ __forceinline__ double sum_strided(const float* __restrict__ base, in
   }
   for (; q < g1; ++q) acc += (double)base[(int64_t)q * stride];
   return acc;
+}
+
+// (value, index) argmax with the lowest index winning ties; NaN never wins.
+__device__ inline bool better(double v, int64_t i, double bv, int64_t bi) {
+  if (isnan(v)) return false;
+  if (isnan(bv)) return true;
+  return v > bv || (v == bv && i < bi);
+}
+
+struct Best {
+  double v;
+  int64_t i;
+  double sum;
+};
+
+__device__ __forceinline__ Best best_of(const Best& a, const Best& b) {
+  const bool take = better(b.v, b.i, a.v, a.i);
+  return Best{take ? b.v : a.v, take ? b.i : a.i, a.sum + b.sum};
+}
+
+// Argmax (lowest index on ties) and sum over a wave, then over the work
+// group's waves, in a fixed order; every thread returns the result.
+__device__ __forceinline__ Best group_best(Best x) {
+  constexpr int kMaxWaves = 16;
+  __shared__ Best sw[kMaxWaves];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+    x = best_of(x, Best{__shfl_xor(x.v, o, 64), __shfl_xor(x.i, o, 64), __shfl_xor(x.sum, o, 64)});
+  const int waves = blockDim.x >> 6;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sw[threadIdx.x >> 6] = x;
+  __syncthreads();
+  Best r = sw[0];
+  for (int w = 1; w < waves; ++w) r = best_of(r, sw[w]);
+  return r;
+}
+
+// Fixed-order merge of nparts argmax partials by one work group: the largest
+// residual diagonal (lowest index on ties), its index and the residual trace,
+// returned to every thread.
+__device__ __forceinline__ Best merge_partials(const double* __restrict__ pv,
+                                               const int64_t* __restrict__ pi,
+                                               const double* __restrict__ psum, int nparts) {
+  Best x{-INFINITY, INT64_MAX, 0.0};
+  for (int g = threadIdx.x; g < nparts; g += blockDim.x) x = best_of(x, Best{pv[g], pi[g], psum[g]});
+  return group_best(x);
 }
 
 // acc - sum_{t < m} L[t][i] lp[t] in increasing t (one FMA each), with sixteen
@@ -168,19 +198,22 @@ __device__ __forceinline__ void stage_y(const float* __restrict__ Y, int k, int 
   }
 }
 
-// z[i][c] = s^-2 w[i][c] - s^-4 sum_m L[m][i] Y[m][c] for one row i.
+// z[i][c] = s^-2 w[i][c] - s^-4 sum_m L[m][i] Y[m][c] for one row i and the
+// columns c0 .. c0 + 7 of every sixteen.  Two threads share a row (c0 = 0 and 8):
+// twice the waves of one thread per row, so twice the loads of L in flight (the
+// pair's loads of L[m][i] are one address).
 __device__ __forceinline__ void z_row(const float* __restrict__ L, int64_t n, int k,
                                       const float* __restrict__ sy, int rp,
                                       const float* __restrict__ w, float* __restrict__ z, int r,
-                                      int64_t i, float inv_s2, float inv_s4) {
-  for (int c0 = 0; c0 < rp; c0 += 16) {
-    float acc[16];
+                                      int64_t i, int c0, float inv_s2, float inv_s4) {
+  for (; c0 < r; c0 += 16) {
+    float acc[8];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) acc[c] = 0.0f;
+    for (int c = 0; c < 8; ++c) acc[c] = 0.0f;
     auto step = [&](float l, int m) {
       const pf4* y4 = reinterpret_cast<const pf4*>(sy + m * rp + c0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < 2; ++q) {
         const pf4 y = y4[q];
         acc[4 * q + 0] = fmaf(l, y[0], acc[4 * q + 0]);
         acc[4 * q + 1] = fmaf(l, y[1], acc[4 * q + 1]);
@@ -199,10 +232,8 @@ __device__ __forceinline__ void z_row(const float* __restrict__ L, int64_t n, in
     }
     for (; m < k; ++m) step(L[(int64_t)m * n + i], m);
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const int cc = c0 + c;
-      if (cc < r) z[i * r + cc] = inv_s2 * w[i * r + cc] - inv_s4 * acc[c];
-    }
+    for (int c = 0; c < 8; ++c)
+      if (c0 + c < r) z[i * r + c0 + c] = inv_s2 * w[i * r + c0 + c] - inv_s4 * acc[c];
   }
 }
 

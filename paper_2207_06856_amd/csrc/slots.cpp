@@ -95,9 +95,9 @@ size_t layout(const SlotSpec& q, void* base, Seg* g) {
     s.T64 = c.take<double>(k * q.r);
     s.Y32 = c.take<float>(k * q.r);
     s.ltpart = c.take<float>(s.nchunk * k * q.r);
-    s.pv = c.take<double>(s.nchunk);
-    s.psum = c.take<double>(s.nchunk);
-    s.pi = c.take<int64_t>(s.nchunk);
+    s.pv = c.take<double>(2 * kSub * s.nchunk);
+    s.psum = c.take<double>(2 * kSub * s.nchunk);
+    s.pi = c.take<int64_t>(2 * kSub * s.nchunk);
   }
   if (g) *g = s;
   return c.off;
