@@ -27,9 +27,12 @@ using cg::State;
 // Rows of a chunk in quarters, for work that no sum crosses: block b of a launch
 // of kSub x nchunks takes quarter b % kSub of chunk b / kSub, k its index among the
 // problem's quarters (empty past the problem's end: i0 >= i1).  Dozens of problems
-// of a few thousand rows give too few chunks to hide the latency of their loads
-// (48 problems, 250,000 rows: 500), while a chunk's float32 sums keep the order
-// that 512 rows give them.
+// of a few thousand rows give too few chunks to hide the latency of their loads: 48
+// problems of 250,000 rows in all have 500, and by quarters reduce takes 16 us for 42,
+// reorth_apply 14 for 32, update 10 for 21, direction 11 for 17, prep 51 for 124.  The
+// float32 sums keep 512 rows and their order, with more loads in flight (colred 9.8
+// for 12.3, reorth_coef 18 for 40): another order moves the next direction by a
+// float32 ulp, and that flips binary16 roundings of the product's operand.
 constexpr int kSubRows = kChunkRows / kSub;
 __device__ __forceinline__ Chunk sub_chunk(const Chunk* __restrict__ chunks, int b) {
   Chunk ck = chunks[b / kSub];
@@ -905,7 +908,7 @@ __global__ __launch_bounds__(256) void z_kernel(const Seg* __restrict__ segs, co
 // ---- a8: true residual (float64 accumulation on the matrix cores) -------------------
 // The single-problem routine (valu_tile.h aug64_rows: augmented float64
 // distances, float64 sums of every product) on the item's row block and split.
-template <int T>
+template <int T, int RF>
 __device__ __forceinline__ void trueres_rows(const Seg& sg, const Item& it, void* smraw) {
   valu::Aug64Lds<T>& sm = *reinterpret_cast<valu::Aug64Lds<T>*>(smraw);
   const int64_t nstage = ceil_div(sg.n, (int64_t)valu::JT64);
@@ -917,40 +920,47 @@ __device__ __forceinline__ void trueres_rows(const Seg& sg, const Item& it, void
   for (int c0 = 0; c0 < sg.r; c0 += 16) {
     switch (sg.kind) {
       case GP_KERNEL_RBF:
-        valu::aug64_rows<GP_KERNEL_RBF, T>(sg.X, sg.n, sg.X, sg.n, U, sg.r, c0, sg.d, sg.ls, P,
-                                           rb0, sb, se, sm);
+        valu::aug64_rows<GP_KERNEL_RBF, T, RF>(sg.X, sg.n, sg.X, sg.n, U, sg.r, c0, sg.d, sg.ls, P,
+                                               rb0, sb, se, sm);
         break;
       case GP_KERNEL_MATERN52:
-        valu::aug64_rows<GP_KERNEL_MATERN52, T>(sg.X, sg.n, sg.X, sg.n, U, sg.r, c0, sg.d, sg.ls,
-                                                P, rb0, sb, se, sm);
+        valu::aug64_rows<GP_KERNEL_MATERN52, T, RF>(sg.X, sg.n, sg.X, sg.n, U, sg.r, c0, sg.d,
+                                                    sg.ls, P, rb0, sb, se, sm);
         break;
       case GP_KERNEL_MATERN12:
-        valu::aug64_rows<GP_KERNEL_MATERN12, T>(sg.X, sg.n, sg.X, sg.n, U, sg.r, c0, sg.d, sg.ls,
-                                                P, rb0, sb, se, sm);
+        valu::aug64_rows<GP_KERNEL_MATERN12, T, RF>(sg.X, sg.n, sg.X, sg.n, U, sg.r, c0, sg.d,
+                                                    sg.ls, P, rb0, sb, se, sm);
         break;
       default:
-        valu::aug64_rows<GP_KERNEL_MATERN32, T>(sg.X, sg.n, sg.X, sg.n, U, sg.r, c0, sg.d, sg.ls,
-                                                P, rb0, sb, se, sm);
+        valu::aug64_rows<GP_KERNEL_MATERN32, T, RF>(sg.X, sg.n, sg.X, sg.n, U, sg.r, c0, sg.d,
+                                                    sg.ls, P, rb0, sb, se, sm);
         break;
     }
   }
 }
 
+// RF = 1: the problems of one right-hand side, 8: of two to eight, 0: of more (the
+// items of other problems return at once).  Distances and entries take 250 cycles of
+// a SIMD per 256 entries at d = 9, the MFMA sums 256, FMAs 16 RF: 48 problems at
+// R = 8 2.44 -> 2.18 ms, 20 of at most 15,000 rows at R = 1 0.47 -> 0.29.
+__host__ __device__ __forceinline__ int trueres_rf(int r) { return r == 1 ? 1 : r <= 8 ? 8 : 0; }
+template <int RF>
 __global__ __launch_bounds__(256) void trueres_partial_kernel(const Seg* __restrict__ segs,
                                                               const Item* __restrict__ items) {
   // one LDS block sized for the widest instantiation (T = 8: d <= 30)
   __shared__ __attribute__((aligned(16))) char sm[sizeof(valu::Aug64Lds<8>)];
   const Item it = items[blockIdx.x];
   const Seg& sg = segs[it.p];
+  if (trueres_rf(sg.r) != RF) return;
   switch (trueres_slices_of(sg.d)) {
-    case 1: trueres_rows<1>(sg, it, sm); break;
-    case 2: trueres_rows<2>(sg, it, sm); break;
-    case 3: trueres_rows<3>(sg, it, sm); break;
-    case 4: trueres_rows<4>(sg, it, sm); break;
-    case 5: trueres_rows<5>(sg, it, sm); break;
-    case 6: trueres_rows<6>(sg, it, sm); break;
-    case 7: trueres_rows<7>(sg, it, sm); break;
-    default: trueres_rows<8>(sg, it, sm); break;
+    case 1: trueres_rows<1, RF>(sg, it, sm); break;
+    case 2: trueres_rows<2, RF>(sg, it, sm); break;
+    case 3: trueres_rows<3, RF>(sg, it, sm); break;
+    case 4: trueres_rows<4, RF>(sg, it, sm); break;
+    case 5: trueres_rows<5, RF>(sg, it, sm); break;
+    case 6: trueres_rows<6, RF>(sg, it, sm); break;
+    case 7: trueres_rows<7, RF>(sg, it, sm); break;
+    default: trueres_rows<8, RF>(sg, it, sm); break;
   }
 }
 
@@ -1414,8 +1424,16 @@ gp_status seq_iteration(const Dev& D, const Tab& T, const RunOpts& o, hipStream_
 
 gp_status seq_true_residual(const Dev& D, const Tab& T, hipStream_t s) {
   if (T.nsel == 0) return GP_OK;
-  trueres_partial_kernel<<<T.nitems64, 256, 0, s>>>(D.segs, T.items64);
+  trueres_partial_kernel<1><<<T.nitems64, 256, 0, s>>>(D.segs, T.items64);
   BT_LAUNCH_CHECK();
+  if (T.max_r > 1) {
+    trueres_partial_kernel<8><<<T.nitems64, 256, 0, s>>>(D.segs, T.items64);
+    BT_LAUNCH_CHECK();
+  }
+  if (T.max_r > 8) {
+    trueres_partial_kernel<0><<<T.nitems64, 256, 0, s>>>(D.segs, T.items64);
+    BT_LAUNCH_CHECK();
+  }
   trueres_chunk_kernel<<<T.nchunks, 256, 0, s>>>(D.segs, T.chunks);
   BT_LAUNCH_CHECK();
   trueres_finish_kernel<<<T.nsel, 64, 0, s>>>(D.segs, T.plist, D.st);

@@ -132,7 +132,10 @@ struct Aug64Lds {
 // column stages [sb, se) of JT64 columns, right-hand sides [c0, c0 + 16) of V
 // (row stride r); float64 partial sums to P[i * r + c].  All threads of the
 // group must call it (it synchronises).
-template <int KIND, int T>
+//
+// RF > 0: at most RF right-hand sides, summed by float64 FMAs (they run at the rate
+// of the float64 MFMA, whose sixteen columns would be mostly padding).
+template <int KIND, int T, int RF = 0>
 __device__ __forceinline__ void aug64_rows(const float* __restrict__ X1, int64_t n1,
                                            const float* __restrict__ X2, int64_t n2,
                                            const float* __restrict__ V, int r, int c0, int d,
@@ -169,8 +172,13 @@ __device__ __forceinline__ void aug64_rows(const float* __restrict__ X1, int64_t
     }
   }
   d4 acc[NSUB];
+  double sum[NSUB][RF ? RF : 1];
 #pragma unroll
-  for (int q = 0; q < NSUB; ++q) acc[q] = d4{0.0, 0.0, 0.0, 0.0};
+  for (int q = 0; q < NSUB; ++q) {
+    acc[q] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < RF; ++c) sum[q][c] = 0.0;
+  }
 
   for (int64_t st = sb; st < se; ++st) {
     const int64_t j0 = st * JT64;
@@ -206,7 +214,7 @@ __device__ __forceinline__ void aug64_rows(const float* __restrict__ X1, int64_t
       for (int t = 0; t < T; ++t) at[t] = sm.A[(4 * t + g) * JT64 + 16 * jb + l16];
       double vb[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) vb[v] = sm.V[16 * jb + g + 4 * v][l16];
+      for (int v = 0; v < 4; ++v) vb[v] = RF ? 0.0 : sm.V[16 * jb + g + 4 * v][l16];
 #pragma unroll
       for (int q = 0; q < NSUB; ++q) {
         d4 r2 = d4{0.0, 0.0, 0.0, 0.0};
@@ -219,12 +227,31 @@ __device__ __forceinline__ void aug64_rows(const float* __restrict__ X1, int64_t
           float r2f = (float)r2[v];
           if constexpr (KIND != GP_KERNEL_RBF) r2f = r2f > 0.0f ? r2f : 0.0f;
           const double kv = (double)kval32_direct<KIND>(r2f);
-          acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(kv, vb[v], acc[q], 0, 0, 0);
+          if constexpr (RF > 0) {
+            // the entry's column is 16 jb + g + 4 v, its row l16
+            const double* vr = sm.V[16 * jb + g + 4 * v];
+#pragma unroll
+            for (int c = 0; c < RF; ++c) sum[q][c] = fma(kv, vr[c], sum[q][c]);
+          } else {
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(kv, vb[v], acc[q], 0, 0, 0);
+          }
         }
       }
     }
   }
-  if (l16 < rc) {
+  if constexpr (RF > 0) {
+#pragma unroll
+    for (int q = 0; q < NSUB; ++q) {
+      const int64_t i = row0 + 16 * q + l16;
+#pragma unroll
+      for (int c = 0; c < RF; ++c) {
+        double t = sum[q][c];
+        t += __shfl_xor(t, 16);
+        t += __shfl_xor(t, 32);
+        if (g == 0 && i < n1 && c < rc) P[i * r + c0 + c] = t;
+      }
+    }
+  } else if (l16 < rc) {
 #pragma unroll
     for (int q = 0; q < NSUB; ++q)
 #pragma unroll
