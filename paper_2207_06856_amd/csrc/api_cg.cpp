@@ -346,6 +346,13 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
 
   Arena ar;
   gp_status wst = workspace_get(s, plan_bytes(p, want_history), &ar);
+  if (wst == GP_ERR_NOMEM && (p.f32_split || p.t64_split)) {
+    // the split operands do not fit: the vector forms need none
+    clear_error();
+    p.f32_split = p.t64_split = false;
+    p.nsplit64 = valu::choose_splits64(n, n, d);
+    wst = workspace_get(s, plan_bytes(p, want_history), &ar);
+  }
   if (wst == GP_ERR_NOMEM && p.sym) {
     // the symmetric product's partial sums (n^2 R 4 / (2 panel) bytes) do not
     // fit: the one-sided product's workspace is O(n)

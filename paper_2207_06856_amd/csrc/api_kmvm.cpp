@@ -226,7 +226,13 @@ static gp_status kmvm_f32_split(const KParams& kp, const float* X1, int64_t n1, 
     if (*no_room) return GP_OK;
   }
   Arena ar;
-  GP_TRY(scratch_arena(src, s, bytes, &ar));
+  const gp_status wst = scratch_arena(src, s, bytes, &ar);
+  if (wst == GP_ERR_NOMEM) {
+    clear_error();
+    *no_room = true;
+    return GP_OK;
+  }
+  GP_TRY(wst);
   GP_TRY(split::carve(p, kp.d, ar));
   float* part = ar.take<float>(std::max((size_t)p.nsplit * p.n1_pad * p.rp, (size_t)vsplit * n1 * r));
   if (!part) return set_error(GP_ERR_NOMEM, "internal: workspace sizing");

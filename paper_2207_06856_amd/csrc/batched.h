@@ -54,7 +54,7 @@ struct Seg {
   float* c1;             // (max_iter + 1) x r first-pass coefficients
   float* gram;           // (max_iter + 1)^2 x r basis Gram matrix w_j^T u_k
   float* ltpart;         // nchunk x rank x r
-  double* pv;            // 2 x quarter chunks: argmax value (by step parity)
+  double* pv;            // 2 x quarter chunks: argmax value by step parity (in part, as psum and pi)
   double* psum;          // 2 x quarter chunks: diagonal sum
   int64_t* pi;           // 2 x quarter chunks: argmax index
   int64_t n, n_pad_r, n_pad_c;

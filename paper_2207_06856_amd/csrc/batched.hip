@@ -28,7 +28,7 @@ using cg::State;
 // of kSub x nchunks takes quarter b % kSub of chunk b / kSub, k its index among the
 // problem's quarters (empty past the problem's end: i0 >= i1).  Dozens of problems
 // of a few thousand rows give too few chunks to hide the latency of their loads: 48
-// problems of 250,000 rows in all have 500, and by quarters reduce takes 16 us for 42,
+// problems of 220,000 rows in all have 500, and by quarters reduce takes 16 us for 42,
 // reorth_apply 14 for 32, update 10 for 21, direction 11 for 17, prep 51 for 124.  The
 // float32 sums keep 512 rows and their order, with more loads in flight (colred 9.8
 // for 12.3, reorth_coef 18 for 40): another order moves the next direction by a

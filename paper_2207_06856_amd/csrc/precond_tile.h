@@ -24,7 +24,7 @@ constexpr int kLtResidentChunks = 512;  // 2 work groups x 256 compute units
 // lane l, element v holds pivot tile + 4 * (l / 16) + v, column ctile + l % 16.
 // The loads of the next 4 U rows are issued before the products of the current
 // ones.  Bound by the loads' latency: staged through LDS in 32-row tiles, two
-// barriers each, 48 problems of rank 20 and 250,000 rows (20 MB of L) took 34 us,
+// barriers each, 48 problems of rank 20 and 220,000 rows (20 MB of L) took 34 us,
 // 17 now; 100,000 rows at rank 100, R = 16 (40 MB) 25 us both ways.  Eight rows in a
 // row per lane would take 12 and 17, but sum in another order, and a float32 ulp
 // of z flips binary16 roundings of the next direction.

@@ -95,9 +95,13 @@ size_t layout(const SlotSpec& q, void* base, Seg* g) {
     s.T64 = c.take<double>(k * q.r);
     s.Y32 = c.take<float>(k * q.r);
     s.ltpart = c.take<float>(s.nchunk * k * q.r);
-    s.pv = c.take<double>(2 * kSub * s.nchunk);
-    s.psum = c.take<double>(2 * kSub * s.nchunk);
-    s.pi = c.take<int64_t>(2 * kSub * s.nchunk);
+    // the argmax partials (48 kSub bytes a chunk of 512 rows) lie in the product's
+    // partials (64 bytes a row and more), which no launch uses before the build ends
+    if (s.part) {
+      s.pv = reinterpret_cast<double*>(s.part);
+      s.psum = s.pv + 2 * kSub * s.nchunk;
+      s.pi = reinterpret_cast<int64_t*>(s.psum + 2 * kSub * s.nchunk);
+    }
   }
   if (g) *g = s;
   return c.off;
