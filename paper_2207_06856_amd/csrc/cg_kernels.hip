@@ -1022,19 +1022,18 @@ gp_status direction_step(const float* z, float* d, const float* rr, float* U, fl
 // matrix, gamma, beta, convergence, the next direction and the basis append.
 // A solve this small spends its iteration on launches and on the latency of
 // their first loads (ten of them, 50 us at n = 2000, R = 1, 8.5 of which is the
-// product); here a phase costs a barrier: 28 us and the product's 8.3, the
-// solve of 60 iterations 3.45 -> 2.50 ms.  Bound by the latency of its chain of
+// product); here a phase costs a barrier: 23 us and the product's 8.3, the
+// solve of 60 iterations 3.5 -> 2.2 ms.  Bound by the latency of its chain of
 // loads, reductions and float64 scalars.  Thread (row lane, column) as in the
-// kernels above; each thread keeps its KE entries of d, q and r in registers (16
-// loads in flight; 32 spill at 1024 threads, 39 us), r and the newest basis
-// vector also lie in LDS for the sweep, in which every wave takes whole basis
-// vectors.
+// kernels above; each thread keeps its KE entries of d, q, r and x in registers
+// (16 loads in flight; 32 gain nothing), r and the newest basis vector also lie
+// in LDS for the sweep, in which every wave takes whole basis vectors.
 // Where the line lies: one compute unit reads the split sums and the basis at
-// 100 to 150 GB/s.  Two entries a thread: n = 2040, R = 1 3.35 -> 2.52 ms, n = 256,
-// R = 8 2.25 -> 1.53 ms.  Four: n = 250, R = 16 3.10 -> 2.11 ms, n = 2040, R = 2 4.14
-// -> 3.65 ms, but n = 4090, R = 1, whose product has more splits, 4.69 -> 4.94 ms.
-// Eight: n = 4000, R = 2 6.59 -> 7.00 ms.  393216 stored floats are 96 pairs of 4096:
-// n = 2040, R = 2, 70 iterations 4.24 -> 3.58 ms, 3.70 at 64 pairs, 3.83 at 32.
+// 100 to 150 GB/s.  Two entries a thread: n = 2040, R = 1 3.35 -> 2.2 ms, n = 256,
+// R = 8 2.25 -> 1.4 ms.  Four: n = 250, R = 16 3.10 -> 2.0 ms, n = 2040, R = 2 4.14
+// -> 3.2 ms, but n = 4090, R = 1, whose product has more splits, 4.69 -> 4.9 ms.
+// Eight: n = 4000, R = 2 6.59 -> 7.0 ms.  393216 stored floats are 96 pairs of 4096:
+// n = 2040, R = 2, 70 iterations: 64 pairs cost 0.1 ms more, 32 0.25.
 constexpr int kFusedThreads = 1024;
 constexpr int kFusedRows = 2048;                                     // n at most
 constexpr int kFusedMax = 4 * kFusedThreads;                         // n * rp2 at most
@@ -1046,41 +1045,84 @@ bool fused_step_fits(const Dims& dm, bool reorth, int pairs) {
   return !reorth || (pairs * dm.r <= kFusedCoef && pairs * dm.n * dm.r <= kFusedBasis);
 }
 
-// Per-column reductions over the group's row lanes: across the lanes of a wave
-// that share a column, then over the 16 waves in order; every thread returns
-// its column's result.
-__device__ __forceinline__ float fused_sum(float v, int rp2, float (*buf)[kMaxR]) {
-  for (int o = 32; o >= rp2; o >>= 1) v += __shfl_xor(v, o, 64);
-  const int lane = threadIdx.x & 63;
-  __syncthreads();
-  if (lane < rp2) buf[threadIdx.x >> 6][lane] = v;
-  __syncthreads();
-  float t = buf[0][threadIdx.x % rp2];
-#pragma unroll
-  for (int w = 1; w < 16; ++w) t += buf[w][threadIdx.x % rp2];
-  return t;
+// Per-column reduction over the group's row lanes of the LSE pair (m, S) or the
+// sum S, and of the sum q2: across the lanes of a wave that share a column, then
+// over the 16 waves by wave 0, whose lanes alone return the result.  Pairs are
+// merged by the largest m first (one exponential each), not one by one: merging 16
+// pairs in a row in all 16 waves took a third of the step.
+struct FusedLds {
+  float m[16][kMaxR], s[16][kMaxR], q[16][kMaxR];
+};
+template <bool LSE>
+__device__ __forceinline__ void fused_rescale(float& S, float m, float M) {
+  if (LSE && m != -INFINITY) S *= __expf(m - M);     // S of an empty pair is 0 or NaN
 }
-__device__ __forceinline__ void fused_lse(float& m, float& S, int rp2, float (*bm)[kMaxR],
-                                          float (*bs)[kMaxR]) {
-  for (int o = 32; o >= rp2; o >>= 1) {
-    const float m2 = __shfl_xor(m, o, 64), S2 = __shfl_xor(S, o, 64);
-    // the lower lane's pair first, so that both lanes form the same value
-    float ma = (threadIdx.x & o) ? m2 : m, Sa = (threadIdx.x & o) ? S2 : S;
-    const float mb = (threadIdx.x & o) ? m : m2, Sb = (threadIdx.x & o) ? S : S2;
-    lse_merge(ma, Sa, mb, Sb);
-    m = ma;
-    S = Sa;
-  }
-  const int lane = threadIdx.x & 63;
+template <bool LSE>
+__device__ __forceinline__ void fused_reduce(float& m, float& S, float& q2, int rp2, FusedLds& sm) {
+  auto across = [&] {
+    if (LSE) {
+      float M = m;
+      for (int o = 32; o >= rp2; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+      fused_rescale<LSE>(S, m, M);
+      m = M;
+    }
+    for (int o = 32; o >= rp2; o >>= 1) {
+      S += __shfl_xor(S, o, 64);
+      q2 += __shfl_xor(q2, o, 64);
+    }
+  };
+  across();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   __syncthreads();
   if (lane < rp2) {
-    bm[threadIdx.x >> 6][lane] = m;
-    bs[threadIdx.x >> 6][lane] = S;
+    sm.m[wave][lane] = m;
+    sm.s[wave][lane] = S;
+    sm.q[wave][lane] = q2;
   }
   __syncthreads();
+  if (wave != 0) return;
+  const int c = lane % rp2, step = 64 / rp2;
+  m = -INFINITY;
+  if (LSE)
+    for (int w = lane / rp2; w < 16; w += step) m = fmaxf(m, sm.m[w][c]);
+  S = q2 = 0.0f;
+  for (int w = lane / rp2; w < 16; w += step) {
+    float t = sm.s[w][c];
+    fused_rescale<LSE>(t, sm.m[w][c], m);
+    S += t;
+    q2 += sm.q[w][c];
+  }
+  across();
+}
+// The pair or sum of KE products u_k v_k (in[k]).
+template <bool LSE, int KE>
+__device__ __forceinline__ void fused_terms(const float (&u)[KE], const float (&v)[KE],
+                                            const bool (&in)[KE], float& m, float& S) {
   m = -INFINITY;
   S = 0.0f;
-  for (int w = 0; w < 16; ++w) lse_merge(m, S, bm[w][threadIdx.x % rp2], bs[w][threadIdx.x % rp2]);
+  if (LSE) {
+    float y[KE];
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < KE; ++k) {
+      const bool some = in[k] && u[k] != 0.0f && v[k] != 0.0f;
+      y[k] = some ? __logf(fabsf(u[k])) + __logf(fabsf(v[k])) : -INFINITY;
+      bad |= some && !isfinite(y[k]);
+      m = fmaxf(m, y[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < KE; ++k)
+      if (y[k] != -INFINITY)
+        S += ((u[k] < 0.0f) != (v[k] < 0.0f)) ? -__expf(y[k] - m) : __expf(y[k] - m);
+    if (bad) {
+      m = -INFINITY;
+      S = NAN;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < KE; ++k)
+      if (in[k]) S = fmaf(u[k], v[k], S);
+  }
 }
 
 template <bool LSE, int KE>
@@ -1092,7 +1134,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
   if (st->nactive == 0) return;
   __shared__ float sR[KE * kFusedThreads], sU[KE * kFusedThreads];
   __shared__ float sc1[kFusedCoef], scoef[kFusedCoef];
-  __shared__ float bm[16][kMaxR], bs[16][kMaxR];
+  __shared__ FusedLds red;
   __shared__ float s_alpha[kMaxR], s_beta[kMaxR], s_sg[kMaxR];
   __shared__ int s_act[kMaxR], s_live;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1102,7 +1144,6 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
   float dv[KE], qv[KE], rv[KE];
 
   // q = K~ d and d^T q
-  float m = -INFINITY, S = 0.0f;
   int at[KE];                               // entries; a valid one where there is none
   bool in[KE];
 #pragma unroll
@@ -1112,6 +1153,15 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
     at[k] = in[k] ? i * r + c : 0;
     dv[k] = in[k] ? d[at[k]] : 0.0f;
     qv[k] = 0.0f;
+  }
+  // what the update needs, read ahead of the reductions
+  const float* Un = U + max(nb - 1, 0) * nr;
+  float xv[KE], un[KE];
+#pragma unroll
+  for (int k = 0; k < KE; ++k) {
+    xv[k] = in[k] ? x[at[k]] : 0.0f;
+    rv[k] = in[k] ? rr[at[k]] : 0.0f;
+    un[k] = in[k] && nb > 0 ? Un[at[k]] : 0.0f;
   }
   // the split sums in split order, 16 loads in flight
   constexpr int kAhead = 16 / KE;
@@ -1129,19 +1179,9 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
   }
 #pragma unroll
   for (int k = 0; k < KE; ++k) qv[k] = in[k] ? fmaf(s2, dv[k], a2 * qv[k]) : 0.0f;
-#pragma unroll
-  for (int k = 0; k < KE; ++k) {
-    if (in[k]) {
-      if (LSE)
-        lse_push(m, S, dv[k], qv[k]);
-      else
-        S = fmaf(dv[k], qv[k], S);
-    }
-  }
-  if (LSE)
-    fused_lse(m, S, rp2, bm, bs);
-  else
-    S = fused_sum(S, rp2, bs);
+  float m, S, q2 = 0.0f;
+  fused_terms<LSE, KE>(dv, qv, in, m, S);
+  fused_reduce<LSE>(m, S, q2, rp2, red);
   if (wave == 0) {
     const int kk = st->k + 1;
     int act = 0;
@@ -1183,24 +1223,18 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
   bool act = c < r && s_act[c];
 #pragma unroll
   for (int k = 0; k < KE; ++k) {
-    rv[k] = 0.0f;
-    if (in[k]) {
-      const int e = at[k];
-      rv[k] = rr[e];
-      if (act) {
-        x[e] = fmaf(s_alpha[c], dv[k], x[e]);
-        rv[k] = fmaf(s_alpha[c], qv[k], rv[k]);
-      }
+    if (in[k] && act) {
+      x[at[k]] = fmaf(s_alpha[c], dv[k], xv[k]);
+      rv[k] = fmaf(s_alpha[c], qv[k], rv[k]);
     }
   }
   if (nb > 0) {
     // c1_j = u_j^T r and the newest Gram column u_j^T u_new, one wave per j
-    const float* Un = U + (nb - 1) * nr;
 #pragma unroll
     for (int k = 0; k < KE; ++k) {
       if (in[k]) {
         sR[at[k]] = rv[k];
-        sU[at[k]] = Un[at[k]];
+        sU[at[k]] = un[k];
       }
     }
     __syncthreads();
@@ -1268,22 +1302,18 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
   }
 
   // ||r||, gamma, beta, convergence (z = r)
-  float q2 = 0.0f;
-  m = -INFINITY;
-  S = 0.0f;
+  q2 = 0.0f;
 #pragma unroll
   for (int k = 0; k < KE; ++k) {
     if (in[k]) {
       if (act) rr[at[k]] = rv[k];
       q2 = fmaf(rv[k], rv[k], q2);
-      if (LSE) lse_push(m, S, rv[k], rv[k]);
     }
   }
-  const float rr2 = fused_sum(q2, rp2, bs);
-  if (LSE)
-    fused_lse(m, S, rp2, bm, bs);
-  else
-    S = rr2;
+  if (LSE) fused_terms<LSE, KE>(rv, rv, in, m, S);
+  fused_reduce<LSE>(m, S, q2, rp2, red);
+  const float rr2 = q2;
+  if (!LSE) S = rr2;
   const int slot = st->nbasis;
   __syncthreads();
   if (wave == 0) {
