@@ -942,10 +942,10 @@ __device__ __forceinline__ void trueres_rows(const Seg& sg, const Item& it, void
 // RF = 1: the problems of one right-hand side, 8: of two to eight, 0: of more (the
 // items of other problems return at once).  Distances and entries take 250 cycles of
 // a SIMD per 256 entries at d = 9, the MFMA sums 256, FMAs 16 RF: 48 problems at
-// R = 8 2.44 -> 2.18 ms, 20 of at most 15,000 rows at R = 1 0.47 -> 0.29.
+// R = 8 2.44 -> 2.18 ms (2.00 with the next stage read ahead), 20 of at most 15,000 rows at R = 1 0.47 -> 0.29.
 __host__ __device__ __forceinline__ int trueres_rf(int r) { return r == 1 ? 1 : r <= 8 ? 8 : 0; }
 template <int RF>
-__global__ __launch_bounds__(256) void trueres_partial_kernel(const Seg* __restrict__ segs,
+__global__ __launch_bounds__(256, 2) void trueres_partial_kernel(const Seg* __restrict__ segs,
                                                               const Item* __restrict__ items) {
   // one LDS block sized for the widest instantiation (T = 8: d <= 30)
   __shared__ __attribute__((aligned(16))) char sm[sizeof(valu::Aug64Lds<8>)];

@@ -180,19 +180,45 @@ __device__ __forceinline__ void aug64_rows(const float* __restrict__ X1, int64_t
     for (int c = 0; c < RF; ++c) sum[q][c] = 0.0;
   }
 
+  // the next stage's coordinates (d <= 4 T - 2: T a thread) and right-hand sides are
+  // read into registers while this one is computed: 48 batched problems, R = 8 2.18 ->
+  // 2.00 ms (two waves a SIMD: the batched kernel is bounded to 256 registers), 100,000
+  // points, R = 16, Matern-1/2 0.47 ms less in a solve of 24.8
+  float xr[T], vr[JT64 * 16 / 256];
+  auto gload = [&](int64_t st) {
+    const int64_t j0 = st * JT64;
+    const int jn = (int)min<int64_t>(JT64, n2 - j0);
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+      const int e = threadIdx.x + 256 * u;
+      xr[u] = e < jn * d ? X2[j0 * d + e] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < JT64 * 16 / 256; ++u) {
+      const int e = threadIdx.x + 256 * u, jj = e >> 4, c = e & 15;
+      vr[u] = jj < jn && c < rc ? V[(j0 + jj) * r + c0 + c] : 0.0f;
+    }
+  };
+  if (sb < se) gload(sb);
   for (int64_t st = sb; st < se; ++st) {
     const int64_t j0 = st * JT64;
     const int jn = (int)min<int64_t>(JT64, n2 - j0);
     __syncthreads();
     // column coordinates of the stage (contiguous in X2): slot m <- -2 b_m
-    for (int e = threadIdx.x; e < JT64 * d; e += blockDim.x) {
-      const int jj = e / d, m = e - jj * d;
-      sm.A[m * JT64 + jj] = jj < jn ? -2.0 * ((double)X2[j0 * d + e] * sm.inv[m]) : 0.0;
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+      const int e = threadIdx.x + 256 * u;
+      if (e < JT64 * d) {
+        const int jj = e / d, m = e - jj * d;
+        sm.A[m * JT64 + jj] = -2.0 * ((double)xr[u] * sm.inv[m]);
+      }
     }
-    for (int e = threadIdx.x; e < JT64 * 16; e += blockDim.x) {
-      const int jj = e >> 4, c = e & 15;
-      sm.V[jj][c] = (jj < jn && c < rc) ? (double)V[(j0 + jj) * r + c0 + c] : 0.0;
+#pragma unroll
+    for (int u = 0; u < JT64 * 16 / 256; ++u) {
+      const int e = threadIdx.x + 256 * u;
+      sm.V[e >> 4][e & 15] = (double)vr[u];
     }
+    if (st + 1 < se) gload(st + 1);
     __syncthreads();
     // slots d, d + 1 (|b|^2, 1) and the zero padding; a padded column is all
     // zero, so its distance is 0, its entry finite, and its right-hand side 0
