@@ -141,11 +141,8 @@ __global__ __launch_bounds__(256) void colmax_kernel(const float* __restrict__ U
 // Column c gets U_c 2^(e_c + gam), C_c 2^(gam - e_c) with e_c the rounded
 // half of log2(max |C_c| / max |U_c|) (balanced largest entries, each within
 // 2^0.5 of m_c = sqrt(max |U_c| max |C_c|)), and gam puts the largest m_c at or
-// below 2^14; where the split form runs (info->ok), the largest entry that W~ can
-// have times the largest G (3) at or below 2^15 instead, since it rounds
-// P = G W~ to binary16 parts.
-__global__ void scale_kernel(const uint32_t* __restrict__ cmax, int r,
-                             const split::Info* __restrict__ info, float* __restrict__ scl) {
+// below 2^14.
+__global__ void scale_kernel(const uint32_t* __restrict__ cmax, int r, float* __restrict__ scl) {
   __shared__ float sm[64];
   __shared__ int sgam;
   const int c = threadIdx.x;
@@ -163,12 +160,7 @@ __global__ void scale_kernel(const uint32_t* __restrict__ cmax, int r,
   if (c == 0) {
     float mx = 0.0f;
     for (int k = 0; k < 64; ++k) mx = fmaxf(mx, sm[k]);
-    int gam = mx > 0.0f ? 14 - (int)ceilf(log2f(mx)) : 0;
-    if (info && info->ok && mx > 0.0f) {
-      double w = 0.0;
-      for (int k = 0; k < 64; ++k) w += (double)sm[k] * (double)sm[k];
-      gam = (int)floor(0.5 * (15.0 - ceil(log2(6.0 * w))));
-    }
+    const int gam = mx > 0.0f ? 14 - (int)ceilf(log2f(mx)) : 0;
     sgam = max(-60, min(60, gam));
     scl[128] = ldexpf(1.0f, -2 * sgam);
   }
@@ -677,7 +669,7 @@ gp_status launch(const KParams& kp, bool ard, const float* X, int64_t n, const f
     GP_TRY(fill_f32(reinterpret_cast<float*>(w.cmax), 128, 0.0f, s));
     colmax_kernel<<<(unsigned)ceil_div(n, kColmaxRows), 256, 0, s>>>(U, B, n, r, inv2m, w.cmax);
     GP_HIP(hipGetLastError());
-    scale_kernel<<<1, 64, 0, s>>>(w.cmax, r, w.skip, w.scl);
+    scale_kernel<<<1, 64, 0, s>>>(w.cmax, r, w.scl);
     GP_HIP(hipGetLastError());
     if (split_form)
       GP_TRY(split_launch(sw, kp, iso, X, n, U, B, r, inv2m, w.scl, spart, s));

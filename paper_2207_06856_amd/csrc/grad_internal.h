@@ -8,20 +8,26 @@ namespace gpmi {
 namespace grad {
 
 constexpr int kGradSplitMaxDim = 16;
-// Its five extra launches cost about 18 us.  With one lengthscale per input the
-// difference form's work is n^2 (3 d + 12): at 4e8 (N = 3000, d = 12) 161 us
-// against 131, at 5e7 (N = 1500, d = 3) 101 against 119.  One isotropic
-// lengthscale leaves only the distance and W to gain on: N = 10,000 129 us
-// against 140, N = 60,000 1050 against 930.
-constexpr double kGradSplitMinWork = 2e8;
-constexpr int64_t kGradSplitMinIso = 16384;
+// Points from which this form is taken.  Its five extra launches cost about 18 us;
+// what it saves per entry depends on how the S_m are summed (grad_split.hip).  The
+// call in us, difference form against this one (R = 16):
+//   d >= 9: n = 2000 125 against 133, 2500 145 against 133, 6000 259 against 160;
+//   d = 5 to 8: n = 4000 127 against 129, 6000 154 against 147, 32,000 698 against
+//     630 (Matern-5/2: 16,000 308 against 309, 24,000 514 against 497);
+//   d <= 4: n = 20,000 256 against 273, 32,000 471 against 456;
+//   one lengthscale: d <= 5 n = 20,000 196 against 207, 28,000 281 against 273;
+//     d >= 6 n = 12,000 162 against 161, 16,384 208 against 189.
+inline int64_t split_min_points(int d, bool iso) {
+  if (iso) return d <= 5 ? 24576 : 16384;
+  return d <= 4 ? 28672 : d <= 8 ? 6144 : 2250;
+}
 
 struct SplitWork {
   split::Plan p;               // point operands
   int64_t rblocks;
-  int nsplit, comps;
+  int nsplit, width;
   _Float16* H;                 // n_pad x 4 x 16 parts of U and C
-  _Float16* Zt;                // 2 x comps x n_pad parts of [b | b^2]
+  double* Zb;                  // n_pad x width coordinates b
 };
 // whether the gradient over `rows` rows of n takes this form (the inputs' range
 // is checked on the device: Info::ok)

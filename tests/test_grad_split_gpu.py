@@ -1,7 +1,7 @@
-"""The gradient's split-operand form (grad_split.hip) against the float64 oracle,
-at the bound of the other gradient tests: 2e-5 sum |dK~_ij| |W_ij| per component
-(22-bit parts of P, W and the coordinates: 2^-22 per factor and product, times
-at most (spread / lengthscale)^2 <= 16 for the expanded squares here)."""
+"""The gradient's split-operand form (grad_split.hip) and its neighbours below the lines
+of its rule against the float64 oracle, at the bound of the other gradient tests:
+2e-5 sum |dK~_ij| |W_ij| per component (float32 kernel values and P = G W, 22-bit parts
+of U and C, float64 sums; float32 differences of coordinates up to d = 4)."""
 
 import numpy as np
 import pytest
