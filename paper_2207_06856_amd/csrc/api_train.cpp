@@ -51,10 +51,13 @@ extern "C" gp_status gp_mll_grad(const gp_kernel* k, const float* X, int64_t n, 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int nl = nlen(d, k->ard);
   Arena ar;
-  GP_TRY(workspace_get(s, grad::workspace_bytes(row_end - row_begin, n, kp.kind, d, k->ard != 0, r) + 8 * (nl + 3) + 256, &ar));
+  bool split_form = false;
+  GP_TRY(grad::workspace(s, row_end - row_begin, n, kp.kind, d, k->ard != 0, r, 8 * (nl + 3) + 256,
+                         &ar, &split_form));
   double* out = ar.take<double>(nl + 3);
   if (!out) return set_error(GP_ERR_NOMEM, "internal: gradient workspace sizing");
-  GP_TRY(grad::launch(kp, k->ard != 0, X, n, U, B, r, row_begin, row_end, out, ar, s));
+  GP_TRY(grad::launch(kp, k->ard != 0, X, n, U, B, r, row_begin, row_end, split_form,
+                      out, ar, s));
   GP_HIP(hipMemcpyAsync(grad, out, 8 * (size_t)(nl + 3), hipMemcpyDeviceToHost, s));
   GP_HIP(hipStreamSynchronize(s));
   return GP_OK;
@@ -214,8 +217,10 @@ extern "C" gp_status gp_trainer_step(gp_trainer* t, gp_train_step_info* info) {
   KParams kp;
   GP_TRY(check_kernel(&k, t->d, false, &kp));
   Arena ar;
-  GP_TRY(workspace_get(t->s, grad::workspace_bytes(t->n, t->n, kp.kind, t->d, t->c.ard != 0, r), &ar));
-  GP_TRY(grad::launch(kp, t->c.ard != 0, t->X, t->n, t->U, t->B, r, 0, t->n, t->st->grad, ar, t->s));
+  bool split_form = false;
+  GP_TRY(grad::workspace(t->s, t->n, t->n, kp.kind, t->d, t->c.ard != 0, r, 0, &ar, &split_form));
+  GP_TRY(grad::launch(kp, t->c.ard != 0, t->X, t->n, t->U, t->B, r, 0, t->n, split_form, t->st->grad,
+                      ar, t->s));
   const train::DevState before = t->host;
   GP_TRY(train::launch_adam(t->st, nl, t->n, train::AdamOpts{t->c.lr, t->c.beta1, t->c.beta2, t->c.eps, t->c.use_priors != 0}, t->s));
   GP_TRY(sync_state(t));

@@ -617,22 +617,34 @@ int choose_splits(int64_t rows, int64_t n, int d) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(want, nstage));
 }
 
-size_t workspace_bytes(int64_t rows, int64_t n, int kind, int d, bool ard, int r) {
+static size_t workspace_bytes(int64_t rows, int64_t n, int d, bool ard, int r, bool split_form) {
   const int64_t nblk = row_blocks(rows, d) * choose_splits(rows, n, d);
   const int64_t nchunk = ceil_div(std::max<int64_t>(rows, 1), kDiagRows);
   size_t b = 8 * (size_t)nblk * (kMaxDim + 1) + 16 * (size_t)nchunk +
              4 * (size_t)n * (dm_of(d) + 1) + 2 * (size_t)n * 4 * rp_of(r) + 4 * 128 + 4 * 129 +
              8 * (kMaxDim + 3) + 9 * 256;
-  if (use_split(kind, n, d, !ard, r, rows)) {
+  if (split_form) {
     const SplitWork w = split_plan(n, d, !ard);
     b += split_bytes(w, d) + 8 * (size_t)(w.rblocks * w.nsplit) * (d + 1) + 256;
   }
   return b;
 }
 
+gp_status workspace(hipStream_t s, int64_t rows, int64_t n, int kind, int d, bool ard, int r,
+                    size_t extra, Arena* ar, bool* split_form) {
+  *split_form = use_split(kind, n, d, !ard, r, rows);
+  gp_status st = workspace_get(s, workspace_bytes(rows, n, d, ard, r, *split_form) + extra, ar);
+  if (st == GP_ERR_NOMEM && *split_form) {
+    clear_error();
+    *split_form = false;
+    st = workspace_get(s, workspace_bytes(rows, n, d, ard, r, false) + extra, ar);
+  }
+  return st;
+}
+
 gp_status launch(const KParams& kp, bool ard, const float* X, int64_t n, const float* U,
-                 const float* B, int r, int64_t i0, int64_t i1, double* out, Arena& ar,
-                 hipStream_t s) {
+                 const float* B, int r, int64_t i0, int64_t i1, bool split_form, double* out,
+                 Arena& ar, hipStream_t s) {
   const int64_t rows = i1 - i0;
   const int nsplit = choose_splits(rows, n, kp.d);
   const int64_t nblk = rows > 0 ? row_blocks(rows, kp.d) * nsplit : 0;
@@ -651,7 +663,6 @@ gp_status launch(const KParams& kp, bool ard, const float* X, int64_t n, const f
   if (!part || !dpart || !w.Xs || !w.nr || !w.H || !w.cmax || !w.scl || !w.sums)
     return set_error(GP_ERR_NOMEM, "internal: gradient workspace sizing");
   const float inv2m = (float)(0.5 / (double)(r - 1));
-  const bool split_form = use_split(kp.kind, n, kp.d, iso, r, rows);
   SplitWork sw{};
   double* spart = nullptr;
   int64_t snblk = 0;

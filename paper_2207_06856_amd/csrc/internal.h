@@ -376,12 +376,15 @@ constexpr int kMaxRank = 128;
 // Pseudo-loss gradient (Sec. 5.3, Eq. approx) and training step kernels.
 // ---------------------------------------------------------------------------
 namespace grad {
-// Workspace bytes of launch() for a row range of `rows` rows, r columns.
-size_t workspace_bytes(int64_t rows, int64_t n, int kind, int d, bool ard, int r);
+// The stream's workspace for launch() over `rows` rows, r columns, and `extra`
+// bytes: with the split form's operands where the rule takes that form
+// (*split_form), without them when they do not fit.
+gp_status workspace(hipStream_t s, int64_t rows, int64_t n, int kind, int d, bool ard, int r,
+                    size_t extra, Arena* ar, bool* split_form);
 // out (device, L + 3 doubles): dL/dl.., dL/da^2, dL/ds^2, 1/2 y^T u_0 over
 // rows [i0, i1); partial sums are carved from ar.
 gp_status launch(const KParams& kp, bool ard, const float* X, int64_t n, const float* U,
-                 const float* B, int r, int64_t i0, int64_t i1, double* out, Arena& ar,
+                 const float* B, int r, int64_t i0, int64_t i1, bool split_form, double* out, Arena& ar,
                  hipStream_t s);
 }  // namespace grad
 
