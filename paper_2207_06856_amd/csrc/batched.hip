@@ -1109,16 +1109,15 @@ __global__ __launch_bounds__(256) void pc_step_kernel(const Seg* __restrict__ se
   double* L = sg.L64;
   for (int t = threadIdx.x; t < m; t += blockDim.x) lp[t] = L[(int64_t)t * n + p];
   for (int t = threadIdx.x; t < d; t += blockDim.x) {
-    const double il = 1.0 / (double)sg.ls[t];
-    inv_l[t] = il;
-    xp[t] = (double)sg.X[p * d + t] * il;
+    inv_l[t] = 1.0 / (double)sg.ls[t];
+    xp[t] = (double)sg.X[p * d + t];
   }
   __syncthreads();
   pc::Best best{-INFINITY, INT64_MAX, 0.0};
   for (int64_t i = ck.i0 + threadIdx.x; i < ck.i1; i += blockDim.x) {
     double r2 = 0.0;
     for (int t = 0; t < d; ++t) {
-      const double df = fma((double)sg.X[i * d + t], inv_l[t], -xp[t]);
+      const double df = ((double)sg.X[i * d + t] - xp[t]) * inv_l[t];  // exactly 0 at the pivot
       r2 = fma(df, df, r2);
     }
     double acc = (double)sg.a2 * kval64(sg.kind, r2);
