@@ -1045,84 +1045,94 @@ bool fused_step_fits(const Dims& dm, bool reorth, int pairs) {
   return !reorth || (pairs * dm.r <= kFusedCoef && pairs * dm.n * dm.r <= kFusedBasis);
 }
 
-// Per-column reduction over the group's row lanes of the LSE pair (m, S) or the
-// sum S, and of the sum q2: across the lanes of a wave that share a column, then
+// Per-column reduction over the group's row lanes of the LSE pair (m, S) (PAIR) and
+// of the float64 sum q (SUM): across the lanes of a wave that share a column, then
 // over the 16 waves by wave 0, whose lanes alone return the result.  Pairs are
 // merged by the largest m first (one exponential each), not one by one: merging 16
 // pairs in a row in all 16 waves took a third of the step.
 struct FusedLds {
-  float m[16][kMaxR], s[16][kMaxR], q[16][kMaxR];
+  float m[16][kMaxR], s[16][kMaxR];
+  double q[16][kMaxR];
 };
-template <bool LSE>
 __device__ __forceinline__ void fused_rescale(float& S, float m, float M) {
-  if (LSE && m != -INFINITY) S *= __expf(m - M);     // S of an empty pair is 0 or NaN
+  if (m != -INFINITY) S *= __expf(m - M);            // S of an empty pair is 0 or NaN
 }
-template <bool LSE>
-__device__ __forceinline__ void fused_reduce(float& m, float& S, float& q2, int rp2, FusedLds& sm) {
+template <bool PAIR, bool SUM>
+__device__ __forceinline__ void fused_reduce(float& m, float& S, double& q, int rp2, FusedLds& sm) {
   auto across = [&] {
-    if (LSE) {
+    if (PAIR) {
       float M = m;
       for (int o = 32; o >= rp2; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
-      fused_rescale<LSE>(S, m, M);
+      fused_rescale(S, m, M);
       m = M;
     }
     for (int o = 32; o >= rp2; o >>= 1) {
-      S += __shfl_xor(S, o, 64);
-      q2 += __shfl_xor(q2, o, 64);
+      if (PAIR) S += __shfl_xor(S, o, 64);
+      if (SUM) q += __shfl_xor(q, o, 64);
     }
   };
   across();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   __syncthreads();
   if (lane < rp2) {
-    sm.m[wave][lane] = m;
-    sm.s[wave][lane] = S;
-    sm.q[wave][lane] = q2;
+    if (PAIR) {
+      sm.m[wave][lane] = m;
+      sm.s[wave][lane] = S;
+    }
+    if (SUM) sm.q[wave][lane] = q;
   }
   __syncthreads();
   if (wave != 0) return;
   const int c = lane % rp2, step = 64 / rp2;
-  m = -INFINITY;
-  if (LSE)
+  if (PAIR) {
+    m = -INFINITY;
+    S = 0.0f;
     for (int w = lane / rp2; w < 16; w += step) m = fmaxf(m, sm.m[w][c]);
-  S = q2 = 0.0f;
+  }
+  if (SUM) q = 0.0;
   for (int w = lane / rp2; w < 16; w += step) {
-    float t = sm.s[w][c];
-    fused_rescale<LSE>(t, sm.m[w][c], m);
-    S += t;
-    q2 += sm.q[w][c];
+    if (PAIR) {
+      float t = sm.s[w][c];
+      fused_rescale(t, sm.m[w][c], m);
+      S += t;
+    }
+    if (SUM) q += sm.q[w][c];
   }
   across();
 }
-// The pair or sum of KE products u_k v_k (in[k]).
-template <bool LSE, int KE>
-__device__ __forceinline__ void fused_terms(const float (&u)[KE], const float (&v)[KE],
-                                            const bool (&in)[KE], float& m, float& S) {
+// The pair of KE products u_k v_k (in[k]).
+template <int KE>
+__device__ __forceinline__ void fused_pair(const float (&u)[KE], const float (&v)[KE],
+                                           const bool (&in)[KE], float& m, float& S) {
   m = -INFINITY;
   S = 0.0f;
-  if (LSE) {
-    float y[KE];
-    bool bad = false;
+  float y[KE];
+  bool bad = false;
 #pragma unroll
-    for (int k = 0; k < KE; ++k) {
-      const bool some = in[k] && u[k] != 0.0f && v[k] != 0.0f;
-      y[k] = some ? __logf(fabsf(u[k])) + __logf(fabsf(v[k])) : -INFINITY;
-      bad |= some && !isfinite(y[k]);
-      m = fmaxf(m, y[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < KE; ++k)
-      if (y[k] != -INFINITY)
-        S += ((u[k] < 0.0f) != (v[k] < 0.0f)) ? -__expf(y[k] - m) : __expf(y[k] - m);
-    if (bad) {
-      m = -INFINITY;
-      S = NAN;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < KE; ++k)
-      if (in[k]) S = fmaf(u[k], v[k], S);
+  for (int k = 0; k < KE; ++k) {
+    const bool some = in[k] && u[k] != 0.0f && v[k] != 0.0f;
+    y[k] = some ? __logf(fabsf(u[k])) + __logf(fabsf(v[k])) : -INFINITY;
+    bad |= some && !isfinite(y[k]);
+    m = fmaxf(m, y[k]);
   }
+#pragma unroll
+  for (int k = 0; k < KE; ++k)
+    if (y[k] != -INFINITY)
+      S += ((u[k] < 0.0f) != (v[k] < 0.0f)) ? -__expf(y[k] - m) : __expf(y[k] - m);
+  if (bad) {
+    m = -INFINITY;
+    S = NAN;
+  }
+}
+// Their sum, products and sums in float64.
+template <int KE>
+__device__ __forceinline__ double fused_dot(const float (&u)[KE], const float (&v)[KE],
+                                            const bool (&in)[KE]) {
+  double q = 0.0;
+#pragma unroll
+  for (int k = 0; k < KE; ++k)
+    if (in[k]) q = fma((double)u[k], (double)v[k], q);
+  return q;
 }
 
 template <bool LSE, int KE>
@@ -1179,9 +1189,13 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
   }
 #pragma unroll
   for (int k = 0; k < KE; ++k) qv[k] = in[k] ? fmaf(s2, dv[k], a2 * qv[k]) : 0.0f;
-  float m, S, q2 = 0.0f;
-  fused_terms<LSE, KE>(dv, qv, in, m, S);
-  fused_reduce<LSE>(m, S, q2, rp2, red);
+  float m, S;
+  double dq = 0.0;
+  if (LSE)
+    fused_pair<KE>(dv, qv, in, m, S);
+  else
+    dq = fused_dot<KE>(dv, qv, in);
+  fused_reduce<LSE, !LSE>(m, S, dq, rp2, red);
   if (wave == 0) {
     const int kk = st->k + 1;
     int act = 0;
@@ -1195,8 +1209,8 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
           ok = isfinite(l);
           if (ok) alpha = exp(st->lg[lane] - l);
         } else {
-          ok = isfinite((double)S) && S > 0.0f;
-          if (ok) alpha = st->lg[lane] / (double)S;
+          ok = isfinite(dq) && dq > 0.0;
+          if (ok) alpha = st->lg[lane] / dq;
         }
         if (!ok || !isfinite(alpha)) {
           alpha = 0.0;
@@ -1302,18 +1316,12 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
   }
 
   // ||r||, gamma, beta, convergence (z = r)
-  q2 = 0.0f;
 #pragma unroll
-  for (int k = 0; k < KE; ++k) {
-    if (in[k]) {
-      if (act) rr[at[k]] = rv[k];
-      q2 = fmaf(rv[k], rv[k], q2);
-    }
-  }
-  if (LSE) fused_terms<LSE, KE>(rv, rv, in, m, S);
-  fused_reduce<LSE>(m, S, q2, rp2, red);
-  const float rr2 = q2;
-  if (!LSE) S = rr2;
+  for (int k = 0; k < KE; ++k)
+    if (in[k] && act) rr[at[k]] = rv[k];
+  double rr2 = fused_dot<KE>(rv, rv, in);
+  if (LSE) fused_pair<KE>(rv, rv, in, m, S);
+  fused_reduce<LSE, true>(m, S, rr2, rp2, red);
   const int slot = st->nbasis;
   __syncthreads();
   if (wave == 0) {
@@ -1326,13 +1334,13 @@ __global__ __launch_bounds__(kFusedThreads) void fused_step_kernel(
         g = lse_value(m, S);
         ok = isfinite(g);
       } else {
-        g = (double)S;
+        g = rr2;
         ok = isfinite(g) && g > 0.0;
       }
       on = st->active[lane];
       float relc = st->rel[lane];
       if (on) {
-        const double rel = sqrt((double)rr2 / st->bnorm2[lane]);
+        const double rel = sqrt(rr2 / st->bnorm2[lane]);
         relc = (float)rel;
         st->rel[lane] = relc;
         if (kk >= min_iter && rel <= tol) {
