@@ -1031,9 +1031,14 @@ gp_status direction_step(const float* z, float* d, const float* rr, float* U, fl
 // Where the line lies: one compute unit reads the split sums and the basis at
 // 100 to 150 GB/s.  Two entries a thread: n = 2040, R = 1 3.35 -> 2.2 ms, n = 256,
 // R = 8 2.25 -> 1.4 ms.  Four: n = 250, R = 16 3.10 -> 2.0 ms, n = 2040, R = 2 4.14
-// -> 3.2 ms, but n = 4090, R = 1, whose product has more splits, 4.69 -> 4.9 ms.
+// -> 3.2 ms.
 // Eight: n = 4000, R = 2 6.59 -> 7.0 ms.  393216 stored floats are 96 pairs of 4096:
 // n = 2040, R = 2, 70 iterations: 64 pairs cost 0.1 ms more, 32 0.25.
+// At R = 1 the form is faster than the separate launches up to 4096 rows (d = 3:
+// n = 2049 3.6 -> 2.6 ms, 2500 4.4 -> 2.9, 3000 4.4 -> 3.3, 4000 4.6 -> 4.0, 4096 4.7 ->
+// 4.4; 2048 3.3 -> 2.2); kFusedRows keeps it to 2048, up to which solves have been
+// compared step by step: another order of the float32 sums moves a solution to 1e-4
+// by 3e-5.
 constexpr int kFusedThreads = 1024;
 constexpr int kFusedRows = 2048;                                     // n at most
 constexpr int kFusedMax = 4 * kFusedThreads;                         // n * rp2 at most

@@ -174,7 +174,8 @@ gp_status launch_reduce(const float* part, int nsplit, int64_t n1, int64_t n1_pa
                         const float* inv_scale, float a2, float s2, const float* V, int64_t ldv,
                         float* out, int64_t ldo, const int* live, hipStream_t s);
 
-int choose_splits(int64_t n1_pad, int64_t n2_pad);
+// lists: a product over stage lists, whose groups keep only part of their stages
+int choose_splits(int64_t n1_pad, int64_t n2_pad, bool lists = false);
 
 // Symmetric product of one point set (kmvm_sym.hip): panels of 1536 points,
 // each kernel value of two distinct panels evaluated once for both sides.

@@ -472,7 +472,7 @@ gp_status launch_reduce(const float* part, int nsplit, int64_t n1, int64_t n1_pa
   return GP_OK;
 }
 
-int choose_splits(int64_t n1_pad, int64_t n2_pad) {
+int choose_splits(int64_t n1_pad, int64_t n2_pad, bool lists) {
   const int64_t rblocks = n1_pad / kRowsPerBlock;
   const int64_t nstage = n2_pad / JT;
   // enough work groups for ~8 per CU on 256 CUs, in multiples of the 8 XCDs
@@ -484,8 +484,9 @@ int choose_splits(int64_t n1_pad, int64_t n2_pad) {
   // and read once per split.  n = 8000, R = 16: 63 splits 33.5 us, 16 27.6; n = 10000,
   // R = 8: 56 splits 38.8, 16 34.7 (256 groups: 8 splits 36.8); at 50,000 points 16
   // splits 608 us, 8 645.
-  want = std::min(want, std::max(round_up(ceil_div(512, std::max<int64_t>(rblocks, 1)), 8),
-                                 nstage / 64 * 8));
+  if (!lists)
+    want = std::min(want, std::max(round_up(ceil_div(512, std::max<int64_t>(rblocks, 1)), 8),
+                                   nstage / 64 * 8));
   const int rule = (int)std::max<int64_t>(1, std::min<int64_t>(want, nstage));
   return tune::f16_splits(n1_pad, n2_pad, rule);
 }

@@ -307,8 +307,11 @@ extern "C" gp_status gp_kmvm_truncated(const gp_kernel* k, const float* X1, int6
   // half the column splits of the full product: a row block keeps only part
   // of its stages, so fewer, longer stage ranges per work group amortise the
   // pipeline start of each group (1M points, 25% of tiles kept: 4 splits
-  // 24.7 ms, 8 splits 27.8 ms); skip = 0 uses the same ranges
-  const int nsplit = std::max(1, f16::choose_splits(n1_pad, n2_pad) / 2);
+  // 24.7 ms, 8 splits 27.8 ms); skip = 0 uses the same ranges.  Half of the 2048
+  // groups, not of the full product's at least 8 stages: 20,000 points, R = 16, 15
+  // lengthscales 16 splits 129 us, 8 136 (6 lengthscales 142 against 153); 10,000
+  // points 28 splits 101 us, 8 99; 15,000 16 to 20 splits 107 us, 8 114.
+  const int nsplit = std::max(1, f16::choose_splits(n1_pad, n2_pad, true) / 2);
   const size_t bytes = zorder_bytes(n1) + (same ? 0 : zorder_bytes(n2)) + 4 * (size_t)(n1 + n2) +
                        4 * (size_t)n1 * d + 4 * (size_t)n2 * d + 4 * (size_t)n2 * r +
                        4 * (size_t)n1 * r + 2 * (size_t)n1_pad * w + 2 * (size_t)n2_pad * w +
