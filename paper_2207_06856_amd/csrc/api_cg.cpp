@@ -105,7 +105,7 @@ size_t plan_bytes(Plan& p, bool want_history) {
   }
   add(4 * 64);                                 // column maxima of d
   if (p.o.true_res_every >= 0) add(8 * (size_t)p.nsplit64 * n * r);
-  if (p.t64_split && !p.f32_split) b += split::operand_bytes(p.t64p, p.kp.d);
+  if (p.t64_split) b += split::operand_bytes(p.t64p, p.kp.d);
   add(4 * cg::kMaxBlocks * cg::kMaxR);
   add(4 * cg::kMaxBlocks * cg::kMaxR);
   add(8 * cg::kMaxBlocks * cg::kMaxR);
@@ -151,12 +151,7 @@ void plan_carve(Plan& p, Arena& a, bool want_history) {
   }
   p.colmax = a.take<uint32_t>(64);
   p.part64 = p.o.true_res_every >= 0 ? a.take<double>((size_t)p.nsplit64 * n * r) : nullptr;
-  if (p.t64_split) {
-    if (p.f32_split)
-      p.t64p = p.f32p;                  // the product's operands serve both
-    else if (split::carve(p.t64p, p.kp.d, a) != GP_OK)
-      return;
-  }
+  if (p.t64_split && split::carve(p.t64p, p.kp.d, a) != GP_OK) return;
   p.pm = a.take<float>(cg::kMaxBlocks * cg::kMaxR);
   p.ps = a.take<float>(cg::kMaxBlocks * cg::kMaxR);
   p.pd = a.take<double>(cg::kMaxBlocks * cg::kMaxR);
@@ -249,7 +244,7 @@ gp_status iteration(Plan& p, int it, hipStream_t s) {
 
 gp_status true_residual(Plan& p, hipStream_t s) {
   if (p.t64_split) {
-    if (!p.t64_ready && !p.f32_split)
+    if (!p.t64_ready)
       GP_TRY(split::prepare(p.t64p, p.kp, p.X, p.n, p.X, p.n, s));
     p.t64_ready = true;
     GP_TRY(split::partial64(p.t64p, p.kp, p.X, p.n, p.U, p.r, p.part64, p.nsplit64, s));
@@ -335,11 +330,11 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
   p.nsplit16 = f16::choose_splits(p.n_pad, p.n_pad);
   p.nsplit32 = valu::choose_splits(n, n, d);
   p.f32_split = !p.fp16 && split::use(p.kp.kind, n, n, d, r);
-  if (p.f32_split) p.f32p = split::plan(n, n, d, r, true, 64);
+  if (p.f32_split) p.f32p = split::plan(n, n, d, r, true, 64, split::kSplitMaxRadius);
   p.nsplit64 = valu::choose_splits64(n, n, d);
   p.t64_split = p.o.true_res_every >= 0 && split::use64(p.kp.kind, n, d);
   if (p.t64_split) {
-    p.t64p = p.f32_split ? p.f32p : split::plan(n, n, d, r, true, 64);
+    p.t64p = split::plan(n, n, d, r, true, 64, split::kSplitMaxRadius, true);
     p.nsplit64 = split::choose_splits64(p.t64p, r);
   }
   const bool want_history = stats && stats->history;

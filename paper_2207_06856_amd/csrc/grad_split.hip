@@ -423,7 +423,7 @@ bool use_split(int kind, int64_t n, int d, bool iso, int r, int64_t rows) {
 
 SplitWork split_plan(int64_t n, int d, bool iso) {
   SplitWork w{};
-  w.p = split::plan(n, n, d, 1, true, 1);
+  w.p = split::plan(n, n, d, 1, true, 1, split::kSplitMaxRadius);
   const int64_t rb = w.p.n1_pad / (64 * row_subtiles(w.p.kc, width_of(d, iso)));
   w.rblocks = rb;
   // about 3000 work groups of at least two stages on average

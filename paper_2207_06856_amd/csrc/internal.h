@@ -252,11 +252,21 @@ struct Info {
   double centre[kMaxDim];
 };
 __host__ __device__ constexpr int operand_chunks(int d) { return 1 + (5 * d + 6 + 31) / 32; }
+// fine operands: chunks of the exact second sum, and all of them
+__host__ __device__ constexpr int f_chunks(int d) { return (2 * d + 31) / 32; }
+__host__ __device__ constexpr int fine_chunks(int d) { return f_chunks(d) + operand_chunks(d); }
+// f_chunks from the width: d <= 16 have five chunks at most
+__host__ __device__ constexpr int f_chunks_of(int kc) { return kc <= 5 ? 1 : 2; }
+static_assert(fine_chunks(16) == 5 && fine_chunks(17) == 6, "f_chunks_of");
 // 16-row subtiles per wave (their operands stay in registers)
-__host__ __device__ constexpr int subtiles(int kc) { return kc <= 3 ? 4 : 2; }
+__host__ __device__ constexpr int subtiles(int kc, bool fine = false) {
+  return kc <= (fine ? 4 : 3) ? 4 : 2;
+}
 struct Plan {
   int kc, rp, nsplit, groups1, groups2;
   bool same;                           // X1 and X2 are one set
+  bool fine;                           // fine operands (split_tile.h)
+  float radius;                        // of the widest box
   int64_t n1_pad, n2_pad;
   _Float16 *Xr, *Xc;
   Info* info;
@@ -265,7 +275,8 @@ struct Plan {
 // whether a float32 product of these sizes takes this form (the inputs' range
 // is checked on the device)
 bool use(int kind, int64_t n1, int64_t n2, int d, int r);
-Plan plan(int64_t n1, int64_t n2, int d, int r, bool same, int most_splits);
+Plan plan(int64_t n1, int64_t n2, int d, int r, bool same, int most_splits, float radius,
+          bool fine = false);
 size_t operand_bytes(const Plan& p, int d);
 size_t part_bytes(const Plan& p);
 gp_status carve(Plan& p, int d, Arena& ar);

@@ -74,7 +74,8 @@ __global__ __launch_bounds__(256) void box_kernel(const float* __restrict__ X1, 
 // One group: the box's centre, the unit u and the exponent scale; ok = 0 when
 // the inputs are not finite or the box is too wide for this form.
 __global__ __launch_bounds__(256) void info_kernel(const float* __restrict__ part, int groups,
-                                                   KParams kp, double arg, Info* __restrict__ o) {
+                                                   KParams kp, double arg, float radius,
+                                                   Info* __restrict__ o) {
   __shared__ float lo[4][kMaxDim], hi[4][kMaxDim];
   __shared__ double half2[kMaxDim];
   const int m = threadIdx.x & 63, q = threadIdx.x >> 6, d = kp.d;
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(256) void info_kernel(const float* __restrict__ par
   if (threadIdx.x == 0) {
     double r2 = 0.0;
     for (int k = 0; k < d; ++k) r2 += half2[k];
-    const bool ok = r2 <= (double)kSplitMaxRadius * kSplitMaxRadius;   // false for NaN
+    const bool ok = r2 <= (double)radius * radius;   // false for NaN
     // |arg| u^2 is a power of two >= |arg| (R / 2000)^2: the exponent argument
     // is then an exact multiple of r^2 / u^2
     int e = -100;
@@ -195,6 +196,99 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ X, 
             const int w = t - 5 * d;
             v0 = w < 3 ? 1.0f : (float)gp[p][w - 3];
             v1 = w < 3 ? (float)gp[p][w] : 1.0f;
+          }
+        }
+      }
+      o0[k] = (_Float16)v0;
+      o1[k] = (_Float16)v1;
+    }
+    if (out0) *reinterpret_cast<h8*>(out0 + i * width + c * 8) = o0;
+    if (out1) *reinterpret_cast<h8*>(out1 + i * width + c * 8) = o1;
+  }
+}
+
+// The same in the fine form.
+__global__ __launch_bounds__(256) void prep_fine_kernel(const float* __restrict__ X, int64_t n,
+                                                        int64_t n_pad, KParams kp, int width,
+                                                   const Info* __restrict__ info,
+                                                   _Float16* __restrict__ out0,
+                                                   _Float16* __restrict__ out1) {
+  if (!info->ok) return;
+  __shared__ float q[kPrepPoints][kSplitMaxDim], f[kPrepPoints][kSplitMaxDim];
+  __shared__ float E[kPrepPoints][kSplitMaxDim];
+  __shared__ float nq[kPrepPoints][2];
+  __shared__ _Float16 hp[kPrepPoints][3];
+  const int d = kp.d;
+  const int64_t i0 = (int64_t)blockIdx.x * kPrepPoints;
+  const double inv_u = info->inv_u;
+  for (int e = threadIdx.x; e < kPrepPoints * d; e += 256) {
+    const int p = e / d, m = e - p * d;
+    double a = 0.0;
+    if (i0 + p < n) a = ((double)X[(i0 + p) * d + m] - info->centre[m]) / (double)kp.ls[m] * inv_u;
+    const double qi = rint(a), fi = rint((a - qi) * 1024.0) / 1024.0;
+    q[p][m] = (float)qi;
+    f[p][m] = (float)fi;
+    E[p][m] = (float)(_Float16)(float)((a - qi - fi) * 2048.0);
+  }
+  __syncthreads();
+  if (threadIdx.x < kPrepPoints) {
+    const int p = threadIdx.x;
+    int N = 0;
+    double G = 0.0, H = 0.0;
+    for (int m = 0; m < d; ++m) {
+      const double qi = (double)q[p][m], fi = (double)f[p][m], ei = (double)E[p][m] / 2048.0;
+      N += (int)q[p][m] * (int)q[p][m];
+      G += 2.0 * qi * fi;
+      H += 2.0 * qi * ei + fi * (fi + 2.0 * ei);
+    }
+    const double Gi = rint(G);
+    H += G - Gi;
+    N += (int)Gi;                                // >= -|f|^2: |q + f|^2 is not negative
+    nq[p][0] = (float)(N & 2047);
+    nq[p][1] = (float)(N >> 11);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const _Float16 h = (_Float16)(float)H;
+      hp[p][k] = h;
+      H -= (double)(float)h;
+    }
+  }
+  __syncthreads();
+  const int chunks = width / 8, rest = 32 * (1 + f_chunks(d));
+  for (int e = threadIdx.x; e < kPrepPoints * chunks; e += 256) {
+    const int p = e / chunks, c = e - p * chunks;
+    const int64_t i = i0 + p;
+    if (i >= n_pad) continue;
+    h8 o0, o1;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int s = c * 8 + k;
+      float v0 = 0.0f, v1 = 0.0f;
+      if (i < n) {
+        if (s < d) {
+          v0 = q[p][s];
+          v1 = -2.0f * v0;
+        } else if (s < d + 4) {
+          const int w = s - d;
+          v0 = w == 0 ? 1.0f : w == 1 ? 2048.0f : nq[p][w - 2];
+          v1 = w == 2 ? 1.0f : w == 3 ? 2048.0f : nq[p][w];
+        } else if (s >= 32 && s < rest) {
+          const int t = s - 32, m = t < d ? t : t - d;
+          if (t < 2 * d) {
+            v0 = t < d ? q[p][m] : f[p][m];
+            v1 = -2.0f * (t < d ? f[p][m] : q[p][m]);
+          }
+        } else if (s >= rest) {
+          const int t = s - rest;
+          if (t < 5 * d) {
+            const int b = t / d, m = t - b * d;
+            const float q2 = q[p][m] / 2048.0f, f5 = f[p][m] / 32.0f, e6 = E[p][m] / 64.0f;
+            v0 = b == 0 ? q2 : b == 1 ? E[p][m] : b == 2 ? f[p][m] : b == 3 ? f5 : e6;
+            v1 = -2.0f * (b == 0 ? E[p][m] : b == 1 ? q2 : b == 2 ? f[p][m] : b == 3 ? e6 : f5);
+          } else if (t < 5 * d + 6) {
+            const int w = t - 5 * d;
+            v0 = w < 3 ? 1.0f : (float)hp[p][w - 3];
+            v1 = w < 3 ? (float)hp[p][w] : 1.0f;
           }
         }
       }
@@ -514,11 +608,14 @@ static int choose_splits(int kc, int rb, int64_t rblocks, int64_t nstage, int mo
   return 1;
 }
 
-Plan plan(int64_t n1, int64_t n2, int d, int r, bool same, int most_splits) {
+Plan plan(int64_t n1, int64_t n2, int d, int r, bool same, int most_splits, float radius,
+          bool fine) {
   Plan p{};
-  p.kc = operand_chunks(d);
+  p.kc = fine ? fine_chunks(d) : operand_chunks(d);
+  p.fine = fine;
+  p.radius = radius;
   p.same = same;
-  const int rows = 64 * subtiles(p.kc);
+  const int rows = 64 * subtiles(p.kc, fine);
   p.n1_pad = round_up(n1, rows);
   p.n2_pad = round_up(n2, JT);
   if (same) p.n1_pad = p.n2_pad = round_up(n1, std::max(rows, JT));
@@ -559,14 +656,15 @@ gp_status prepare(const Plan& p, const KParams& kp, const float* X1, int64_t n1,
   box_kernel<<<(unsigned)(p.groups1 + p.groups2), 256, 0, s>>>(X1, n1, X2, n2, kp.d, p.groups1,
                                                                p.box);
   GP_HIP(hipGetLastError());
-  info_kernel<<<1, 256, 0, s>>>(p.box, p.groups1 + p.groups2, kp, arg, p.info);
+  info_kernel<<<1, 256, 0, s>>>(p.box, p.groups1 + p.groups2, kp, arg, p.radius, p.info);
   GP_HIP(hipGetLastError());
   const int w = 32 * p.kc;
-  prep_kernel<<<(unsigned)ceil_div(p.n1_pad, (int64_t)kPrepPoints), 256, 0, s>>>(
+  const auto prep = p.fine ? &prep_fine_kernel : &prep_kernel;
+  prep<<<(unsigned)ceil_div(p.n1_pad, (int64_t)kPrepPoints), 256, 0, s>>>(
       X1, n1, p.n1_pad, kp, w, p.info, p.Xr, p.same ? p.Xc : nullptr);
   GP_HIP(hipGetLastError());
   if (!p.same) {
-    prep_kernel<<<(unsigned)ceil_div(p.n2_pad, (int64_t)kPrepPoints), 256, 0, s>>>(
+    prep<<<(unsigned)ceil_div(p.n2_pad, (int64_t)kPrepPoints), 256, 0, s>>>(
         X2, n2, p.n2_pad, kp, w, p.info, nullptr, p.Xc);
     GP_HIP(hipGetLastError());
   }

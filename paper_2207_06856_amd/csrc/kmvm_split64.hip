@@ -1,11 +1,14 @@
 // Float64-accumulated product on split operands (the solver's true residual):
-// the float32 entry k(x_i, x_j) from the exact integer distances of
-// split_tile.h, widened, and every product k v summed in float64 -- the sums
-// of valu_tile.h's aug64_rows with its distance MFMAs replaced.  Those take
-// T = ceil((d + 2) / 4) float64 MFMAs of 64 cycles per 16 x 16 entries, three
-// quarters of the time the sums themselves take at d = 8; KC binary16 MFMAs of
-// 16 cycles give the squared distance to well below the float32 rounding of
-// the entry.
+// the float32 entry k(x_i, x_j) from the fine distances of split_tile.h, widened,
+// and every product k v summed in float64 -- the sums of valu_tile.h's aug64_rows
+// with its distance MFMAs replaced.  Those take T = ceil((d + 2) / 4) float64 MFMAs
+// of 64 cycles per 16 x 16 entries, three quarters of the time the sums themselves
+// take at d = 8; KC binary16 MFMAs of 16 cycles and two additions give r^2 with the
+// two roundings that the float64 distance takes as a float32 argument, and the
+// diagonal exactly: the residual's error is the float64 distances' to 5% (n = 8400,
+// d = 2 to 12, boxes and clusters of radius 4 to 31, all three kernels; the coarser
+// operands of the float32 product doubled it at d = 12 and lost the last digits of
+// residuals near 1e-8 on wide boxes).
 //
 // With the entries' lane layout (row l16, columns 4 g + v) product MFMA v takes
 // the columns {4 g + v}: A is the entry, B the right-hand side l16 of that
@@ -14,6 +17,7 @@
 // float64 FMAs instead, R of them per entry rather than 16.
 
 #include <algorithm>
+#include <type_traits>
 
 #include "split_tile.h"
 
@@ -30,7 +34,7 @@ __global__ __launch_bounds__(256) void f64_kernel(const _Float16* __restrict__ X
                                                   int64_t n1, int64_t n2, double* __restrict__ part,
                                                   int nsplit, const Info* __restrict__ info) {
   if (!info->ok) return;
-  constexpr int NSUB = subtiles(KC);
+  constexpr int NSUB = subtiles(KC, true);
   constexpr int KP = 32 * KC, XS = KP + 8;
   constexpr int RW = RT ? RT : 16;             // right-hand sides staged
   constexpr int XPT = JT * KP / 8 / 256, VPT = (JT * RW + 255) / 256;
@@ -98,40 +102,53 @@ __global__ __launch_bounds__(256) void f64_kernel(const _Float16* __restrict__ X
     if (more) gload(st + 1);
     const _Float16* X = sX[buf];
     const double* Vs = sV[buf];
+    const int off = __builtin_amdgcn_readfirstlane((int)(row0 - st * JT));   // wave-uniform
+    auto columns = [&](auto diag) {
+      constexpr bool DIAG = decltype(diag)::value;
 #pragma unroll 1
-    for (int jb = 0; jb < JT / 16; ++jb) {
-      h8 a[KC];
+      for (int jb = 0; jb < JT / 16; ++jb) {
+        h8 a[KC];
 #pragma unroll
-      for (int kc = 0; kc < KC; ++kc)
-        a[kc] = *reinterpret_cast<const h8*>(X + (jb * 16 + l16) * XS + kc * 32 + g * 8);
-      float k[NSUB][4];
+        for (int kc = 0; kc < KC; ++kc)
+          a[kc] = *reinterpret_cast<const h8*>(X + (jb * 16 + l16) * XS + kc * 32 + g * 8);
+        float k[NSUB][4];
 #pragma unroll
-      for (int q = 0; q < NSUB; ++q) {
-        const f4 s = sqdist<KC>(a, bi[q]);
+        for (int q = 0; q < NSUB; ++q) {
+          f4 s = sqdist_fine<KC>(a, bi[q]);
+          // the diagonal's distance is 0, not the rounding of T (a Matern value near
+          // t = 0 rounds to 3e-8 of 1)
+          if (DIAG && off == (jb - q) * 16)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) k[q][v] = kval<KIND>(s[v], cs);
-      }
+            for (int v = 0; v < 4; ++v) s[v] = l16 == 4 * g + v ? 0.0f : s[v];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const double* vr = Vs + (jb * 16 + 4 * g + v) * RW;
-        if constexpr (RT == 0) {
-          const double b = vr[l16];
+          for (int v = 0; v < 4; ++v) k[q][v] = kval<KIND>(s[v], cs);
+        }
 #pragma unroll
-          for (int q = 0; q < NSUB; ++q)
-            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)k[q][v], b, acc[q], 0, 0, 0);
-        } else {
-          double b[RT ? RT : 1];
+        for (int v = 0; v < 4; ++v) {
+          const double* vr = Vs + (jb * 16 + 4 * g + v) * RW;
+          if constexpr (RT == 0) {
+            const double b = vr[l16];
 #pragma unroll
-          for (int c = 0; c < RT; ++c) b[c] = vr[c];
+            for (int q = 0; q < NSUB; ++q)
+              acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)k[q][v], b, acc[q], 0, 0, 0);
+          } else {
+            double b[RT ? RT : 1];
 #pragma unroll
-          for (int q = 0; q < NSUB; ++q) {
-            const double kd = (double)k[q][v];
+            for (int c = 0; c < RT; ++c) b[c] = vr[c];
 #pragma unroll
-            for (int c = 0; c < RT; ++c) sum[q][c] = fma(kd, b[c], sum[q][c]);
+            for (int q = 0; q < NSUB; ++q) {
+              const double kd = (double)k[q][v];
+#pragma unroll
+              for (int c = 0; c < RT; ++c) sum[q][c] = fma(kd, b[c], sum[q][c]);
+            }
           }
         }
       }
-    }
+    };
+    if (off > -JT && off < JT)                   // a stage that holds some of the wave's rows
+      columns(std::true_type{});
+    else
+      columns(std::false_type{});
     if (more) lstore(buf ^ 1);
     __syncthreads();
   }
@@ -162,11 +179,12 @@ typedef void (*F64Fn)(const _Float16*, const _Float16*, const float*, int, int, 
 template <int KIND, int RT>
 static F64Fn f64_fn(int kc) {
   switch (kc) {
-    case 2: return &f64_kernel<KIND, 2, RT>;
     case 3: return &f64_kernel<KIND, 3, RT>;
     case 4: return &f64_kernel<KIND, 4, RT>;
     case 5: return &f64_kernel<KIND, 5, RT>;
     case 6: return &f64_kernel<KIND, 6, RT>;
+    case 7: return &f64_kernel<KIND, 7, RT>;
+    case 8: return &f64_kernel<KIND, 8, RT>;
   }
   return nullptr;
 }
@@ -192,7 +210,7 @@ gp_status partial64(const Plan& p, const KParams& kp, const float* X, int64_t n,
                    : kp.kind == GP_KERNEL_MATERN32 ? f64_fn<GP_KERNEL_MATERN32>(p.kc, rt)
                                                    : nullptr;
   if (!fn) return set_error(GP_ERR_ARG, "internal: no split product for this kernel");
-  const int64_t blocks = p.n1_pad / (64 * subtiles(p.kc)) * nsplit;
+  const int64_t blocks = p.n1_pad / (64 * subtiles(p.kc, true)) * nsplit;
   for (int c0 = 0; c0 < r; c0 += step) {
     fn<<<(unsigned)blocks, 256, 0, s>>>(p.Xr, p.Xc, V, r, c0, n, n, part, nsplit, p.info);
     GP_HIP(hipGetLastError());
@@ -205,7 +223,7 @@ int choose_splits64(const Plan& p, int r) {
   const int rt = fma_rhs(r), rw = rt ? rt : 16;
   const int lds = 2 * (2 * JT * (32 * p.kc + 8) + 8 * JT * rw);
   const int64_t resident = 256 * std::max(1, std::min(3, 160 * 1024 / (lds + 512)));
-  const int64_t rblocks = p.n1_pad / (64 * subtiles(p.kc));
+  const int64_t rblocks = p.n1_pad / (64 * subtiles(p.kc, true));
   const int64_t smax = std::max<int64_t>(1, std::min<int64_t>(64, p.n2_pad / JT / 4));
   auto cost = [&](int64_t sp) { return (double)ceil_div(rblocks * sp, resident) / (double)sp; };
   double best = 1e300;

@@ -12,11 +12,13 @@
 // |a_i|^2 + |a_j|^2 - 2 a_i.a_j, which is what keeps a plain float32 (or
 // split) expansion from the accuracy of coordinate differences.  The bracket is
 // smaller by |f| / |q| ~ 2^-11, and the following MFMAs add it from f in two
-// binary16 parts and g = 2 q.f + |f|^2 in three; their float32 roundings are
-// about 2^-11 u^2, i.e. R^2 2^-32 at most in r^2.  Coordinate differences of
-// the float32 x / l carry 2 r |x / l| 2^-25, which is more than that at r ~ 1
-// up to R = kSplitMaxRadius, the limit of this form.  u is chosen so that the
-// scale from r^2 / u^2 to the exponent's argument is a power of two: the
+// binary16 parts and g = 2 q.f + |f|^2 in three.  Every one of them rounds at the
+// size of the sum so far, and q.f at up to 2^12 before it cancels: an entry's r^2
+// carries a few 2^-24 of itself and 1.2e-10 R^2.  Coordinate differences of the
+// float32 x / l carry 2 r |x / l| 2^-25, and their float32 sum d / 2 roundings, which
+// is more on ordinary points; on boxes wide enough to leave little but the
+// diagonal of K it is less, hence the radius limits of the callers.  u is chosen so
+// that the scale from r^2 / u^2 to the exponent's argument is a power of two: the
 // argument takes no further rounding, and no constant's.
 // Not for Matern-1/2, whose value falls linearly in r at r = 0, where an
 // absolute error of r^2 would be magnified.
@@ -27,6 +29,25 @@
 //   d .. d+3    1, 2048, N0, N1     N0, N1, 1, 2048
 //   32 + ..     q, q, f1, f2, f1    -2 f1, -2 f2, -2 q, -2 q, -2 f1     (d each)
 //   then        1, 1, 1, g1..g3     g1..g3, 1, 1, 1
+//
+// The fine form, for the true residual, whose distances are float64 otherwise:
+// a / u = q + f + e, f a multiple of 2^-10 and e = E / 2048, E in binary16 (a to 2^-24 u,
+// 2^-35 R), with the expanded sums
+//   I = -2 q_i.q_j + N_i + N_j,      N = |q|^2 + rint(2 q.f),
+//   F = -2 q_i.f_j - 2 f_i.q_j,
+//   T = -2 q_i.e_j - 2 e_i.q_j - 2 f_i.f_j - 2 f_i.e_j - 2 e_i.f_j + h_i + h_j,
+//       h = 2 q.f - rint(2 q.f) + 2 q.e + |f|^2 + 2 f.e
+// (|e_i - e_j|^2 < d 2^-20 is left out).  F's terms are multiples of 2^-9 whose
+// partial sums stay below 2^15, so that its MFMAs are exact like I's, and I + F is
+// exact for close points.  T is some 2^4 at most before it cancels, with h in three
+// binary16 parts: its roundings are about 2^-19 u^2, R^2 2^-40 in r^2; I + F and
+// (I + F) + T are rounded once each, as the float64 distance is when it becomes a
+// float32 and is scaled to the exponent's argument.  One more MFMA and two additions:
+//   slot        side 0                           side 1
+//   first chunk as above, with this N
+//   F           q, f                             -2 f, -2 q                      (d each)
+//   T           q / 2^11, E, f, f / 2^5, E / 2^6 -2 E, -q / 2^10, -2 f, -E / 2^5, -f / 2^4
+//   then        1, 1, 1, h1..h3                  h1..h3, 1, 1, 1
 #pragma once
 
 #include "fused_tile.h"
@@ -46,6 +67,21 @@ __device__ __forceinline__ f4 sqdist(const h8 (&a)[KC], const h8 (&b)[KC]) {
   f4 s = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int kc = 0; kc < KC; ++kc) s = f16::mfma32<_Float16>(a[kc], b[kc], s);
+  return s;
+}
+
+// The same from fine operands.
+template <int KC>
+__device__ __forceinline__ f4 sqdist_fine(const h8 (&a)[KC], const h8 (&b)[KC]) {
+  constexpr int F = 1 + f_chunks_of(KC);         // the first chunk of T
+  const f4 z = f4{0.f, 0.f, 0.f, 0.f};
+  f4 s = f16::mfma32<_Float16>(a[0], b[0], z), f = z, t = z;
+#pragma unroll
+  for (int kc = 1; kc < F; ++kc) f = f16::mfma32<_Float16>(a[kc], b[kc], f);
+#pragma unroll
+  for (int kc = F; kc < KC; ++kc) t = f16::mfma32<_Float16>(a[kc], b[kc], t);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) s[v] = (s[v] + f[v]) + t[v];
   return s;
 }
 
