@@ -3,11 +3,14 @@
 // kmvm_valu.hip, with both contractions moved to 16-bit MFMAs that lose nothing:
 //   * the squared distances come from exact integer products plus a small
 //     remainder (split_tile.h);
-//   * the entry k and the right-hand side v are cut into three bfloat16 parts
-//     of 8 bits each (by truncation, so the parts hold all 24 bits and have
-//     the entry's sign), and k v = k1 v1 + k1 v2 + k2 v1 + k1 v3 + k2 v2 +
-//     k3 v1 up to 2^-24; bfloat16 has float32's range, so no scaling is needed
-//     and an entry of any size keeps its 24 bits.
+//   * the entry k and the right-hand side v are cut into three bfloat16 parts of 8
+//     bits each that hold all 24 bits, k's by truncation, v's each the nearest to
+//     what is left: k v = k1 v1 + k1 v2 + k2 v1 + k1 v3 + k2 v2 + k3 v1 leaves out
+//     k3 v2 + k2 v3 + k3 v3, at most 1.5 2^-23 of k v and of the sign of v2 and v3,
+//     which differs from column to column.  (With v cut off too it is 2^-21 and
+//     always in one direction, 6e-8 of a same-sign sum; with k rounded too, 2^-24
+//     for 6% of the launch.)  bfloat16 has float32's range, so no scaling is needed;
+//     the third part is normal, and the 24 bits whole, from about 2^-110 on.
 // Per 16 x 16 tile of entries that is KC + 3 RB MFMAs of 16 cycles and, per
 // entry, one multiplication, the exponential and 5.5 operations for the parts,
 // against 2 d + 16 RB vector operations and the library expf of the vector
@@ -404,18 +407,23 @@ __global__ __launch_bounds__(256) void main_kernel(const _Float16* __restrict__ 
         if (ch < JT * RP) sF[buf][c * kVS + jj] = v;
         continue;
       }
-      const uint32_t a = __float_as_uint(v);
-      const bool inf = (a & 0x7fffffffu) == 0x7f800000u;
-      const float r1 = inf ? 0.0f : v - __uint_as_float(a & 0xffff0000u);
-      const uint32_t b = __float_as_uint(r1);
-      const float r2 = r1 - __uint_as_float(b & 0xffff0000u);
-      if (inf) sInf = 1;
-      // a NaN whose set bits all lie in the low half would truncate to infinity
-      const uint32_t top = v != v ? 0x7fc00000u : a;
+      __bf16 v1 = (__bf16)v;
+      float r1 = v - (float)v1;
+      const uint32_t a = __float_as_uint(v) & 0x7fffffffu;
+      if (__builtin_expect(a >= 0x7f7f8000u, 0)) {
+        if (a == 0x7f800000u) {
+          r1 = 0.0f;
+          sInf = 1;
+        } else if (a < 0x7f800000u) {            // no infinite part of a finite value
+          v1 = __builtin_bit_cast(__bf16, (unsigned short)(__float_as_uint(v) >> 16));
+          r1 = v - (float)v1;
+        }
+      }
+      const __bf16 v2 = (__bf16)r1;
       const int at = c * kVS + jj;
-      sV[buf][0][at] = __builtin_bit_cast(__bf16, (unsigned short)(top >> 16));
-      sV[buf][1][at] = __builtin_bit_cast(__bf16, (unsigned short)(b >> 16));
-      sV[buf][2][at] = __builtin_bit_cast(__bf16, (unsigned short)(__float_as_uint(r2) >> 16));
+      sV[buf][0][at] = v1;
+      sV[buf][1][at] = v2;
+      sV[buf][2][at] = (__bf16)(r1 - (float)v2);
     }
   };
 
