@@ -330,7 +330,7 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
   p.nsplit16 = f16::choose_splits(p.n_pad, p.n_pad);
   p.nsplit32 = valu::choose_splits(n, n, d);
   p.f32_split = !p.fp16 && split::use(p.kp.kind, n, n, d, r);
-  if (p.f32_split) p.f32p = split::plan(n, n, d, r, true, 64, split::kSplitMaxRadius);
+  if (p.f32_split) p.f32p = split::plan(n, n, d, r, true, 64, split::kSplitProductRadius);
   p.nsplit64 = valu::choose_splits64(n, n, d);
   p.t64_split = p.o.true_res_every >= 0 && split::use64(p.kp.kind, n, d);
   if (p.t64_split) {

@@ -209,7 +209,7 @@ static gp_status kmvm_f32_split(const KParams& kp, const float* X1, int64_t n1, 
                                 hipStream_t s, const ScratchSource& src, bool* no_room) {
   const bool same = X1 == X2 && n1 == n2;
   int vsplit = valu::choose_splits(n1, n2, kp.d);
-  split::Plan p = split::plan(n1, n2, kp.d, r, same, 64, split::kSplitMaxRadius);
+  split::Plan p = split::plan(n1, n2, kp.d, r, same, 64, split::kSplitProductRadius);
   auto need = [&] {
     return split::operand_bytes(p, kp.d) + 512 +
            std::max(split::part_bytes(p), f32_bytes(n1, n2, r, 0, vsplit));

@@ -236,7 +236,13 @@ int choose_splits64(int64_t n1, int64_t n2, int d);
 namespace split {
 constexpr int kStageCols = 64;         // columns per LDS stage
 constexpr int kSplitMaxDim = 28;       // d + 4 slots of the first 32-wide chunk
+// the widest boxes (half diagonal in lengthscales): the gradient, whose other form
+// has larger errors throughout, and the true residual on fine operands ...
 constexpr float kSplitMaxRadius = 32.0f;
+// ... and the float32 product.  Its error against float64 is half the vector form's
+// where far entries weigh, the same where little but the diagonal is left, and within
+// 3% above it on clusters of sd 0.1 up to here (Matern, d >= 12: 5 to 15% at 31)
+constexpr float kSplitProductRadius = 20.0f;
 // smallest sets and smallest vector-form work n1 n2 (2 d + r + 12) (operations)
 // that take this form: its four extra launches cost about 20 us, which the
 // vector form's time passes from there on (N = 4000, d = 8, R = 16, work 7e8:

@@ -27,6 +27,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 #include "split_tile.h"
@@ -338,12 +339,12 @@ __device__ __forceinline__ void parts3(const float (&k)[8], b8 (&o)[3]) {
 // 4 g + v of its row, the four lanes of a row are added at the end, and the
 // partial sums are part[split][row][RT].
 template <int KIND, int KC, int RB, int RT>
-__global__ __launch_bounds__(256) void main_kernel(const _Float16* __restrict__ Xr,
+__global__ __launch_bounds__(256, 2) void main_kernel(const _Float16* __restrict__ Xr,
                                                    const _Float16* __restrict__ Xc,
                                                    const float* __restrict__ V, int r, int c0,
                                                    int64_t n2, float* __restrict__ part,
                                                    int64_t n1_pad, int nsplit, int64_t nstage,
-                                                   const Info* __restrict__ info,
+                                                   const Info* __restrict__ info, int same,
                                                    const int* __restrict__ live) {
   if (live && *live == 0) return;
   if (!info->ok) return;
@@ -440,76 +441,95 @@ __global__ __launch_bounds__(256) void main_kernel(const _Float16* __restrict__ 
     if (more) gload(st + 1);
     const bool has_inf = sInf != 0;
     const _Float16* X = sX[buf];
+    const int off = __builtin_amdgcn_readfirstlane((int)(row0 - st * JT));   // wave-uniform
+    auto columns = [&](auto diag) {
+      constexpr bool DIAG = decltype(diag)::value;
+      // the rare copy must not set the registers (R = 32, d = 12: 378 us, unrolled 549)
+      constexpr int kUnroll = DIAG && (RB == 2 || KC > 4) ? 1 : JT / 32;
+#pragma unroll kUnroll
+      for (int jb = 0; jb < JT / 32; ++jb) {
+        h8 a0[KC], a1[KC];
 #pragma unroll
-    for (int jb = 0; jb < JT / 32; ++jb) {
-      h8 a0[KC], a1[KC];
-#pragma unroll
-      for (int kc = 0; kc < KC; ++kc) {
-        a0[kc] = *reinterpret_cast<const h8*>(X + (jb * 32 + l16) * XS + kc * 32 + g * 8);
-        a1[kc] = *reinterpret_cast<const h8*>(X + (jb * 32 + 16 + l16) * XS + kc * 32 + g * 8);
-      }
-      f4 fv[RT ? RT : 1][2];
-#pragma unroll
-      for (int c = 0; c < RT; ++c)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          fv[c][h] = *reinterpret_cast<const f4*>(&sF[buf][c * kVS + jb * 32 + 16 * h + g * 4]);
-      b8 bv[RB ? RB : 1][3], bf[RB ? RB : 1];
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          const __bf16* vr = &sV[buf][p][(rb * 16 + l16) * kVS + jb * 32 + g * 4];
-          const b4 lo = *reinterpret_cast<const b4*>(vr);
-          const b4 hi = *reinterpret_cast<const b4*>(vr + 16);
-          bv[rb][p] = b8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        for (int kc = 0; kc < KC; ++kc) {
+          a0[kc] = *reinterpret_cast<const h8*>(X + (jb * 32 + l16) * XS + kc * 32 + g * 8);
+          a1[kc] = *reinterpret_cast<const h8*>(X + (jb * 32 + 16 + l16) * XS + kc * 32 + g * 8);
         }
-        bf[rb] = bv[rb][0];
-        if (has_inf) {
+        f4 fv[RT ? RT : 1][2];
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const unsigned short w = __builtin_bit_cast(unsigned short, bv[rb][0][e]);
-            if ((w & 0x7fff) == 0x7f80) bf[rb][e] = (__bf16)0.0f;
+        for (int c = 0; c < RT; ++c)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            fv[c][h] = *reinterpret_cast<const f4*>(&sF[buf][c * kVS + jb * 32 + 16 * h + g * 4]);
+        b8 bv[RB ? RB : 1][3], bf[RB ? RB : 1];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+          for (int p = 0; p < 3; ++p) {
+            const __bf16* vr = &sV[buf][p][(rb * 16 + l16) * kVS + jb * 32 + g * 4];
+            const b4 lo = *reinterpret_cast<const b4*>(vr);
+            const b4 hi = *reinterpret_cast<const b4*>(vr + 16);
+            bv[rb][p] = b8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+          }
+          bf[rb] = bv[rb][0];
+          if (has_inf) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const unsigned short w = __builtin_bit_cast(unsigned short, bv[rb][0][e]);
+              if ((w & 0x7fff) == 0x7f80) bf[rb][e] = (__bf16)0.0f;
+            }
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < NSUB; ++q) {
+          f4 s0 = sqdist<KC>(a0, bi[q]);
+          f4 s1 = sqdist<KC>(a1, bi[q]);
+          if constexpr (DIAG) {
+            // the diagonal's distance is 0, not its expansion's roundings
+            const int at = off + (q - 2 * jb) * 16 + l16 - 4 * g;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              s0[v] = at == v ? 0.0f : s0[v];
+              s1[v] = at - 16 == v ? 0.0f : s1[v];
+            }
+          }
+          float k[8];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            k[v] = kval<KIND>(s0[v], cs);
+            k[4 + v] = kval<KIND>(s1[v], cs);
+          }
+          if constexpr (RB == 0) {
+#pragma unroll
+            for (int c = 0; c < RT; ++c)
+#pragma unroll
+              for (int v = 0; v < 8; ++v) sum[q][c] = fmaf(k[v], fv[c][v / 4][v % 4], sum[q][c]);
+            continue;
+          }
+          b8 kp[3];
+          parts3(k, kp);
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) {
+            // 32 columns from zero, smallest products first, then one vector add:
+            // an MFMA cuts the low bits of products far below its accumulator, so
+            // a long chain on one accumulator falls short of a same-sign sum
+            // (2e-6 of it over 40,000 columns; 3% of the launch buys that back)
+            f4 t = f4{0.f, 0.f, 0.f, 0.f};
+            t = f16::mfma32<__bf16>(kp[2], bf[rb], t);
+            t = f16::mfma32<__bf16>(kp[1], bv[rb][1], t);
+            t = f16::mfma32<__bf16>(kp[0], bv[rb][2], t);
+            t = f16::mfma32<__bf16>(kp[1], bf[rb], t);
+            t = f16::mfma32<__bf16>(kp[0], bv[rb][1], t);
+            t = f16::mfma32<__bf16>(kp[0], bv[rb][0], t);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[q][rb][v] += t[v];
           }
         }
       }
-#pragma unroll
-      for (int q = 0; q < NSUB; ++q) {
-        const f4 s0 = sqdist<KC>(a0, bi[q]);
-        const f4 s1 = sqdist<KC>(a1, bi[q]);
-        float k[8];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          k[v] = kval<KIND>(s0[v], cs);
-          k[4 + v] = kval<KIND>(s1[v], cs);
-        }
-        if constexpr (RB == 0) {
-#pragma unroll
-          for (int c = 0; c < RT; ++c)
-#pragma unroll
-            for (int v = 0; v < 8; ++v) sum[q][c] = fmaf(k[v], fv[c][v / 4][v % 4], sum[q][c]);
-          continue;
-        }
-        b8 kp[3];
-        parts3(k, kp);
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          // 32 columns from zero, smallest products first, then one vector add:
-          // an MFMA cuts the low bits of products far below its accumulator, so
-          // a long chain on one accumulator falls short of a same-sign sum
-          // (2e-6 of it over 40,000 columns; 3% of the launch buys that back)
-          f4 t = f4{0.f, 0.f, 0.f, 0.f};
-          t = f16::mfma32<__bf16>(kp[2], bf[rb], t);
-          t = f16::mfma32<__bf16>(kp[1], bv[rb][1], t);
-          t = f16::mfma32<__bf16>(kp[0], bv[rb][2], t);
-          t = f16::mfma32<__bf16>(kp[1], bf[rb], t);
-          t = f16::mfma32<__bf16>(kp[0], bv[rb][1], t);
-          t = f16::mfma32<__bf16>(kp[0], bv[rb][0], t);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[q][rb][v] += t[v];
-        }
-      }
-    }
+    };
+    if (same && off > -JT * NSUB / 4 && off < JT)    // a stage that holds some of the wave's rows
+      columns(std::true_type{});
+    else
+      columns(std::false_type{});
     if (more) lstore(buf ^ 1);
     __syncthreads();
   }
@@ -558,7 +578,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
 // ---- host side ----------------------------------------------------------------
 // The instantiation's function for (kind, KC, RB).
 typedef void (*MainFn)(const _Float16*, const _Float16*, const float*, int, int, int64_t, float*,
-                       int64_t, int, int64_t, const Info*, const int*);
+                       int64_t, int, int64_t, const Info*, int, const int*);
 template <int KIND, int RB, int RT>
 static MainFn main_fn(int kc) {
   switch (kc) {
@@ -692,7 +712,7 @@ gp_status product(const Plan& p, const KParams& kp, const float* X1, int64_t n1,
     if (!fn) return set_error(GP_ERR_ARG, "internal: unsupported operand width %d", 32 * p.kc);
     fn<<<(unsigned)(p.n1_pad / rows * p.nsplit), 256, 0, s>>>(p.Xr, p.Xc, V, r, c0, n2, part,
                                                               p.n1_pad, p.nsplit, nstage, p.info,
-                                                              live);
+                                                              p.same ? 1 : 0, live);
     GP_HIP(hipGetLastError());
     reduce_kernel<<<(unsigned)ceil_div(n1 * rc, (int64_t)256), 256, 0, s>>>(
         part, p.nsplit, p.n1_pad, p.rp, vpart, vsplit, n1, r, c0, rc, kp.a2, kp.s2,

@@ -12,14 +12,16 @@
 // |a_i|^2 + |a_j|^2 - 2 a_i.a_j, which is what keeps a plain float32 (or
 // split) expansion from the accuracy of coordinate differences.  The bracket is
 // smaller by |f| / |q| ~ 2^-11, and the following MFMAs add it from f in two
-// binary16 parts and g = 2 q.f + |f|^2 in three.  Every one of them rounds at the
-// size of the sum so far, and q.f at up to 2^12 before it cancels: an entry's r^2
-// carries a few 2^-24 of itself and 1.2e-10 R^2.  Coordinate differences of the
-// float32 x / l carry 2 r |x / l| 2^-25, and their float32 sum d / 2 roundings, which
-// is more on ordinary points; on boxes wide enough to leave little but the
-// diagonal of K it is less, hence the radius limits of the callers.  u is chosen so
-// that the scale from r^2 / u^2 to the exponent's argument is a power of two: the
-// argument takes no further rounding, and no constant's.
+// binary16 parts and g = 2 q.f + |f|^2 in three, from zero, and the two sums are
+// added once.  (On top of the first sum every MFMA would round at its size: 1.1 to 3
+// times the error of sums of far entries.)  The remainder rounds at q.f's size, up to
+// 2^12 before it cancels: an entry's r^2 carries 2^-25 of itself and 1.2e-10 R^2.
+// Coordinate differences of the float32 x / l carry 2 r |x / l| 2^-25, and their
+// float32 sum d / 2 roundings: more on ordinary points, less for close ones on wide
+// boxes, hence the radius limits of the callers; a caller with one point set takes
+// the diagonal's distance as 0.  u is chosen so that the scale from r^2 / u^2 to the
+// exponent's argument is a power of two: the argument takes no further rounding, and
+// no constant's.
 // Not for Matern-1/2, whose value falls linearly in r at r = 0, where an
 // absolute error of r^2 would be magnified.
 //
@@ -64,9 +66,12 @@ using f16::h8;
 // a lane is column 4 g + v, row l16.
 template <int KC>
 __device__ __forceinline__ f4 sqdist(const h8 (&a)[KC], const h8 (&b)[KC]) {
-  f4 s = f4{0.f, 0.f, 0.f, 0.f};
+  const f4 z = f4{0.f, 0.f, 0.f, 0.f};
+  f4 s = f16::mfma32<_Float16>(a[0], b[0], z), t = z;
 #pragma unroll
-  for (int kc = 0; kc < KC; ++kc) s = f16::mfma32<_Float16>(a[kc], b[kc], s);
+  for (int kc = 1; kc < KC; ++kc) t = f16::mfma32<_Float16>(a[kc], b[kc], t);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) s[v] += t[v];
   return s;
 }
 
