@@ -51,11 +51,13 @@ struct Plan {
   int nsplit16;
   // fp32 product
   bool f32_split;                 // on the matrix cores (kmvm_split.hip) where the inputs' range allows
+  bool f32_known;                 // the range has been read back: it does
   split::Plan f32p;
   int nsplit32;
   int nsplit64;
   bool t64_split;                 // true residual on split operands (kmvm_split64.hip)
   bool t64_ready;                 // its operands are prepared
+  int nsplit64_max;               // of the two forms
   split::Plan t64p;
   int max_basis;
   // buffers
@@ -104,7 +106,7 @@ size_t plan_bytes(Plan& p, bool want_history) {
     add(4 * (size_t)p.nsplit32 * n * r);
   }
   add(4 * 64);                                 // column maxima of d
-  if (p.o.true_res_every >= 0) add(8 * (size_t)p.nsplit64 * n * r);
+  if (p.o.true_res_every >= 0) add(8 * (size_t)p.nsplit64_max * n * r);
   if (p.t64_split) b += split::operand_bytes(p.t64p, p.kp.d);
   add(4 * cg::kMaxBlocks * cg::kMaxR);
   add(4 * cg::kMaxBlocks * cg::kMaxR);
@@ -150,7 +152,7 @@ void plan_carve(Plan& p, Arena& a, bool want_history) {
     p.part32 = a.take<float>((size_t)p.nsplit32 * n * r);
   }
   p.colmax = a.take<uint32_t>(64);
-  p.part64 = p.o.true_res_every >= 0 ? a.take<double>((size_t)p.nsplit64 * n * r) : nullptr;
+  p.part64 = p.o.true_res_every >= 0 ? a.take<double>((size_t)p.nsplit64_max * n * r) : nullptr;
   if (p.t64_split && split::carve(p.t64p, p.kp.d, a) != GP_OK) return;
   p.pm = a.take<float>(cg::kMaxBlocks * cg::kMaxR);
   p.ps = a.take<float>(cg::kMaxBlocks * cg::kMaxR);
@@ -188,8 +190,8 @@ gp_status product(Plan& p, const float* v, float* out, const int* live, hipStrea
                               p.kp.s2, v, p.r, out, p.r, live, s);
   }
   if (p.f32_split)
-    return split::product(p.f32p, p.kp, p.X, p.n, p.X, p.n, v, p.r, p.part32, p.part32, p.nsplit32,
-                          true, out, live, s);
+    return split::product(p.f32p, p.kp, p.X, p.n, p.X, p.n, v, p.r, p.part32,
+                          p.f32_known ? nullptr : p.part32, p.nsplit32, true, out, live, s);
   GP_TRY(valu::launch_partial(p.kp, p.X, p.n, p.X, p.n, v, p.r, p.part32, false, p.nsplit32, live,
                               s));
   return valu::launch_reduce32(p.part32, p.nsplit32, p.n, p.r, p.kp.a2, p.kp.s2, v, out, live, s);
@@ -244,10 +246,9 @@ gp_status iteration(Plan& p, int it, hipStream_t s) {
 
 gp_status true_residual(Plan& p, hipStream_t s) {
   if (p.t64_split) {
-    if (!p.t64_ready)
-      GP_TRY(split::prepare(p.t64p, p.kp, p.X, p.n, p.X, p.n, s));
+    if (!p.t64_ready) GP_TRY(split::prepare(p.t64p, p.kp, p.X, p.n, p.X, p.n, s, true));
     p.t64_ready = true;
-    GP_TRY(split::partial64(p.t64p, p.kp, p.X, p.n, p.U, p.r, p.part64, p.nsplit64, s));
+    GP_TRY(split::partial64(p.t64p, p.kp, p.n, p.U, p.r, p.part64, p.nsplit64, s));
   } else {
     GP_TRY(valu::launch_partial(p.kp, p.X, p.n, p.X, p.n, p.U, p.r, p.part64, true, p.nsplit64,
                                 nullptr, s));
@@ -331,11 +332,13 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
   p.nsplit32 = valu::choose_splits(n, n, d);
   p.f32_split = !p.fp16 && split::use(p.kp.kind, n, n, d, r);
   if (p.f32_split) p.f32p = split::plan(n, n, d, r, true, 64, split::kSplitProductRadius);
-  p.nsplit64 = valu::choose_splits64(n, n, d);
+  const int vsplit64 = valu::choose_splits64(n, n, d);
+  p.nsplit64 = p.nsplit64_max = vsplit64;
   p.t64_split = p.o.true_res_every >= 0 && split::use64(p.kp.kind, n, d);
   if (p.t64_split) {
     p.t64p = split::plan(n, n, d, r, true, 64, split::kSplitMaxRadius, true);
     p.nsplit64 = split::choose_splits64(p.t64p, r);
+    p.nsplit64_max = std::max(p.nsplit64, vsplit64);
   }
   const bool want_history = stats && stats->history;
 
@@ -345,7 +348,7 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
     // the split operands do not fit: the vector forms need none
     clear_error();
     p.f32_split = p.t64_split = false;
-    p.nsplit64 = valu::choose_splits64(n, n, d);
+    p.nsplit64 = p.nsplit64_max = vsplit64;
     wst = workspace_get(s, plan_bytes(p, want_history), &ar);
   }
   if (wst == GP_ERR_NOMEM && p.sym) {
@@ -378,6 +381,8 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
   } else if (p.f32_split) {
     GP_TRY(split::prepare(p.f32p, p.kp, X, n, X, n, s));
   }
+  if (p.t64_split)
+    GP_TRY(split::measure(p.t64p, p.kp, X, n, X, n, s, p.f32_split ? p.f32p.box : nullptr));
   if (p.o.x0_given) {
     GP_TRY(quantise(p, U, false, nullptr, s));
     GP_TRY(product(p, U, p.q, nullptr, s));
@@ -393,7 +398,19 @@ extern "C" gp_status gp_cg_solve(const gp_kernel* k, const float* X, int64_t n, 
   // ---- iterations ----
   cg::State hs;
   GP_HIP(hipMemcpyAsync(&hs, p.st, sizeof hs, hipMemcpyDeviceToHost, s));
+  int f32_ok = 0, t64_ok = 0;
+  if (p.f32_split)
+    GP_HIP(hipMemcpyAsync(&f32_ok, &p.f32p.info->ok, sizeof f32_ok, hipMemcpyDeviceToHost, s));
+  if (p.t64_split)
+    GP_HIP(hipMemcpyAsync(&t64_ok, &p.t64p.info->ok, sizeof t64_ok, hipMemcpyDeviceToHost, s));
   GP_HIP(hipStreamSynchronize(s));
+  // whether the points' range allows the split forms: from here on only the form
+  // that runs is launched, at its own split count
+  p.f32_split = p.f32_known = p.f32_split && f32_ok;
+  if (p.t64_split && !t64_ok) {
+    p.t64_split = false;
+    p.nsplit64 = vsplit64;
+  }
   // periodic true residuals: row j after (j + 1) * every launched iterations
   const int every = p.o.true_res_every;
   const int trows = every > 0 ? p.o.max_iter / every : 0;

@@ -286,25 +286,28 @@ Plan plan(int64_t n1, int64_t n2, int d, int r, bool same, int most_splits, floa
 size_t operand_bytes(const Plan& p, int d);
 size_t part_bytes(const Plan& p);
 gp_status carve(Plan& p, int d, Arena& ar);
-// operands of both sets (once per point set)
+// box, unit and Info of both sets (box: of the same sets, from another plan's
+// measure); then their operands too (once per point set)
+gp_status measure(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
+                  int64_t n2, hipStream_t s, const float* box = nullptr);
 gp_status prepare(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
-                  int64_t n2, hipStream_t s);
+                  int64_t n2, hipStream_t s, bool measured = false);
 // out = a2 K V (+ s2 V); vpart (vsplit x n1 x r) takes the vector form's sums
-// when the inputs' range rules this form out.
+// when the inputs' range rules this form out (null: it is known not to).
 gp_status product(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
                   int64_t n2, const float* V, int r, float* part, float* vpart, int vsplit,
                   bool add_noise, float* out, const int* live, hipStream_t s);
 // Float64-accumulated sums of one point set (kmvm_split64.hip): part[split][i][c]
-// = sum over the split's columns of k(x_i, x_j) V_jc; the vector form's layout,
-// which it writes itself when the inputs' range rules this form out.
+// = sum over the split's columns of k(x_i, x_j) V_jc, the vector form's layout;
+// the inputs' range is known to allow it.
 // from this many points: preparing the operands costs about 20 us, what the
 // cheaper distances save at N = 6000 (R = 5: 64 us against 75 at N = 5000, 459
 // against 168 at N = 20,000, R = 1)
 constexpr int64_t kSplit64MinPoints = 8192;
 bool use64(int kind, int64_t n, int d);
 int choose_splits64(const Plan& p, int r);
-gp_status partial64(const Plan& p, const KParams& kp, const float* X, int64_t n, const float* V,
-                    int r, double* part, int nsplit, hipStream_t s);
+gp_status partial64(const Plan& p, const KParams& kp, int64_t n, const float* V, int r,
+                    double* part, int nsplit, hipStream_t s);
 }  // namespace split
 
 // ---------------------------------------------------------------------------

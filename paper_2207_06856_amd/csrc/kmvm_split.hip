@@ -671,8 +671,8 @@ gp_status carve(Plan& p, int d, Arena& ar) {
   return GP_OK;
 }
 
-gp_status prepare(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
-                  int64_t n2, hipStream_t s) {
+gp_status measure(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
+                  int64_t n2, hipStream_t s, const float* box) {
   // v_sqrt_f32 falls short of the root by 1.2e-8 of it on average (16M arguments
   // in [1, 4), worst 9.3e-8), which every entry of a Matern sum would share:
   // its argument is raised by twice that
@@ -681,11 +681,19 @@ gp_status prepare(const Plan& p, const KParams& kp, const float* X1, int64_t n1,
                          ? -0.5 * kLog2e
                          : (kp.kind == GP_KERNEL_MATERN52 ? 5.0 : 3.0) * kLog2e * kLog2e *
                                (1.0 + 2.0 * kSqrtBias);
-  box_kernel<<<(unsigned)(p.groups1 + p.groups2), 256, 0, s>>>(X1, n1, X2, n2, kp.d, p.groups1,
-                                                               p.box);
+  if (!box) {
+    box_kernel<<<(unsigned)(p.groups1 + p.groups2), 256, 0, s>>>(X1, n1, X2, n2, kp.d, p.groups1,
+                                                                 p.box);
+    GP_HIP(hipGetLastError());
+  }
+  info_kernel<<<1, 256, 0, s>>>(box ? box : p.box, p.groups1 + p.groups2, kp, arg, p.radius, p.info);
   GP_HIP(hipGetLastError());
-  info_kernel<<<1, 256, 0, s>>>(p.box, p.groups1 + p.groups2, kp, arg, p.radius, p.info);
-  GP_HIP(hipGetLastError());
+  return GP_OK;
+}
+
+gp_status prepare(const Plan& p, const KParams& kp, const float* X1, int64_t n1, const float* X2,
+                  int64_t n2, hipStream_t s, bool measured) {
+  if (!measured) GP_TRY(measure(p, kp, X1, n1, X2, n2, s));
   const int w = 32 * p.kc;
   const auto prep = p.fine ? &prep_fine_kernel : &prep_kernel;
   prep<<<(unsigned)ceil_div(p.n1_pad, (int64_t)kPrepPoints), 256, 0, s>>>(
@@ -704,8 +712,9 @@ gp_status product(const Plan& p, const KParams& kp, const float* X1, int64_t n1,
                   bool add_noise, float* out, const int* live, hipStream_t s) {
   const int rows = 64 * subtiles(p.kc);
   const int64_t nstage = p.n2_pad / JT;
-  GP_TRY(valu::launch_partial(kp, X1, n1, X2, n2, V, r, vpart, false, vsplit, live, s,
-                              &p.info->ok));
+  if (vpart)
+    GP_TRY(valu::launch_partial(kp, X1, n1, X2, n2, V, r, vpart, false, vsplit, live, s,
+                                &p.info->ok));
   for (int c0 = 0; c0 < r; c0 += p.rp) {
     const int rc = std::min(p.rp, r - c0);
     const MainFn fn = main_fn(kp.kind, p.kc, p.rp);

@@ -201,9 +201,8 @@ static F64Fn f64_fn(int kc, int rt) {
 // Right-hand sides of one FMA launch, 0 for the 16-wide MFMA form.
 static int fma_rhs(int r) { return r == 1 ? 1 : r <= 4 ? 4 : r <= 8 ? 8 : 0; }
 
-gp_status partial64(const Plan& p, const KParams& kp, const float* X, int64_t n, const float* V,
-                    int r, double* part, int nsplit, hipStream_t s) {
-  GP_TRY(valu::launch_partial(kp, X, n, X, n, V, r, part, true, nsplit, nullptr, s, &p.info->ok));
+gp_status partial64(const Plan& p, const KParams& kp, int64_t n, const float* V, int r,
+                    double* part, int nsplit, hipStream_t s) {
   const int rt = fma_rhs(r), step = rt ? rt : 16;
   const F64Fn fn = kp.kind == GP_KERNEL_RBF        ? f64_fn<GP_KERNEL_RBF>(p.kc, rt)
                    : kp.kind == GP_KERNEL_MATERN52 ? f64_fn<GP_KERNEL_MATERN52>(p.kc, rt)
