@@ -300,9 +300,11 @@ gp_status product(const Plan& p, const KParams& kp, const float* X1, int64_t n1,
 // Float64-accumulated sums of one point set (kmvm_split64.hip): part[split][i][c]
 // = sum over the split's columns of k(x_i, x_j) V_jc, the vector form's layout;
 // the inputs' range is known to allow it.
-// from this many points: preparing the operands costs about 20 us, what the
-// cheaper distances save at N = 6000 (R = 5: 64 us against 75 at N = 5000, 459
-// against 168 at N = 20,000, R = 1)
+// from this many points, where one right-hand side pays for the operands' 20 us.  One
+// residual on float64 distances against one on the operands: N = 8200: 85 us and 79
+// (d = 3, R = 1), 98 and 114 (d = 8, R = 5), 104 and 123 (d = 8, R = 16); N = 10,000:
+// 117 and 82, 132 and 127, 138 and 141; N = 20,000: 374 and 158, 428 and 299, 443 and
+// 396; N = 40,000: 1344 and 453, 1536 and 947, 1546 and 1307
 constexpr int64_t kSplit64MinPoints = 8192;
 bool use64(int kind, int64_t n, int d);
 int choose_splits64(const Plan& p, int r);

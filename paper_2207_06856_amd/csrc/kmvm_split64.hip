@@ -17,7 +17,6 @@
 // float64 FMAs instead, R of them per entry rather than 16.
 
 #include <algorithm>
-#include <type_traits>
 
 #include "split_tile.h"
 
@@ -102,55 +101,73 @@ __global__ __launch_bounds__(256) void f64_kernel(const _Float16* __restrict__ X
     if (more) gload(st + 1);
     const _Float16* X = sX[buf];
     const double* Vs = sV[buf];
-    const int off = __builtin_amdgcn_readfirstlane((int)(row0 - st * JT));   // wave-uniform
-    auto columns = [&](auto diag) {
-      constexpr bool DIAG = decltype(diag)::value;
 #pragma unroll 1
-      for (int jb = 0; jb < JT / 16; ++jb) {
-        h8 a[KC];
+    for (int jb = 0; jb < JT / 16; ++jb) {
+      h8 a[KC];
 #pragma unroll
-        for (int kc = 0; kc < KC; ++kc)
-          a[kc] = *reinterpret_cast<const h8*>(X + (jb * 16 + l16) * XS + kc * 32 + g * 8);
-        float k[NSUB][4];
+      for (int kc = 0; kc < KC; ++kc)
+        a[kc] = *reinterpret_cast<const h8*>(X + (jb * 16 + l16) * XS + kc * 32 + g * 8);
+      float k[NSUB][4];
 #pragma unroll
-        for (int q = 0; q < NSUB; ++q) {
-          f4 s = sqdist_fine<KC>(a, bi[q]);
-          // the diagonal's distance is 0, not the rounding of T (a Matern value near
-          // t = 0 rounds to 3e-8 of 1)
-          if (DIAG && off == (jb - q) * 16)
+      for (int q = 0; q < NSUB; ++q) {
+        const f4 s = sqdist_fine<KC>(a, bi[q]);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) s[v] = l16 == 4 * g + v ? 0.0f : s[v];
+        for (int v = 0; v < 4; ++v) k[q][v] = kval<KIND>(s[v], cs);
+      }
 #pragma unroll
-          for (int v = 0; v < 4; ++v) k[q][v] = kval<KIND>(s[v], cs);
-        }
+      for (int v = 0; v < 4; ++v) {
+        const double* vr = Vs + (jb * 16 + 4 * g + v) * RW;
+        if constexpr (RT == 0) {
+          const double b = vr[l16];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const double* vr = Vs + (jb * 16 + 4 * g + v) * RW;
-          if constexpr (RT == 0) {
-            const double b = vr[l16];
+          for (int q = 0; q < NSUB; ++q)
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)k[q][v], b, acc[q], 0, 0, 0);
+        } else {
+          double b[RT ? RT : 1];
 #pragma unroll
-            for (int q = 0; q < NSUB; ++q)
-              acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)k[q][v], b, acc[q], 0, 0, 0);
-          } else {
-            double b[RT ? RT : 1];
+          for (int c = 0; c < RT; ++c) b[c] = vr[c];
 #pragma unroll
-            for (int c = 0; c < RT; ++c) b[c] = vr[c];
+          for (int q = 0; q < NSUB; ++q) {
+            const double kd = (double)k[q][v];
 #pragma unroll
-            for (int q = 0; q < NSUB; ++q) {
-              const double kd = (double)k[q][v];
-#pragma unroll
-              for (int c = 0; c < RT; ++c) sum[q][c] = fma(kd, b[c], sum[q][c]);
-            }
+            for (int c = 0; c < RT; ++c) sum[q][c] = fma(kd, b[c], sum[q][c]);
           }
         }
       }
-    };
-    if (off > -JT && off < JT)                   // a stage that holds some of the wave's rows
-      columns(std::true_type{});
-    else
-      columns(std::false_type{});
+    }
     if (more) lstore(buf ^ 1);
     __syncthreads();
+  }
+  // The diagonal's entry is 1, not the kernel of T's rounding (a Matern value near 0
+  // rounds to 3e-8 of 1): the split that summed it adds (1 - k) v, k from the same
+  // operations.  (A second loop for the stages that hold the wave's rows took the
+  // registers of the right-hand sides' sums: one wave per SIMD at d <= 10 with five to
+  // eight of them, 1.49 ms a residual at N = 40,000, d = 8, R = 5, for 0.95 ms.)
+#pragma unroll
+  for (int q = 0; q < NSUB; ++q) {
+    const int64_t i0 = row0 + q * 16;
+    if (i0 >= n1 || i0 / JT < sb || i0 / JT >= se) continue;    // wave-uniform
+    h8 a[KC];
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+      a[kc] = *reinterpret_cast<const h8*>(Xc + (i0 + l16) * KP + kc * 32 + g * 8);
+    const f4 s = sqdist_fine<KC>(a, bi[q]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t j = i0 + 4 * g + v;
+      const double e = l16 == 4 * g + v ? 1.0 - (double)kval<KIND>(s[v], cs) : 0.0;
+      // nothing to add to a sum that is not finite
+      auto rhs = [&](int c) {
+        const float x = j < n2 && c < rc ? V[j * r + c0 + c] : 0.0f;
+        return isfinite(x) ? (double)x : 0.0;
+      };
+      if constexpr (RT == 0) {
+        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(e, rhs(l16), acc[q], 0, 0, 0);
+      } else if (l16 == 4 * g + v) {
+#pragma unroll
+        for (int c = 0; c < RT; ++c) sum[q][c] = fma(e, rhs(c), sum[q][c]);
+      }
+    }
   }
   double* P = part + (int64_t)split * n1 * r;
 #pragma unroll

@@ -95,3 +95,11 @@ def test_little_left_of_the_residual_matern(gpu_lib, kind, r):
     c = np.random.default_rng(340).permutation(1 << 16)[:8400]
     X = np.where((c[:, None] >> np.arange(16)) & 1, 7.5, -7.5).astype(np.float32)
     check_little_left(gpu_lib, X, kind, r)
+
+
+# one and five to eight right-hand sides: the diagonal's correction of each sum's form
+@pytest.mark.parametrize("kind,r,n", [(1, 8, 8400), (3, 1, 8193), (1, 5, 8447)])
+def test_little_left_of_the_residual_matern_few(gpu_lib, kind, r, n):
+    c = np.random.default_rng(341).permutation(1 << 16)[:n]
+    X = np.where((c[:, None] >> np.arange(16)) & 1, 7.5, -7.5).astype(np.float32)
+    check_little_left(gpu_lib, X, kind, r)
