@@ -403,16 +403,14 @@ def serve_stream_measurement(gpmi, count, progress_s=30.0):
             "peak_arena_gb": round(st["peak_bytes"] / 1e9, 2)}
 
 
-# Vector instructions per evaluated entry of the gradient reduction's inner
-# loop (gfx950 assembly: 245 vector instructions and 3 float32 MFMAs per 8
-# entries a lane, for d = 8 with ARD): per input dimension a difference, a
-# square and the accumulation, the RBF value, the W entry, kappa W, G W and the
-# clamp of r^2.  With the symmetric tiling an entry (i, j) past the diagonal
-# block stands for (j, i) as well, so about half of the N^2 logical entries
-# are evaluated.  The roofline is the vector issue rate: 256 CUs x 4 SIMDs x
-# 16 lanes x 2.4 GHz = 39.3 T lane-instructions/s (no packed FP32).
-GRAD_VALU_PER_ENTRY_D8 = 245 / 8
-PEAK_LANE_INSTR_PER_S = 256 * 4 * 16 * 2.4e9
+# Matrix-core cycles of the gradient reduction per 256 evaluated entries at d = 8 with
+# ARD and 16 right-hand sides: four float64 MFMAs of 64 cycles (the sums of P b and
+# P b^2), three binary16 MFMAs of 16 cycles for r^2 and three for W + W^T.  Nothing
+# else issues beside the float64 ones, and the vector work of the entries comes on
+# top.  With the symmetric tiling an entry (i, j) past the diagonal block stands for
+# (j, i) as well, so about half of the N^2 logical entries are evaluated.
+GRAD_MFMA_CYCLES_D8 = 4 * 64 + 6 * 16
+SIMD_CYCLES_PER_S = 256 * 4 * 2.4e9
 
 
 def grad_evaluated_entries(n, d):
@@ -465,7 +463,7 @@ def training_measurement(gpmi, torch, dev, steps=8):
     grad_ms = ev[0].elapsed_time(ev[1]) / reps
     entries = float(n) * float(n)
     evaluated = grad_evaluated_entries(n, d)
-    lane_instr = evaluated * GRAD_VALU_PER_ENTRY_D8 / (grad_ms / 1e3)
+    simd_cycles = SIMD_CYCLES_PER_S * (grad_ms / 1e3) / (evaluated / 256)
     sec = lambda k: float(np.median([i[k] for i in infos]) * 1e3)
     return {"workload": f"App. C training: N={n}, d={d}, RBF-ARD, {M} probes, rank {RANK}, "
                         "binary16 product, CG tol 1.0 (10..50 iterations), priors, Adam 0.1",
@@ -479,11 +477,10 @@ def training_measurement(gpmi, torch, dev, steps=8):
             "grad_kernel": {"avg_ms": round(grad_ms, 3),
                             "logical_gentries_per_s": round(entries / (grad_ms / 1e3) / 1e9, 1),
                             "evaluated_entries": evaluated,
-                            "bound": "alu",
-                            "achieved_lane_instr_per_s": round(lane_instr, -9),
-                            "peak_lane_instr_per_s": PEAK_LANE_INSTR_PER_S,
-                            "frac": round(lane_instr / PEAK_LANE_INSTR_PER_S, 4),
-                            "valu_instr_per_evaluated_entry": round(GRAD_VALU_PER_ENTRY_D8, 3)}}
+                            "bound": "issue",
+                            "simd_cycles_per_256_entries": round(simd_cycles, 1),
+                            "mfma_cycles_per_256_entries": GRAD_MFMA_CYCLES_D8,
+                            "frac": round(GRAD_MFMA_CYCLES_D8 / simd_cycles, 4)}}
 
 
 def truncation_measurement(gpmi, torch, dev, reps=3):

@@ -627,8 +627,9 @@ gp_status gp_tune_set(const gp_tune_info* in);
  *        the rows adds up to it, which is how the sum shards)
  *  grad  HOST array of L + 3 doubles: dL/dl_1..dL/dl_L, dL/da^2, dL/ds^2 and,
  *        last, 1/2 y^T u_0 over the row range (the data-fit half of Eq. loss).
- * The kernel's entries are float32 (no binary16 rounding); every sum is
- * combined in float64 in a fixed order, so results are deterministic.
+ * The kernel's entries are float32; U and C enter W in two binary16 parts each
+ * (22 bits).  Every sum is combined in float64 in a fixed order, so results are
+ * deterministic.
  * Synchronises `stream`.  Errors: GP_ERR_ARG, GP_ERR_NOMEM, GP_ERR_HIP.
  */
 gp_status gp_mll_grad(const gp_kernel* k, const float* X, int64_t n, int32_t d, const float* B,

@@ -1135,10 +1135,10 @@ __global__ __launch_bounds__(256) void pc_step_kernel(const Seg* __restrict__ se
 // tb)); the (tb, ta) tile is its mirror image (the products commute, so the
 // mirrored sums are the same numbers).  On the float64 matrix cores: lane (row or
 // column l % 16, group l / 16) of wave w takes rows 8 (16 s + w) + 2 (l / 16) and
-// the next of every step s, two loads of 16 bytes and two MFMAs, eight steps in
-// flight, with no LDS and no barrier before the waves' sums are added.  Through
-// LDS with 256 threads a tile's chain over its problem's rows was the whole
-// launch: 537 us at 20,000 rows, 147 now (one work group reads a whole factor).
+// the next of every step s, 8-byte loads and two MFMAs, four steps in flight, with
+// no LDS and no barrier before the waves' sums are added.  Through LDS with 256
+// threads a tile's chain over its problem's rows was the whole launch: 537 us at
+// 20,000 rows, 147 now (one work group reads a whole factor).
 constexpr int kSyrkThreads = 1024;
 __global__ __launch_bounds__(kSyrkThreads) void pc_syrk_kernel(const Seg* __restrict__ segs,
                                                                const PcState* __restrict__ ps,

@@ -245,9 +245,10 @@ constexpr float kSplitMaxRadius = 32.0f;
 constexpr float kSplitProductRadius = 20.0f;
 // smallest sets and smallest vector-form work n1 n2 (2 d + r + 12) (operations)
 // that take this form: its four extra launches cost about 20 us, which the
-// vector form's time passes from there on (N = 4000, d = 8, R = 16, work 7e8:
-// 44 us against 41; N = 8000, d = 3, R = 1, work 1.2e9: 48 against 40; 500 x
-// 20000, d = 8, R = 16, work 4e8: 56 against 63)
+// vector form's time passes near there.  Vector form and this one: N = 3000, d = 8,
+// R = 16 (work 4e8): 36 us and 44; N = 4000 (7e8): 47 and 44; N = 5000 (1.1e9): 95 and
+// 52; N = 6000, d = 3, R = 1 (7e8): 48 and 38; N = 9000 (1.5e9): 90 and 48; 500 x
+// 20,000, d = 8, R = 16 (4e8): 56 and 65; 60,000 x 400, d = 5, R = 8 (7e8): 62 and 67
 constexpr int64_t kSplitMinRows = 256;
 constexpr double kSplitMinWork = 1073741824.0;
 // Scale data of a prepared point set, written on the device.

@@ -12,16 +12,17 @@
 //     for 6% of the launch.)  bfloat16 has float32's range, so no scaling is needed;
 //     the third part is normal, and the 24 bits whole, from about 2^-110 on.
 // Per 16 x 16 tile of entries that is KC + 3 RB MFMAs of 16 cycles and, per
-// entry, one multiplication, the exponential and 5.5 operations for the parts,
-// against 2 d + 16 RB vector operations and the library expf of the vector
-// form.  With at most four right-hand sides the parts cost more than the sums
-// they feed, and each lane adds its entries' products by float32 FMAs instead.
-// Bound by issue: at N = 40,011, d = 8, R = 16 (RBF) the launch takes 275 cycles
+// entry, the addition of the distance's two sums, one multiplication, the
+// exponential and 5.5 operations for the parts, against 2 d + 16 RB vector
+// operations and the library expf of the vector form.  With at most four
+// right-hand sides the parts cost more than the sums they feed, and each lane adds
+// its entries' products by float32 FMAs instead.
+// Bound by issue: at N = 40,011, d = 8, R = 16 (RBF) the launch takes 285 cycles
 // of a SIMD per 256 entries, where the matrix cores' 96 and the vector unit's
-// 141 add up to 237.  Product calls there, against the vector form: 0.70 ms
-// from 1.85 (d = 8, R = 16), 0.28 from 1.02 (d = 3, R = 1), 1.08 from 3.55
-// (Matern-5/2, d = 16, R = 16), 1.42 from 7.00 (d = 12, R = 32); the relative
-// error against float64 falls from 7.3e-7 to 5.0e-7, because a lane's chain of
+// 157 add up to 253.  Product calls there, against the vector form: 0.76 ms
+// from 1.85 (d = 8, R = 16), 0.31 from 1.02 (d = 3, R = 1), 1.14 from 3.55
+// (Matern-5/2, d = 16, R = 16); N = 20,000: 0.38 from 1.75 (d = 12, R = 32).  The
+// relative error against float64 falls from 7.3e-7 to 3.9e-7: a lane's chain of
 // sums is a thirty-second as long.
 
 #include <math.h>
@@ -614,8 +615,8 @@ bool use(int kind, int64_t n1, int64_t n2, int d, int r) {
          n2 >= kSplitMinRows && (double)n1 * (double)n2 * (2 * d + r + 12) >= kSplitMinWork;
 }
 
-// Work groups resident per compute unit: the 160 KB of LDS, and the registers
-// of the instantiations (three waves per SIMD).
+// Work groups resident per compute unit: the 160 KB of LDS, and three waves per SIMD
+// (two of the widest instantiations' registers: their grids' rounds are then a guess).
 constexpr int kCus = 256;
 static int groups_per_cu(int kc, int rb) {
   const int lds = 2 * (2 * JT * (32 * kc + 8) + 3 * 2 * 16 * rb * kVS);

@@ -14,7 +14,10 @@
 // the columns {4 g + v}: A is the entry, B the right-hand side l16 of that
 // column.  That MFMA is 16 wide in right-hand sides and runs at the vector
 // unit's float64 rate, so up to eight right-hand sides (RT > 0) are summed by
-// float64 FMAs instead, R of them per entry rather than 16.
+// float64 FMAs instead, R of them per entry rather than 16.  One residual on the
+// float64 distances and on these: N = 100,000, d = 8, R = 16 9.75 ms and 7.60 (5.95
+// of them the product MFMAs); N = 40,000, d = 8, R = 5 1.54 and 0.95, R = 1 1.53 and
+// 0.50.
 
 #include <algorithm>
 

@@ -281,7 +281,7 @@ __global__ void to_f32_kernel(const double* __restrict__ a, float* __restrict__ 
 // writes a k x r float32 partial; lt_sum adds the chunk partials in chunk order
 // in float64 (four threads per entry, fixed split, fixed combination) and
 // lt_solve applies C^{-1} in float64 (Y = C^{-1} T, stored as float32 for the
-// second product).  z = s^-2 w - s^-4 L Y with one thread per row.
+// second product).  z = s^-2 w - s^-4 L Y with two threads per row.
 // The chunk count stops at twice the CU count (the chunks also fix how the
 // float32 partials group the rows, so the count does not follow the occupancy):
 // one round of longer chunks instead of a second, partly empty round.

@@ -2,7 +2,7 @@
 // by the single-problem and batched kernels:
 //   T = L^T w   skinny product with a huge reduction dimension, on the
 //               float32 matrix cores (v_mfma_f32_16x16x4f32);
-//   z = s^-2 w - s^-4 L Y   one thread per row, Y staged in LDS.
+//   z = s^-2 w - s^-4 L Y   two threads per row, Y staged in LDS.
 // L is rank x n (each pivot column contiguous), w and z are n x r.
 #pragma once
 
